@@ -292,6 +292,21 @@ __global__ __launch_bounds__(256) void k_gather_rows(int64_t n, const int32_t *_
   dst[f] = k < src_cols ? src[(size_t)perm[i] * src_stride + k] : 0.0f;
 }
 
+// Z-ordered colour records in the layout of the march's matrix operands:
+// [channel][k][q] of coefficient m = 4q + k, zero past the degree, so that one
+// 16-byte read gives a lane its coefficients of all four inner steps.
+__global__ __launch_bounds__(256) void k_pack_colour(int64_t n, const int32_t *__restrict__ counters,
+                                                     const uint32_t *__restrict__ perm,
+                                                     const float *__restrict__ sh, int sh_k,
+                                                     float *__restrict__ col) {
+  const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = f / kColFloats;
+  const int e = (int)(f - i * kColFloats);
+  if (i >= n || i >= counters[0]) return;
+  const int ch = e >> 4, m = 4 * (e & 3) + ((e >> 2) & 3);
+  col[f] = m < sh_k ? sh[((size_t)perm[i] * sh_k + m) * 3 + ch] : 0.0f;
+}
+
 // Node boxes without inter-thread synchronisation: a segment tree (heap
 // layout, P leaves, P a power of two) over the Z-ordered leaf boxes gives the
 // union of any leaf range in O(log P) reads; every internal node's child
@@ -498,9 +513,7 @@ hipError_t launch_build(const BuildArgs &a, hipStream_t st) {
   k_gather_rows<<<nblk(n * kAuxFloats, 256), 256, 0, st>>>(n, a.counters, perm, a.aux_user,
                                                            kAuxFloats, kAuxFloats, a.aux,
                                                            kAuxFloats);
-  k_gather_rows<<<nblk(n * a.col_stride, 256), 256, 0, st>>>(n, a.counters, perm, a.sh,
-                                                             3 * a.sh_k, 3 * a.sh_k, a.col,
-                                                             a.col_stride);
+  k_pack_colour<<<nblk(n * kColFloats, 256), 256, 0, st>>>(n, a.counters, perm, a.sh, a.sh_k, a.col);
   if (a.n_sg > 0) {
     k_sg_pack<<<nblk(n, 256), 256, 0, st>>>(n, a.n_sg, a.sg, a.sg_user);
     k_gather_rows<<<nblk(n * kSgFloats, 256), 256, 0, st>>>(n, a.counters, perm, a.sg_user,

@@ -10,8 +10,12 @@ constexpr int kBlock = 256;               // 4 waves, each owning its own 64-ray
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxViewsPerLaunch = 24;    // view table travels as a kernel argument
 constexpr int kGeomFloats = 16;           // packed geometry record (64 B)
-constexpr int kAccFloats = 64;            // per-Gaussian gradient accumulator (256 B)
-constexpr int kColFloats = 48;            // colour record: 3 x 16 SH coefficients, zero past the degree
+// Per-Gaussian gradient accumulator (256 B): slots 0..2 first moment of dq
+// over the local offsets z, 3..8 second moment (xx xy xz yy yz zz), 9 sum of
+// w dL/dw, 16.. SH coefficients [channel][16].
+constexpr int kAccFloats = 64;
+constexpr int kColFloats = 48;            // colour record: 3 channels x 16 SH coefficients, zero past the degree,
+                                          // [channel][k][q] for coefficient 4q + k
 // 4-wide node record: 4 child boxes (lo xyz, hi xyz), 4 child links (>= 0
 // 4-wide node, < 0 leaf ~j, kNoChild none), 4 leaf ranges (first, last).
 constexpr int kNode4Floats = 36;
@@ -116,7 +120,9 @@ __device__ __forceinline__ float uniform_float(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
+// (the builtin takes the lane mask as it is; __ballot makes an integer of the
+// predicate and compares it again, two vector instructions a call)
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 // Real SH basis (Condon-Shortley phase, index l^2+l+m) at a unit direction,
 // as polynomials in (x, y, z) for degrees 0..3; entries m >= k are zero.

@@ -11,9 +11,10 @@
 // several segments and its memory latency is spread over 64 independent node
 // fetches per round.  A window too large for the list is processed in Z-index
 // chunks: the walk pauses when the list is full and resumes after the chunk.
-// The geometry of 64 list entries is fetched at once, one entry per lane, and
-// handed to each candidate with readlane; colour records are read at
-// wave-uniform addresses through the scalar cache.  Closest-hit restarts
+// The geometry of 64 list entries is fetched at once, one entry per lane; each
+// group of four candidates takes its ray directions from the matrix cores and
+// the rest with readlane (for_each_candidate).  The forward reads colour
+// records at wave-uniform addresses through the scalar cache.  Closest-hit restarts
 // beyond the window use a depth-first packet traversal, nearer child first.
 //
 // Every ray meets its Gaussians in Z-index order (window lists and their
@@ -101,7 +102,7 @@ __device__ __forceinline__ Gauss load_gauss(const float *geom, int j) {
 // closest approach; the chord is t* -/+ sqrt((k^2 - h^2) / A).
 struct Chord {
   float A, ts, h2, tin, tout;
-  bool exists;
+  bool exists;   // (chord_local, chord)
 };
 
 // The ray in the Gaussian's local frame (g carries the origin, with_origin).
@@ -115,9 +116,9 @@ __device__ __forceinline__ void ray_local(const Gauss &g, const Ray &r, float &o
   dpz = fmaf(g.m[6], r.dx, fmaf(g.m[7], r.dy, g.m[8] * r.dz));
 }
 
-__device__ __forceinline__ Chord chord(const Gauss &g, const Ray &r) {
-  float opx, opy, opz, dpx, dpy, dpz;
-  ray_local(g, r, opx, opy, opz, dpx, dpy, dpz);
+// From the ray's local-frame origin (opx, opy, opz) and direction.
+__device__ __forceinline__ Chord chord_local(float opx, float opy, float opz, float dpx, float dpy,
+                                             float dpz, float k2) {
   Chord c;
   c.A = fmaf(dpx, dpx, fmaf(dpy, dpy, dpz * dpz));
   const float B = fmaf(opx, dpx, fmaf(opy, dpy, opz * dpz));
@@ -125,15 +126,21 @@ __device__ __forceinline__ Chord chord(const Gauss &g, const Ray &r) {
   c.ts = -B * rA;
   const float px = fmaf(c.ts, dpx, opx), py = fmaf(c.ts, dpy, opy), pz = fmaf(c.ts, dpz, opz);
   c.h2 = fmaf(px, px, fmaf(py, py, pz * pz));
-  c.exists = c.h2 <= g.k2;
-  const float w = __builtin_amdgcn_sqrtf(fmaxf(g.k2 - c.h2, 0.0f) * rA);
+  c.exists = c.h2 <= k2;
+  const float w = __builtin_amdgcn_sqrtf(fmaxf(k2 - c.h2, 0.0f) * rA);
   c.tin = c.ts - w;
   c.tout = c.ts + w;
   return c;
 }
 
+__device__ __forceinline__ Chord chord(const Gauss &g, const Ray &r) {
+  float opx, opy, opz, dpx, dpy, dpz;
+  ray_local(g, r, opx, opy, opz, dpx, dpy, dpz);
+  return chord_local(opx, opy, opz, dpx, dpy, dpz, g.k2);
+}
+
 // Colour of a Gaussian at the lane's direction: c = sum_m f_m Y_m.  Every
-// colour record is kColFloats long whatever the degree (zero past 3 sh_k) and
+// colour record is kColFloats long whatever the degree (zero past sh_k) and
 // Y_m = 0 for m >= sh_k, so the record is read at fixed offsets, without
 // branches, and the terms past the degree add exact zeros.  The record's
 // three 64-byte scalar loads (colour_load) can be issued ahead of work that
@@ -158,20 +165,11 @@ __device__ __forceinline__ void colour_eval(const ColRec &rc, const float *Y, fl
                                             float &cb) {
   float acc[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int q = 0; q < kColFloats / 4; q++) {
-    const float fv[4] = {rc.f[q].x, rc.f[q].y, rc.f[q].z, rc.f[q].w};
+  for (int m = 0; m < 16; m++)
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const int flat = 4 * q + e;
-      acc[flat % 3] = fmaf(fv[e], Y[flat / 3], acc[flat % 3]);
-    }
-  }
+    for (int c = 0; c < 3; c++)   // coefficient m = 4q + k of channel c: [c][k][q]
+      acc[c] = fmaf(rc.f[4 * c + (m & 3)][m >> 2], Y[m], acc[c]);
   cr = acc[0]; cg = acc[1]; cb = acc[2];
-}
-
-__device__ __forceinline__ void colour(const float *col, int j, const float *Y, float &cr,
-                                       float &cg, float &cb) {
-  colour_eval(colour_load(col, j), Y, cr, cg, cb);
 }
 
 // Spherical-Gaussian lobes of Gaussian j added to the lane's colour:
@@ -335,43 +333,29 @@ struct SegState {
 };
 
 
-// The N_S sample weights of one Gaussian for one lane:
+// The sample weights of one Gaussian for one lane:
 // w_k = sigma~ exp(-q(t_k)/2) if q(t_k) <= k^2 else 0.  With t_k = t_0 + k dt
 // and q(t) = A (t - t*)^2 + h^2, the exponent log2 sigma~ - q_k log2(e)/2 is
 // a quadratic in the sample index, e_0 + k e_1 + k^2 e_2, so each sample
 // costs two FMAs before its exp2; the truncation test q_k <= k^2 is the
 // same quadratic against log2 sigma~ - k^2 log2(e)/2.
-// With SKIP, returns the (wave-uniform) mask of samples that some active
-// lane sees inside the Gaussian: the others have w_k = 0 in every lane, and
-// callers may skip them (adding their zero terms would change nothing).  The
-// forward gains from it; in the backward the extra branches cost more
-// registers than they save.
-template <int NS, bool SKIP = false>
-__device__ __forceinline__ uint32_t sample_weights(const Gauss &g, const Chord &c,
-                                                   const Samples &sp, float *w) {
+struct SampleExp {
+  float e0, e1, e2, e_min;
+  __device__ __forceinline__ float at(int k) const {
+    return k == 0 ? e0 : fmaf((float)(k * k), e2, fmaf((float)k, e1, e0));
+  }
+};
+
+__device__ __forceinline__ SampleExp sample_exp(float k2, float l2sig, const Chord &c,
+                                                const Samples &sp) {
   const float u0 = sp.t0 - c.ts;
   const float Au0 = c.A * u0;
-  const float e0 = fmaf(-fmaf(Au0, u0, c.h2), kHalfLog2e, g.l2sig);
-  const float e1 = -kHalfLog2e * (2.0f * Au0 * sp.dt);
-  const float e2 = -kHalfLog2e * (c.A * sp.dt * sp.dt);
-  const float e_min = fmaf(-g.k2, kHalfLog2e, g.l2sig);
-  uint32_t live = 0;
-#pragma unroll
-  for (int k = 0; k < NS; k++) {
-    const float x = k == 0 ? e0 : fmaf((float)(k * k), e2, fmaf((float)k, e1, e0));
-    const bool in = x >= e_min;
-    if (SKIP) {
-      w[k] = 0.0f;
-      if (ballot(in) != 0) {
-        w[k] = in ? __builtin_amdgcn_exp2f(x) : 0.0f;
-        live |= 1u << k;
-      }
-    } else {
-      const float e = __builtin_amdgcn_exp2f(x);
-      w[k] = in ? e : 0.0f;
-    }
-  }
-  return SKIP ? live : (1u << NS) - 1u;
+  SampleExp x;
+  x.e0 = fmaf(-fmaf(Au0, u0, c.h2), kHalfLog2e, l2sig);
+  x.e1 = -kHalfLog2e * (2.0f * Au0 * sp.dt);
+  x.e2 = -kHalfLog2e * (c.A * sp.dt * sp.dt);
+  x.e_min = fmaf(-k2, kHalfLog2e, l2sig);
+  return x;
 }
 
 // Segment bounds [a, b], step and sample positions of a live lane.
@@ -417,6 +401,29 @@ __device__ __forceinline__ float swap16_sum(float a, float b) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
                                                   false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+// 4x4 transposition between four registers and the wave's four 16-lane rows:
+// row q of x[g] becomes row g of x[q].
+__device__ __forceinline__ void transpose_rows(float (&x)[4]) {
+  uint32_t u[4];
+#pragma unroll
+  for (int g = 0; g < 4; g++) u[g] = __float_as_uint(x[g]);
+#pragma unroll
+  for (int g = 0; g < 2; g++) {
+    const auto p = __builtin_amdgcn_permlane32_swap(u[g], u[g + 2], false, false);
+    u[g] = p[0];
+    u[g + 2] = p[1];
+  }
+#pragma unroll
+  for (int g = 0; g < 4; g += 2) {
+    const auto p = __builtin_amdgcn_permlane16_swap(u[g], u[g + 1], false, false);
+    u[g] = p[0];
+    u[g + 1] = p[1];
+  }
+#pragma unroll
+  for (int g = 0; g < 4; g++) x[g] = __uint_as_float(u[g]);
 }
 __device__ __forceinline__ float uniform_lane(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
@@ -482,6 +489,36 @@ __device__ __forceinline__ float wave_sum_slots16(const float *g, int lane) {
   return u;
 }
 
+// Sum over the wave of the kGeomSlots = 10 geometry and density slots of one
+// Gaussian, in 25 instructions: the same stages as above on five pairs of
+// slots (i, i + 5), the fifth pair carried along without a partner where
+// there is none.  slot_of_lane gives the slot a lane's result belongs to, or
+// -1 where another lane holds the same total.
+constexpr int kGeomSlots = 10;
+__device__ __forceinline__ float wave_sum_slots10(const float *g, int lane) {
+  float y[5], z[2];
+#pragma unroll
+  for (int i = 0; i < 5; i++) y[i] = swap32_sum(g[i], g[i + 5]);   // bit 5: i or i + 5
+  z[0] = swap16_sum(y[0], y[1]);                                   // bit 4: 0 or 1
+  z[1] = swap16_sum(y[2], y[3]);                                   // bit 4: 2 or 3
+  float x[2];
+  x[1] = swap16_sum(y[4], y[4]);
+  dpp_stage_bit<1, 0x140, 8>(z, lane);                             // bit 3: {0, 1} or {2, 3}
+  x[0] = z[0];
+  x[1] += dpp<0x140>(x[1]);
+  dpp_stage_bit<1, 0x141, 4>(x, lane);                             // bit 2: {0 .. 3} or 4
+  float u = x[0];
+  u += dpp<0xb1>(u);
+  u += dpp<0x4e>(u);
+  return u;
+}
+__device__ __forceinline__ int slot_of_lane(int lane) {
+  const int hi = (lane >> 5) * 5;
+  if (lane & 3) return -1;
+  if (lane & 4) return (lane & 24) == 0 ? 4 + hi : -1;
+  return ((lane >> 4) & 1) + 2 * ((lane >> 3) & 1) + hi;
+}
+
 // SH-coefficient gradients of a batch of up to 16 Gaussians, a small dense
 // product on the matrix cores.  For Gaussian b of the batch and channel c,
 // dL/df_{m,c} = sum over the tile's rays r of Y_m(d_r) G_c(r) S_b(r), S_b(r)
@@ -494,7 +531,6 @@ __device__ __forceinline__ float wave_sum_slots16(const float *g, int lane) {
 // i + 16k, second Y[k][j] in lane j + 16k, D[i][j] in lane j + 16 (i / 4),
 // register i % 4.  Each atomic instruction therefore adds 16 consecutive
 // floats (one 64-byte line) to each of 4 Gaussians' rows.
-typedef float f4v __attribute__((ext_vector_type(4)));
 constexpr int kSbStride = 66;   // floats per staged row: transposed reads hit distinct banks
 
 struct ShBatch {
@@ -722,16 +758,24 @@ constexpr int kStageCap = 160;   // staged leaves; a round adds at most 2 per no
 constexpr int kListCap = 512;    // window list entries (multiple of 64, at most 512)
 
 struct WaveMem {
-  float rdx[64], rdy[64], rdz[64], rix[64], riy[64], riz[64], rlo[64], rhi[64];
+  float rlo[64], rhi[64];          // the rays' windows
   struct {                         // traversal state, kept while a collection is paused
     int32_t ring_id[kRingCap], ring_first[kRingCap];
     int32_t st_id[kStageCap];
   } c;
-  int32_t order[kListCap];         // slots of the current chunk's entries, in Z-index order
+  uint16_t order[kListCap];        // slots of the current chunk's entries, in Z-index order
   int32_t l_id[kListCap];
   float l_tin[kListCap], l_tout[kListCap];
-  int32_t cnt_box[64];             // per-ray AABB-only leaf count (statistics)
+  int32_t cand[64];                // a block's candidates, packed to the front
 };
+
+// Statistics only: the tile's rays and their AABB-only leaf counts.
+struct StatMem {
+  float rdx[64], rdy[64], rdz[64], rix[64], riy[64], riz[64];
+  int32_t cnt_box[64];
+};
+template <bool STATS> struct StatMemOf {};
+template <> struct StatMemOf<true> : StatMem {};
 
 __device__ __forceinline__ uint64_t join64(uint32_t lo, uint32_t hi) {
   return (uint64_t)lo | ((uint64_t)hi << 32);
@@ -742,7 +786,7 @@ __device__ __forceinline__ uint64_t lanes_below(int lane) {
 }
 
 // Lane-local ray r from the wave's LDS copy (origin is wave-uniform).
-__device__ __forceinline__ Ray lds_ray(const WaveMem &M, const Ray &self, int r) {
+__device__ __forceinline__ Ray lds_ray(const StatMem &M, const Ray &self, int r) {
   Ray q;
   q.ox = self.ox; q.oy = self.oy; q.oz = self.oz;
   q.dx = M.rdx[r]; q.dy = M.rdy[r]; q.dz = M.rdz[r];
@@ -898,7 +942,7 @@ __device__ __forceinline__ int sort_list(WaveMem &M, int lane, int count, int zc
 #pragma unroll
   for (int q = 0; q < 8; q++) {
     const int e = 64 * q + lane;
-    if (e < valid) M.order[e] = (int)(key[q] & 511u);
+    if (e < valid) M.order[e] = (uint16_t)(key[q] & 511u);
   }
   __builtin_amdgcn_wave_barrier();
   return valid;
@@ -1103,7 +1147,7 @@ __device__ __forceinline__ void trav_advance(WaveMem &M, int lane, Trav &t) {
 // finished chunk's entries into M.order and returns their number, or -1 on
 // a malformed tree (error flag set).
 __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray &self, int lane, Trav &t,
-                        int n_active, bool stats, int32_t *err, int32_t &nodes_out,
+                        int n_active, StatMem *stats, int32_t *err, int32_t &nodes_out,
                         int32_t &leaves_out, int64_t *cyc_excl) {
   if (n_active <= 0 || t.rays == 0 || t.z0 >= t.z1) {
     t.count = 0;
@@ -1270,11 +1314,11 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
         const float *bx = s.aabb + 6 * (size_t)(test ? j : 0);
         for (uint64_t rem = rays; rem; rem &= rem - 1) {
           const int r = __builtin_ctzll(rem);
-          const Ray q = lds_ray(M, self, r);
+          const Ray q = lds_ray(*stats, self, r);
           const float lo = M.rlo[r], hi = M.rhi[r];
           if (!test || !box_hit(bx[0], bx[1], bx[2], bx[3], bx[4], bx[5], q, lo, hi)) continue;
           const Chord ch = chord(g, q);
-          if (!(ch.exists && ch.tin <= hi && ch.tout >= lo)) atomicAdd(&M.cnt_box[r], 1);
+          if (!(ch.exists && ch.tin <= hi && ch.tout >= lo)) atomicAdd(&stats->cnt_box[r], 1);
         }
         if (cyc_excl) *cyc_excl += clock64() - c0;
       }
@@ -1334,48 +1378,136 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
 
 enum SourceKind { SRC_LIST = 0, SRC_BRUTE = 1 };
 
-// Reads lane `src`'s copy of a geometry record (wave-uniform result).
-__device__ __forceinline__ Gauss gauss_from_lane(const Gauss &v, int src) {
-  Gauss g;
-  auto rl = [src](float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src));
-  };
-  g.mx = rl(v.mx); g.my = rl(v.my); g.mz = rl(v.mz); g.k2 = rl(v.k2);
-#pragma unroll
-  for (int k = 0; k < 9; k++) g.m[k] = rl(v.m[k]);
-  g.sig = rl(v.sig); g.l2sig = rl(v.l2sig); g.rad = rl(v.rad);
-  g.ox = rl(v.ox); g.oy = rl(v.oy); g.oz = rl(v.oz);
-  return g;
-}
-
 // Entries of M.order carry a mark bit above the slot index: set by a MARK
 // pass for the entries some lane hit, read by a FILTER pass over the same
 // list and the same segments.
-constexpr int kOrderMark = 1 << 16;
+constexpr int kOrderMark = 1 << 15;
 enum CandMode { CAND_ALL = 0, CAND_MARK = 1, CAND_FILTER = 2 };
 
-// Calls fn(j, g) for every candidate j with its geometry record g.
+// Candidates are taken four at a time, and the ray direction in each one's
+// frame, d' = M d, comes from the matrix cores (in the backward the SH colour
+// sum_m f_m Y_m(d) too): the rows of a 16x16x4 FP32 product are 4 candidates x
+// (3 components + 1 unused), its columns 16 of the tile's rays, its inner
+// index 4 terms of the sum.  d' is one product per 16 rays, the colour four
+// chained ones over the 16 coefficients.  Operand layout of
+// v_mfma_f32_16x16x4_f32 (wave64): first operand X[i][k] in lane i + 16k,
+// second Y[k][j] in lane j + 16k, D[i][j] in lane j + 16 (i / 4), register
+// i % 4; so candidate q's three components for ray group g end in row q of the
+// group's registers, and a 4x4 row transposition hands every lane (ray) its
+// own values of the four candidates.  The unit adds the four products one
+// after another in ascending k with one rounding each (measured bit for bit),
+// so the values are those of the FMA chains fma(m_0, dx, fma(m_1, dy, m_2 dz))
+// (terms in the order z, y, x) and f_0 Y_0 + f_1 Y_1 + ... .
+//
+// What bounds the loop is the SIMD's issue time, in which FP32 matrix
+// instructions and vector instructions do not overlap (16000 of one take
+// 0.245 ms, 128000 of the other 0.455 ms, both together 0.686 ms).  Measured
+// per instruction with the SIMD full: 16x16x4 product 15.3 ns, row swap 3.4,
+// readlane 1.85, FMA with a scalar operand 1.77, without 1.0.  d' of a
+// candidate: 9 readlanes and 9 FMAs on them 32.6 ns, one product and three
+// swaps 25.5 ns.  Its colour: 48 scalar-operand FMAs 85 ns and a scalar load's
+// latency, against 71 ns with the operands loaded a group ahead -- but for
+// every candidate.  In the forward, where half the candidates are hit by no
+// lane, the colour therefore stays with the vector units; the backward's
+// candidates are the hit ones.  1M Gaussians, 4 x 1024x768: forward 41.5 ->
+// 39.7 ms (43.2 with the colour here too), backward 32.4 -> 27.5 ms (with the
+// ten-slot reduction).
+struct TileOps {
+  float d[4];      // direction operand of rays 16g .. 16g + 15: k = 0, 1, 2 -> z, y, x; 3 -> 0
+  float y[4][4];   // basis operand, [ray group][4 coefficients 4q .. 4q + 3] (COL)
+};
+
+template <bool COL>
+__device__ __forceinline__ void tile_ops(TileOps &o, const Ray &r, const float *Y, int lane) {
+  const int k = lane >> 4;
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const int src = 16 * g + (lane & 15);
+    const float x = __shfl(r.dx, src, 64), y = __shfl(r.dy, src, 64), z = __shfl(r.dz, src, 64);
+    o.d[g] = k == 0 ? z : k == 1 ? y : k == 2 ? x : 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if constexpr (!COL) break;
+      float t[4];
+#pragma unroll
+      for (int e = 0; e < 4; e++) t[e] = __shfl(Y[4 * q + e], src, 64);
+      o.y[g][q] = k == 0 ? t[0] : k == 1 ? t[1] : k == 2 ? t[2] : t[3];
+    }
+  }
+}
+
+// One candidate that some lane of the wave hit, as the segment loops see it:
+// the lane's chord and colour, and (pass B) its ray in the local frame.
+struct Cand {
+  float k2, l2sig;          // uniform
+  Chord ch;
+  float ox, oy, oz;         // uniform
+  float dx, dy, dz;
+  float cr, cg, cb;
+};
+
+// A lane's matrix operands of a group of four candidates.
+struct CandOps {
+  float m;       // lane (row 4c + i, k): M_c[i][2 - k]
+  vf4 f;         // lane (row 4c + i, k): coefficients 4q + k, q = 0..3, of channel i
+};
+
+// Issues the operand loads of a lane's candidate of the group (`mine`: that of
+// row c of its operands, c = (lane >> 2) & 3).
+template <bool COL>
+__device__ __forceinline__ CandOps cand_fetch(const SceneDev &s, uint32_t mine, int lane) {
+  const int i = min(lane & 3, 2), k = lane >> 4;
+  CandOps G;
+  // (32-bit byte offsets: at most 2^23 records of 192 bytes)
+  const uint32_t mo = mine * (4u * kGeomFloats) + 4u * (uint32_t)(G_M + 3 * i + 2 - min(k, 2));
+  G.m = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s.geom) + mo);
+  if (COL) {
+    const uint32_t fo = mine * (4u * kColFloats) + 4u * (uint32_t)(16 * i + 4 * k);
+    G.f = *reinterpret_cast<const vf4 *>(reinterpret_cast<const char *>(s.col) + fo);
+  }
+  return G;
+}
+template <bool COL>
+__device__ __forceinline__ void cand_pin(const CandOps &G) {
+  pin_lane(__float_as_uint(G.m));
+  if (COL) pin_loaded(G.f);
+}
+
+// Calls fn(c, j, g, hit) for every candidate j (the c-th of its group of four,
+// a constant in each inlined copy) whose chord meets [lo, hi] in some lane
+// with `want` set; `hit` says in which lanes, g is its Cand (colour left out
+// unless COL).  visit() runs once per candidate tested (statistics).
 // `a_min`/`b_max` bound the live lanes' segments for the list's uniform
 // depth pre-check.  List entries are taken 64 at a time: lane i holds entry
 // base + i and loads that entry's geometry, so one memory round trip serves
-// the whole block; the surviving candidates are then read back with readlane.
-// CAND_MARK: fn returns whether some lane hit the candidate, and the entry's
-// mark is set to that; CAND_FILTER: only marked entries are visited (list
-// source only; the brute-force source visits everything).
-// With use_marks, a CAND_MARK pass trusts the marks already set (from a
-// record of the same pass) and visits only the marked entries.
-template <int MODE = CAND_ALL, class Fn>
+// the whole block; the surviving candidates then go through in groups of
+// four, the next group's operand loads in flight meanwhile.  A group's four
+// chords are one branch-free run of vector work, so that the four dependent
+// chains (with a reciprocal and a square root each) overlap; the colour's
+// matrix instructions are spread through it.
+// after(c, j) runs for the hit candidates of a group once the next operands
+// have arrived: memory operations that count against the same counter
+// (atomics) belong there, or the wait for the loads would wait for them too.
+// CAND_MARK: a visited entry's mark is set to whether some lane hit it.  With
+// use_marks, a CAND_MARK pass trusts the marks already set (from a record of
+// the same pass) and visits only the marked entries, and a CAND_FILTER pass
+// visits only the marked entries (list source only; the brute-force source
+// visits everything).
+template <int MODE, bool COL, class Visit, class Fn, class After>
 __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, WaveMem &M,
                                                    int count, int lane, float a_min, float b_max,
-                                                   int n_active, const Ray &r, Fn &&fn,
-                                                   bool use_marks = false) {
-  const float ox = r.ox, oy = r.oy, oz = r.oz;
-  if (kind == SRC_LIST) {
-    for (int base = 0; base < count; base += 64) {
-      const int e = base + lane;
-      int id = 0, o = 0;
-      bool keep = false;
-      if (e < count) {
+                                                   int n_active, const Ray &r, const TileOps &ops,
+                                                   bool want, float lo, float hi, Visit &&visit,
+                                                   Fn &&fn, After &&after, bool use_marks = false) {
+  const bool list = kind == SRC_LIST;
+  const int total = list ? count : n_active;
+  const uint64_t wanted = ballot(want);
+  for (int base = 0; base < total; base += 64) {
+    const int e = base + lane;
+    int id = 0, o = 0;
+    bool keep = false;
+    if (e < total) {
+      if (list) {
         const int om = M.order[e];
         o = om & (kOrderMark - 1);
         // the entry's three words are read together (no short-circuit
@@ -1383,26 +1515,140 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
         const float tin = M.l_tin[o], tout = M.l_tout[o];
         id = M.l_id[o];
         keep = !(tin > b_max) & !(tout < a_min);
-        if (MODE == CAND_FILTER || (MODE == CAND_MARK && use_marks))
-          keep = keep & ((om & kOrderMark) != 0);
+        if (MODE != CAND_ALL) keep = keep & (!use_marks | ((om & kOrderMark) != 0));
+      } else {
+        id = e;
+        keep = true;
       }
-      const uint64_t bits0 = ballot(keep);
-      if (!bits0) continue;
-      const Gauss mine = with_origin(load_gauss_lane(s.geom, keep ? id : 0), ox, oy, oz);
-      uint64_t hits = 0;   // (uniform) the block's candidates some lane hit
-      for (uint64_t bits = bits0; bits; bits &= bits - 1) {
-        const int src = __builtin_ctzll(bits);
-        if constexpr (MODE == CAND_MARK) {
-          if (fn(__builtin_amdgcn_readlane(id, src), gauss_from_lane(mine, src))) hits |= 1ull << src;
-        } else {
-          fn(__builtin_amdgcn_readlane(id, src), gauss_from_lane(mine, src));
+    }
+    const uint64_t kept = ballot(keep);
+    if (!kept) continue;
+    const int n = __popcll(kept), rank = __popcll(kept & lanes_below(lane));
+    // the block's candidates move to lanes 0 .. n - 1, in order
+    if (keep) M.cand[rank] = id;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t first_of = (uint32_t)M.cand[min((lane >> 2) & 3, n - 1)];
+    const int cid = M.cand[min(lane, n - 1)];
+    __builtin_amdgcn_wave_barrier();
+    CandOps cur = cand_fetch<COL>(s, first_of, lane);
+    const Gauss mine = with_origin(load_gauss_lane(s.geom, cid), r.ox, r.oy, r.oz);
+    int next_id = __shfl(cid, 4 + ((lane >> 2) & 3), 64);
+    cand_pin<COL>(cur);
+    uint64_t hits = 0;   // (uniform) the block's candidates some lane hit
+    for (int first = 0; first < n; first += 4) {
+      // d' of the group's candidates, transposed to the lanes; the next
+      // group's loads and the readlanes run beside the matrix instructions
+      f4v acc[4];
+      const float mm = lane < 48 ? cur.m : 0.0f;
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const f4v z = {0.0f, 0.0f, 0.0f, 0.0f};
+        acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(mm, ops.d[g], z, 0, 0, 0);
+      }
+      const CandOps nxt = cand_fetch<COL>(s, (uint32_t)next_id, lane);
+      Cand g[4];
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        g[c].ox = uniform_lane(mine.ox, first + c);
+        g[c].oy = uniform_lane(mine.oy, first + c);
+        g[c].oz = uniform_lane(mine.oz, first + c);
+        g[c].k2 = uniform_lane(mine.k2, first + c);
+        g[c].l2sig = uniform_lane(mine.l2sig, first + c);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      next_id = __shfl(cid, first + 8 + ((lane >> 2) & 3), 64);
+      {
+        float d[3][4];
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+#pragma unroll
+          for (int q = 0; q < 4; q++) d[i][q] = acc[q][i];
+          transpose_rows(d[i]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; c++) { g[c].dx = d[0][c]; g[c].dy = d[1][c]; g[c].dz = d[2][c]; }
+      }
+      // the four chords (chord_local, step by step), one of the colour's 16
+      // matrix instructions before every few vector ones; the barriers keep
+      // the order, which the compiler's scheduler would undo
+      if constexpr (COL) {
+#pragma unroll
+        for (int p = 0; p < 4; p++) acc[p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+      auto mm_step = [&](int i) {
+        if constexpr (COL) {
+          __builtin_amdgcn_sched_barrier(0);
+          acc[i & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.f[i >> 2], ops.y[i & 3][i >> 2],
+                                                           acc[i & 3], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      float B[4], rA[4], x[4], w[4];
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        if (!(c & 1)) mm_step(c >> 1);
+        g[c].ch.A = fmaf(g[c].dx, g[c].dx, fmaf(g[c].dy, g[c].dy, g[c].dz * g[c].dz));
+      }
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        if (!(c & 1)) mm_step(2 + (c >> 1));
+        rA[c] = __builtin_amdgcn_rcpf(g[c].ch.A);
+        B[c] = fmaf(g[c].ox, g[c].dx, fmaf(g[c].oy, g[c].dy, g[c].oz * g[c].dz));
+      }
+      mm_step(4);
+#pragma unroll
+      for (int c = 0; c < 4; c++) g[c].ch.ts = -B[c] * rA[c];
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        mm_step(5 + c);
+        const float px = fmaf(g[c].ch.ts, g[c].dx, g[c].ox), py = fmaf(g[c].ch.ts, g[c].dy, g[c].oy),
+                    pz = fmaf(g[c].ch.ts, g[c].dz, g[c].oz);
+        g[c].ch.h2 = fmaf(px, px, fmaf(py, py, pz * pz));
+      }
+      mm_step(9);
+#pragma unroll
+      for (int c = 0; c < 4; c++) x[c] = fmaxf(g[c].k2 - g[c].ch.h2, 0.0f);
+      mm_step(10);
+#pragma unroll
+      for (int c = 0; c < 4; c++) w[c] = __builtin_amdgcn_sqrtf(x[c] * rA[c]);
+      mm_step(11);
+      uint64_t any[4];
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        g[c].ch.tin = g[c].ch.ts - w[c];
+        g[c].ch.tout = g[c].ch.ts + w[c];
+        // lane masks, not a chain of short-circuit branches
+        any[c] = ballot(g[c].ch.h2 <= g[c].k2) & ballot(g[c].ch.tin <= hi) &
+                 ballot(g[c].ch.tout >= lo) & (first + c < n ? wanted : 0ull);
+        mm_step(12 + c);
+      }
+      float col[3][4];
+      if constexpr (COL) {
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+#pragma unroll
+          for (int q = 0; q < 4; q++) col[i][q] = acc[q][i];
+          transpose_rows(col[i]);
         }
       }
-      if (MODE == CAND_MARK && !use_marks && keep)
-        M.order[e] = o | (((hits >> lane) & 1ull) ? kOrderMark : 0);
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        if (first + c < n) visit();
+        if (any[c] != 0) {
+          if (MODE == CAND_MARK) hits |= 1ull << (first + c);
+          if constexpr (COL) { g[c].cr = col[0][c]; g[c].cg = col[1][c]; g[c].cb = col[2][c]; }
+          fn(c, __builtin_amdgcn_readlane(cid, first + c), g[c],
+             __builtin_amdgcn_inverse_ballot_w64(any[c]));
+        }
+      }
+      cand_pin<COL>(nxt);
+#pragma unroll
+      for (int c = 0; c < 4; c++)
+        if (any[c] != 0) after(c, __builtin_amdgcn_readlane(cid, first + c));
+      cur = nxt;
     }
-  } else {
-    for (int e = 0; e < n_active; e++) fn(e, with_origin(load_gauss(s.geom, e), ox, oy, oz));
+    if (MODE == CAND_MARK && list && !use_marks && keep)
+      M.order[e] = (uint16_t)(o | (((hits >> rank) & 1ull) ? kOrderMark : 0));
   }
 }
 
@@ -1612,7 +1858,7 @@ __device__ __forceinline__ int rec_load(const MarchOpts &op, WaveMem &M, uint32_
     M.l_id[e] = (int)p[kWrecHeader + 3 * e];
     M.l_tin[e] = __uint_as_float(p[kWrecHeader + 3 * e + 1]);
     M.l_tout[e] = __uint_as_float(p[kWrecHeader + 3 * e + 2]);
-    M.order[e] = e;
+    M.order[e] = (uint16_t)e;
   }
   __builtin_amdgcn_wave_barrier();
   *next = (uint32_t)uniform_int((int)p[0]);
@@ -1644,7 +1890,7 @@ __device__ __forceinline__ bool rec_load_marks(const MarchOpts &op, WaveMem &M, 
       const int e = 64 * q + lane;
       if (q < words && e < count) {
         const int o = M.order[e] & (kOrderMark - 1);
-        M.order[e] = o | (((w[q] >> (lane & 31)) & 1u) ? kOrderMark : 0);
+        M.order[e] = (uint16_t)(o | (((w[q] >> (lane & 31)) & 1u) ? kOrderMark : 0));
       }
     }
   }
@@ -1678,7 +1924,7 @@ __device__ __forceinline__ bool rec_next_marks(WinRec &R, const MarchOpts &op, W
 // against the whole kernel.
 template <bool REPLAY>
 __device__ __forceinline__ int collect(const SceneDev &s, const MarchOpts &op, WaveMem &M,
-                                       const Ray &r, int lane, Trav &t, int n_active, bool stats,
+                                       const Ray &r, int lane, Trav &t, int n_active, StatMem *stats,
                                        int32_t *err, int32_t &nodes, int32_t &leaves,
                                        int64_t *cyc_excl, WinRec &R, uint32_t *start) {
   if (REPLAY && op.replay_mode == 2 && R.ok) {
@@ -1732,7 +1978,7 @@ struct Window {
 template <bool REPLAY>
 __device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts &op, WaveMem &M,
                                               const Ray &r, int lane, int n_active, bool alive,
-                                              float a, float b, Window &w, bool stats,
+                                              float a, float b, Window &w, StatMem *stats,
                                               int32_t *err, int32_t &nodes, int32_t &leaves,
                                               int32_t &windows, bool &fits, WinRec &R,
                                               int64_t *cyc_excl = nullptr) {
@@ -1775,7 +2021,7 @@ __device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts
 // for the lanes in `lanes` over their segments [a, b].
 __device__ __forceinline__ void first_chunk(const SceneDev &s, WaveMem &M, const Ray &r, int lane,
                                             int n_active, bool lanes, float a, float b, int zend,
-                                            Window &w, bool stats, int32_t *err, int32_t &nodes,
+                                            Window &w, StatMem *stats, int32_t *err, int32_t &nodes,
                                             int32_t &leaves, int32_t &windows) {
   const uint64_t rays = ballot(lanes);
   M.rlo[lane] = lanes ? a : kInf;
@@ -1794,7 +2040,7 @@ __device__ __forceinline__ void first_chunk(const SceneDev &s, WaveMem &M, const
 template <bool REPLAY>
 __device__ __forceinline__ bool next_chunk(const SceneDev &s, const MarchOpts &op, WaveMem &M,
                                            const Ray &r, int lane, int n_active, bool lanes,
-                                           float a, float b, Window &w, bool stats, int32_t *err,
+                                           float a, float b, Window &w, StatMem *stats, int32_t *err,
                                            int32_t &nodes, int32_t &leaves, int32_t &windows,
                                            WinRec &R, int64_t *cyc_excl = nullptr) {
   if (!w.chunked) return false;
@@ -1827,6 +2073,9 @@ template <int NS, bool DUMP, bool STATS, bool SG = false>
 __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, ViewTable vt, MarchOpts op,
                                                    FwdOut out, LaunchShape ls) {
   __shared__ WaveMem M;
+  __shared__ StatMemOf<STATS> SM;
+  StatMem *sm = nullptr;
+  if constexpr (STATS) sm = &SM;
   const int lane = threadIdx.x;
   const int n_active = uniform_int(s.counters[0]);
   const bool grid = !op.adaptive && op.ess != 2;
@@ -1859,12 +2108,16 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
     }
     const View &V = vt.v[px.view];
     const Ray r = make_ray(V, px.px, px.py);
-    M.rdx[lane] = r.dx; M.rdy[lane] = r.dy; M.rdz[lane] = r.dz;
-    M.rix[lane] = r.ix; M.riy[lane] = r.iy; M.riz[lane] = r.iz;
-    M.cnt_box[lane] = 0;
+    if constexpr (STATS) {
+      sm->rdx[lane] = r.dx; sm->rdy[lane] = r.dy; sm->rdz[lane] = r.dz;
+      sm->rix[lane] = r.ix; sm->riy[lane] = r.iy; sm->riz[lane] = r.iz;
+      sm->cnt_box[lane] = 0;
+    }
     const float tn = V.t_near, tf = V.t_far;
     float Y[16];
     sh_basis(op.sh_k, r.dx, r.dy, r.dz, Y);
+    TileOps ops;
+    tile_ops<false>(ops, r, Y, lane);
 
     SegState ss;
     int n_closest = 0;   // closest-hit queries of this lane's ray so far
@@ -1925,7 +2178,7 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
       if (!ss.alive) { sp.t0 = 0.0f; sp.dt = 0.0f; }
       bool go;
       if (stats) cyc_t0 = clock64();
-      ensure_window<false>(s, op, M, r, lane, n_active, ss.alive, a, b, win, stats, ls.error_flag,
+      ensure_window<false>(s, op, M, r, lane, n_active, ss.alive, a, b, win, sm, ls.error_flag,
                     cnt[ST_NODES], cnt[ST_LEAVES], cnt[ST_WINDOWS], go, rec,
                     stats ? &cyc_boxstat : nullptr);
       if (stats) cyc_collect += clock64() - cyc_t0;
@@ -1938,15 +2191,10 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
       int nhit = 0;
 
       do {
-        for_each_candidate<CAND_MARK>(win.kind, s, M, win.count, lane, a_min, b_max, n_active, r,
-                                      [&](int j, const Gauss &g) {
-        const bool want = go;
-        if (stats) cnt[ST_CAND]++;
-        const Chord c = chord(g, r);
-        // one conjunction, not a chain of short-circuit branches: the test
-        // stays in lane masks, with no branch per term
-        const bool hit = want & c.exists & (c.tin <= hi) & (c.tout >= lo);
-        if (ballot(hit) == 0) return false;
+        for_each_candidate<CAND_MARK, false>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
+                                             r, ops, go, lo, hi, [&] { if (stats) cnt[ST_CAND]++; },
+                                            [&](int, int j, const Cand &g, bool hit) {
+        const Chord &c = g.ch;
         if (stats) cnt[ST_CAND_HIT]++;
         if (hit) {
           nhit++;
@@ -1961,8 +2209,21 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
           // the colour record's loads go out before the sample weights,
           // which do not need them
           const ColRec rc = colour_load(s.col, j);
+          const SampleExp se = sample_exp(g.k2, g.l2sig, c, sp);
           float wk[NS];
-          const uint32_t live = sample_weights<NS, true>(g, c, sp, wk);
+          uint32_t live = 0;   // (uniform) samples some lane sees inside the Gaussian
+#pragma unroll
+          for (int k = 0; k < NS; k++) {
+            const float x = se.at(k);
+            const bool in = x >= se.e_min;
+            // samples no lane sees inside the Gaussian are skipped with a
+            // uniform branch (their terms are exact zeros)
+            wk[k] = 0.0f;
+            if (ballot(in) != 0) {
+              wk[k] = in ? __builtin_amdgcn_exp2f(x) : 0.0f;
+              live |= 1u << k;
+            }
+          }
           float cr, cg, cb;
           colour_eval(rc, Y, cr, cg, cb);
           if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
@@ -1975,13 +2236,12 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
             W2[k] = fmaf(wk[k], cb, W2[k]);
           }
         }
-        return true;
-      });
+      }, [](int, int) {});
         // the entries this pass hit, for a replaying backward
         if (op.replay_mode == 1 && win.kind == SRC_LIST) rec_put_marks(rec, op, M, win.count, lane);
       } while ([&] {
         if (stats) cyc_t0 = clock64();
-        const bool more = next_chunk<false>(s, op, M, r, lane, n_active, go, a, b, win, stats,
+        const bool more = next_chunk<false>(s, op, M, r, lane, n_active, go, a, b, win, sm,
                                      ls.error_flag, cnt[ST_NODES], cnt[ST_LEAVES], cnt[ST_WINDOWS],
                                      rec, stats ? &cyc_boxstat : nullptr);
         if (stats) cyc_collect += clock64() - cyc_t0;
@@ -1994,12 +2254,11 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
       float best = kInf;
       if (op.ess && win.kind == SRC_LIST && !win.chunked && ballot(empty)) {
         const float bmin = wave_min(empty ? b : kInf);
-        for_each_candidate(SRC_LIST, s, M, win.count, lane, bmin, kInf, n_active, r,
-                           [&](int j, const Gauss &g) {
-          const bool want = empty;
-          const Chord c = chord(g, r);
-          if (want && c.exists && c.tout >= b && c.tin <= win.hi) best = fminf(best, fmaxf(c.tin, b));
-        });
+        for_each_candidate<CAND_ALL, false>(SRC_LIST, s, M, win.count, lane, bmin, kInf, n_active,
+                                            r, ops, empty, b, win.hi, [] {},
+                                            [&](int, int, const Cand &g, bool hit) {
+          if (hit) best = fminf(best, fmaxf(g.ch.tin, b));
+        }, [](int, int) {});
       }
       // the step's per-sample sums and restarts, for a replaying backward
       if (op.replay_mode == 1 && op.sample_rec)
@@ -2030,7 +2289,7 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
 
     rec_finish(rec, op, lane);
     if (stats) {
-      cnt[ST_BOX_ONLY] += M.cnt_box[lane];
+      cnt[ST_BOX_ONLY] += sm->cnt_box[lane];
       cnt[ST_KCYC_COLLECT] = (int32_t)((cyc_collect - cyc_boxstat) >> 10);
       cnt[ST_KCYC_CLOSEST] = (int32_t)(cyc_closest >> 10);
       cnt[ST_KCYC_TILE] = (int32_t)((clock64() - cyc_tile - cyc_boxstat) >> 10);
@@ -2093,7 +2352,7 @@ __device__ __forceinline__ void sg_slots(const float *sg, float *sgacc, int j, f
 // segment's per-sample sums from the forward's record (or sums them again
 // where there is none), recomputes the transmittance before every sample,
 // derives dL/dsigma_k and dL/dW_k, then revisits the Gaussians some lane hit
-// for their parameter adjoints.  The 16
+// for their parameter adjoints.  The ten
 // geometry and density slots are summed over the wave (DPP and half-wave
 // swaps) before one atomic per slot; the SH-coefficient slots, a per-ray
 // constant times one scalar per (ray, Gaussian), are staged 16 Gaussians at a
@@ -2107,6 +2366,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
   __shared__ float sb[16 * kSbStride];   // staged S rows of the SH batch
   ShBatch shb;
   const int lane = threadIdx.x;
+  const int slot = slot_of_lane(lane);
   const int n_active = uniform_int(s.counters[0]);
   const bool grid = !op.adaptive && op.ess != 2;
   bool first = true;
@@ -2125,8 +2385,6 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
     const Pixel px = tile_pixel(vt, op, w, lane);
     const View &V = vt.v[px.view];
     const Ray r = make_ray(V, px.px, px.py);
-    M.rdx[lane] = r.dx; M.rdy[lane] = r.dy; M.rdz[lane] = r.dz;
-    M.rix[lane] = r.ix; M.riy[lane] = r.iy; M.riz[lane] = r.iz;
     const float tn = V.t_near, tf = V.t_far;
     float Y[16];
     sh_basis(op.sh_k, r.dx, r.dy, r.dz, Y);
@@ -2143,6 +2401,8 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
     }
     // (the list arrays are free before the tile's first window)
     sh_batch_start(shb, sb, M.l_tin, Y, Gc0, Gc1, Gc2, lane);
+    TileOps ops;
+    tile_ops<true>(ops, r, Y, lane);
     float GP = 0.0f;
     SegState ss;
     int n_closest = 0;   // closest-hit queries of this lane's ray so far
@@ -2186,7 +2446,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
       }
       if (!ss.alive) { sp.t0 = 0.0f; sp.dt = 0.0f; }
       bool go;
-      ensure_window<true>(s, op, M, r, lane, n_active, ss.alive, a, b, win, false, ls.error_flag,
+      ensure_window<true>(s, op, M, r, lane, n_active, ss.alive, a, b, win, nullptr, ls.error_flag,
                     dummy_nodes, dummy_leaves, dummy_windows, go, rec);
       const float a_min = wave_min(go ? a : kInf), b_max = wave_max(go ? b : -kInf);
       const float lo = go ? a : kInf, hi = go ? b : -kInf;
@@ -2204,29 +2464,26 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
       do {
         const bool use_marks = rec_next_marks(rec, op, M, win.count, win.kind, lane, ls.error_flag);
         if (!from_rec)
-        for_each_candidate<CAND_MARK>(win.kind, s, M, win.count, lane, a_min, b_max, n_active, r,
-                                      [&](int j, const Gauss &g) {
-        const bool want = go;
-        const Chord c = chord(g, r);
-        const bool hit = want & c.exists & (c.tin <= hi) & (c.tout >= lo);
-        if (ballot(hit) == 0) return false;
+        for_each_candidate<CAND_MARK, true>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
+                                            r, ops, go, lo, hi, [] {},
+                                            [&](int, int j, const Cand &g, bool hit) {
+        const Chord &c = g.ch;
         if (hit) {
           nhit++;
-          float cr, cg, cb;
-          colour(s.col, j, Y, cr, cg, cb);
+          float cr = g.cr, cg = g.cg, cb = g.cb;
           if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
           const float gc = fmaf(Gc0, cr, fmaf(Gc1, cg, Gc2 * cb));
-          float wk[NS];
-          sample_weights<NS>(g, c, sp, wk);
+          const SampleExp se = sample_exp(g.k2, g.l2sig, c, sp);
 #pragma unroll
           for (int k = 0; k < NS; k++) {
-            sg[k] += wk[k];
-            GW[k] = fmaf(wk[k], gc, GW[k]);
+            const float x = se.at(k);
+            const float w = x >= se.e_min ? __builtin_amdgcn_exp2f(x) : 0.0f;
+            sg[k] += w;
+            GW[k] = fmaf(w, gc, GW[k]);
           }
         }
-        return true;
-      }, use_marks);
-      } while (next_chunk<true>(s, op, M, r, lane, n_active, go, a, b, win, false, ls.error_flag,
+      }, [](int, int) {}, use_marks);
+      } while (next_chunk<true>(s, op, M, r, lane, n_active, go, a, b, win, nullptr, ls.error_flag,
                             dummy_nodes, dummy_leaves, dummy_windows, rec));
       float best = kInf;
       if (from_rec)
@@ -2261,104 +2518,103 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
 
       // pass B: per-Gaussian adjoints
       if (ballot(any) != 0) {
-        auto pass_b = [&](int j, const Gauss &g) {
-          const bool want = any;
-          float opx, opy, opz, dpx, dpy, dpz;
-          ray_local(g, r, opx, opy, opz, dpx, dpy, dpz);
-          const Chord c = chord(g, r);
-          const bool hit = want & c.exists & (c.tin <= hi) & (c.tout >= lo);
-          if (ballot(hit) == 0) return;
+        float red[4];   // the group's reduced slots, one candidate each
+        auto pass_b = [&](int ci, int j, const Cand &g, bool hit) {
+          const Chord &c = g.ch;
           float S = 0.0f;
-          float v[16];
+          float v[kGeomSlots];
 #pragma unroll
-          for (int e2 = 0; e2 < 16; e2++) v[e2] = 0.0f;
+          for (int e2 = 0; e2 < kGeomSlots; e2++) v[e2] = 0.0f;
           if (hit) {
-            // the colour record's loads go out first: the sample weights and
-            // the geometry terms below do not need them
-            const ColRec rc = colour_load(s.col, j);
-            float wk[NS];
-            sample_weights<NS>(g, c, sp, wk);
-            // closest-approach point in the local frame, and its world
-            // offset from the mean
-            const float pxl = fmaf(c.ts, dpx, opx), pyl = fmaf(c.ts, dpy, opy),
-                        pzl = fmaf(c.ts, dpz, opz);
-            const float Ps[3] = {fmaf(c.ts, r.dx, r.ox - g.mx), fmaf(c.ts, r.dy, r.oy - g.my),
-                                 fmaf(c.ts, r.dz, r.oz - g.mz)};
-            const float inv_sig = __builtin_amdgcn_rcpf(g.sig);
-            float cr, cg, cb;
-            colour_eval(rc, Y, cr, cg, cb);
+            float cr = g.cr, cg = g.cg, cb = g.cb;
             if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
             const float gc = fmaf(Gc0, cr, fmaf(Gc1, cg, Gc2 * cb));
+            const SampleExp se = sample_exp(g.k2, g.l2sig, c, sp);
             // dL/dw_k = dsigma_k + G.c_l T_k phi_k; dq_k = -w_k dL/dw_k / 2
             // moments over u_k = u_0 + k dt from sums over the sample index
             float ds = 0.0f, F1 = 0.0f, F2 = 0.0f;
 #pragma unroll
             for (int k = 0; k < NS; k++) {
-              const float wdw = wk[k] * fmaf(GW[k], gc, sg[k]);
+              const float x = se.at(k);
+              const float e = __builtin_amdgcn_exp2f(x);
+              const float w = x >= se.e_min ? e : 0.0f;
+              const float wdw = w * fmaf(GW[k], gc, sg[k]);
               ds += wdw;
               F1 = fmaf((float)k, wdw, F1);
               F2 = fmaf((float)(k * k), wdw, F2);
-              S = fmaf(wk[k], GW[k], S);
+              S = fmaf(w, GW[k], S);
             }
             const float u0 = sp.t0 - c.ts;
             const float E1 = fmaf(u0, ds, sp.dt * F1);                         // sum wdw u
             const float E2 = fmaf(u0, fmaf(u0, ds, 2.0f * sp.dt * F1), sp.dt * sp.dt * F2);
             const float D0 = -0.5f * ds, D1 = -0.5f * E1, D2 = -0.5f * E2;
-            // z_k = p + u_k d' with p = o' + t* d' (closest approach, local frame)
-            const float Zs[3] = {fmaf(D0, pxl, D1 * dpx), fmaf(D0, pyl, D1 * dpy),
-                                 fmaf(D0, pzl, D1 * dpz)};
-            const float Us[3] = {fmaf(D1, pxl, D2 * dpx), fmaf(D1, pyl, D2 * dpy),
-                                 fmaf(D1, pzl, D2 * dpz)};
-            const float dd[3] = {r.dx, r.dy, r.dz};
-            v[0] = Zs[0]; v[1] = Zs[1]; v[2] = Zs[2];
-#pragma unroll
-            for (int i = 0; i < 3; i++)
-#pragma unroll
-              for (int jj = 0; jj < 3; jj++) v[3 + 3 * i + jj] = fmaf(Zs[i], Ps[jj], Us[i] * dd[jj]);
-            v[12] = fmaf(D0, pxl * pxl, fmaf(2.0f * D1, pxl * dpx, D2 * dpx * dpx));
-            v[13] = fmaf(D0, pyl * pyl, fmaf(2.0f * D1, pyl * dpy, D2 * dpy * dpy));
-            v[14] = fmaf(D0, pzl * pzl, fmaf(2.0f * D1, pzl * dpz, D2 * dpz * dpz));
-            v[15] = ds * inv_sig;
+            // z_k = p + u_k d' with p = o' + t* d' (closest approach, local
+            // frame): the first and second moments of dq over z
+            const float px = fmaf(c.ts, g.dx, g.ox), py = fmaf(c.ts, g.dy, g.oy),
+                        pz = fmaf(c.ts, g.dz, g.oz);
+            const float Zx = fmaf(D0, px, D1 * g.dx), Zy = fmaf(D0, py, D1 * g.dy),
+                        Zz = fmaf(D0, pz, D1 * g.dz);
+            const float Ux = fmaf(D1, px, D2 * g.dx), Uy = fmaf(D1, py, D2 * g.dy),
+                        Uz = fmaf(D1, pz, D2 * g.dz);
+            v[0] = Zx; v[1] = Zy; v[2] = Zz;
+            v[3] = fmaf(Zx, px, Ux * g.dx);
+            v[4] = fmaf(Zx, py, Ux * g.dy);
+            v[5] = fmaf(Zx, pz, Ux * g.dz);
+            v[6] = fmaf(Zy, py, Uy * g.dy);
+            v[7] = fmaf(Zy, pz, Uy * g.dz);
+            v[8] = fmaf(Zz, pz, Uz * g.dz);
+            v[9] = ds;
           }
-          // slots [0,16): geometry and density, summed over the wave; the SH
+          // the geometry and density slots are summed over the wave; the SH
           // slots go through the matrix-core batch
           sb[shb.n * kSbStride + lane] = S;
           shb.id = lane == shb.n ? j : shb.id;
-          const float mine = wave_sum_slots16(v, lane);
-          if ((lane & 3) == 0) unsafeAtomicAdd(in.acc + (size_t)kAccFloats * j + (lane >> 2), mine);
+          shb.n++;
+          red[ci] = wave_sum_slots10(v, lane);
           if constexpr (SG) sg_slots(s.sg, in.sgacc, j, hit ? S : 0.0f, Gc0, Gc1, Gc2, r, lane);
-          if (++shb.n == 16) sh_batch_flush(shb, sb, in.acc, op.sh_k, lane);
+        };
+        // a group's atomics go out together, behind the next group's loads
+        auto put_b = [&](int c, int j) {
+          if (slot >= 0) unsafeAtomicAdd(in.acc + (size_t)kAccFloats * j + slot, red[c]);
+          if (shb.n > 12) sh_batch_flush(shb, sb, in.acc, op.sh_k, lane);
         };
         // the list still holds the whole window, or the segment's last Z
         // chunk [zlast, end), its entries marked by pass A; a chunked segment
         // then visits [0, zlast): re-read from the record with the forward's
         // marks when replaying, else collected again
         const int zlast = win.chunked ? win.t.z0 : 0;
-        const bool reread = win.chunked && zlast > 0 && rec.ok;
+        const bool earlier = win.chunked && zlast > 0;
+        const bool reread = earlier && rec.ok;
         uint32_t off = win.rec_first;
         int n_cur = win.count, kind_cur = win.kind;
+        bool marked = true;      // visit the marked entries only
         for (bool cur = true;; cur = false) {
           if (!cur) {
-            if (!reread || off == win.rec_last || off == kWrecNone) break;
-            uint32_t next, after;
-            const int c = rec_load(op, M, off, lane, &next);
-            n_cur = c > 0 ? c : 0;
-            kind_cur = SRC_LIST;
-            if (c < 0 || next == kWrecNone || !rec_load_marks(op, M, next, n_cur, lane, &after)) {
-              if (ls.error_flag) *ls.error_flag = 5;
-              break;
+            if (!earlier) break;
+            if (reread) {
+              if (off == win.rec_last || off == kWrecNone) break;
+              uint32_t next, after;
+              const int c = rec_load(op, M, off, lane, &next);
+              n_cur = c > 0 ? c : 0;
+              if (c < 0 || next == kWrecNone || !rec_load_marks(op, M, next, n_cur, lane, &after)) {
+                if (ls.error_flag) *ls.error_flag = 5;
+                break;
+              }
+              off = after;
+            } else {
+              if (marked)
+                first_chunk(s, M, r, lane, n_active, any, a, b, zlast, win, nullptr, ls.error_flag,
+                            dummy_nodes, dummy_leaves, dummy_windows);
+              else if (!next_chunk<true>(s, op, M, r, lane, n_active, any, a, b, win, nullptr,
+                                         ls.error_flag, dummy_nodes, dummy_leaves, dummy_windows, rec))
+                break;
+              marked = false;
+              n_cur = win.count;
             }
-            off = after;
+            kind_cur = SRC_LIST;
           }
-          for_each_candidate<CAND_FILTER>(kind_cur, s, M, n_cur, lane, a_min, b_max, n_active, r,
-                                          pass_b);
-        }
-        if (win.chunked && zlast > 0 && !rec.ok) {
-          first_chunk(s, M, r, lane, n_active, any, a, b, zlast, win, false, ls.error_flag,
-                      dummy_nodes, dummy_leaves, dummy_windows);
-          do for_each_candidate(win.kind, s, M, win.count, lane, a_min, b_max, n_active, r, pass_b);
-          while (next_chunk<true>(s, op, M, r, lane, n_active, any, a, b, win, false, ls.error_flag,
-                            dummy_nodes, dummy_leaves, dummy_windows, rec));
+          for_each_candidate<CAND_FILTER, true>(kind_cur, s, M, n_cur, lane, a_min, b_max, n_active,
+                                                r, ops, any, lo, hi, [] {}, pass_b, put_b, marked);
         }
       }
 
@@ -2367,12 +2623,11 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
       const bool empty = go && nhit == 0;
       if (!from_rec && op.ess && win.kind == SRC_LIST && !win.chunked && ballot(empty)) {
         const float bmin = wave_min(empty ? b : kInf);
-        for_each_candidate(SRC_LIST, s, M, win.count, lane, bmin, kInf, n_active, r,
-                           [&](int j, const Gauss &g) {
-          const bool want = empty;
-          const Chord c = chord(g, r);
-          if (want && c.exists && c.tout >= b && c.tin <= win.hi) best = fminf(best, fmaxf(c.tin, b));
-        });
+        for_each_candidate<CAND_ALL, false>(SRC_LIST, s, M, win.count, lane, bmin, kInf, n_active,
+                                            r, ops, empty, b, win.hi, [] {},
+                                            [&](int, int, const Cand &g, bool hit) {
+          if (hit) best = fminf(best, fmaxf(g.ch.tin, b));
+        }, [](int, int) {});
       }
       if (go) step_after(op, grid, nhit > 0, best, tn, dS, b, ss);
     }
@@ -2417,13 +2672,23 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t n, const int32_t *__re
   for (int jj = 0; jj < 3; jj++)
     put(gm[3 * u + jj], -2.0f * (G[G_M + jj] * Z[0] + G[G_M + 3 + jj] * Z[1] + G[G_M + 6 + jj] * Z[2]));
   // dL/dl_i = -2 sum z_i^2 dq
-  for (int k = 0; k < 3; k++) put(gl[3 * u + k], -2.0f * A[12 + k]);
-  // dL/dR_ji = 2 G'_ij / s_i
+  put(gl[3 * u], -2.0f * A[3]);
+  put(gl[3 * u + 1], -2.0f * A[6]);
+  put(gl[3 * u + 2], -2.0f * A[8]);
+  // dL/dR_ji = 2 G'_ij / s_i with G' = sum dq z x^T, x = R S z the world
+  // offset from the mean: G'_ij = sum_l (sum dq z_i z_l) s_l R_jl
   const float *X = aux + (size_t)kAuxFloats * i;
-  float dR[9];
-  for (int ii = 0; ii < 3; ii++)
-    for (int jj = 0; jj < 3; jj++) dR[3 * jj + ii] = 2.0f * A[3 + 3 * ii + jj] / X[ii];
   const float w = X[3], x = X[4], y = X[5], z = X[6], qn = X[7];
+  const float R[9] = {1.0f - 2.0f * (y * y + z * z), 2.0f * (x * y - w * z), 2.0f * (x * z + w * y),
+                      2.0f * (x * y + w * z), 1.0f - 2.0f * (x * x + z * z), 2.0f * (y * z - w * x),
+                      2.0f * (x * z - w * y), 2.0f * (y * z + w * x), 1.0f - 2.0f * (x * x + y * y)};
+  const float m2[9] = {A[3], A[4], A[5], A[4], A[6], A[7], A[5], A[7], A[8]};
+  float dR[9];
+  for (int ii = 0; ii < 3; ii++) {
+    const float e0 = m2[3 * ii] * X[0], e1 = m2[3 * ii + 1] * X[1], e2 = m2[3 * ii + 2] * X[2];
+    for (int jj = 0; jj < 3; jj++)
+      dR[3 * jj + ii] = 2.0f * fmaf(e0, R[3 * jj], fmaf(e1, R[3 * jj + 1], e2 * R[3 * jj + 2])) / X[ii];
+  }
   float dq[4];
   dq[0] = 2.0f * (-z * dR[1] + y * dR[2] + z * dR[3] - x * dR[5] - y * dR[6] + x * dR[7]);
   dq[1] = 2.0f * (y * dR[1] + z * dR[2] + y * dR[3] - 2.0f * x * dR[4] - w * dR[5] + z * dR[6] +
@@ -2435,7 +2700,7 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t n, const int32_t *__re
   const float pr = dq[0] * w + dq[1] * x + dq[2] * y + dq[3] * z;
   const float qh[4] = {w, x, y, z};
   for (int k = 0; k < 4; k++) put(gq[4 * u + k], (dq[k] - pr * qh[k]) / qn);
-  put(gd[u], A[15]);
+  put(gd[u], A[9] / G[G_SIG]);
   for (int m = 0; m < sh_k; m++)
     for (int ch = 0; ch < 3; ch++) {
       put(gsh[(size_t)3 * sh_k * u + 3 * m + ch], A[16 + 16 * ch + m]);

@@ -1,0 +1,57 @@
+"""The march's candidate loop at the edges of its blocks: blocks of 64 list
+entries, groups of four candidates, against the FP64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2509_07782_amd import inputs
+
+from helpers import oracle_opts, renderer_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 63, 64, 65, 67, 128, 131])
+def test_candidate_groups_against_oracle(torch_cuda, n):
+    """n Gaussians that all cover the whole view: every segment's candidate
+    list holds about n entries, so blocks and groups of every remainder run,
+    forward, replaying backward and searching backward; brute force (blocks of
+    consecutive Gaussians) gives the same bits."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    rng = np.random.default_rng(400 + n)
+    sc = inputs.make_scene("cluster", n, 41)
+    sc["means"] = (0.05 * rng.standard_normal((n, 3))).astype(np.float32)
+    sc["log_scales"] = rng.normal(-1.2, 0.3, (n, 3)).astype(np.float32)
+    sc["density"] = (0.05 + rng.random(n)).astype(np.float32)
+    cam = inputs.look_at_camera(19, 13, (0.1, 0.2, 2.5), fov_deg=20.0)
+    r, p = renderer_for(sc)
+    o = RenderOptions(dt=0.05, ess=1, t_eps=0.0)
+    st = r.new_state()
+    rgb, T = r.forward([cam], o, state=st)
+    brute, Tb = r.forward([cam], RenderOptions(dt=0.05, ess=1, t_eps=0.0, brute_force=True))
+    assert torch.equal(rgb, brute) and torch.equal(T, Tb)
+    oo = oracle_opts(o)
+    orgb, oT, _, _ = oracle.render(sc, cam, oo)
+    # FP32 sums of n terms of order one
+    assert np.abs(rgb.cpu().numpy() - orgb).max() <= 1e-4
+    assert np.abs(T.cpu().numpy() - oT).max() <= 1e-4
+    g = np.random.default_rng(7).standard_normal(orgb.shape)
+    gt = torch.from_numpy(g.astype(np.float32)).cuda()
+    ref = oracle.backward(sc, cam, oo, np.arange(cam.n_rays), g, np.zeros(cam.n_rays))
+    for state_opts in (o, RenderOptions(dt=0.05, ess=1, t_eps=0.0, no_record=True)):
+        s2 = r.new_state()
+        rgb2, T2 = r.forward([cam], state_opts, state=s2)
+        grads = r.backward(s2, rgb2, T2, gt, None, p)
+        for k, v in grads.items():
+            a = v.cpu().numpy().astype(np.float64)
+            assert np.linalg.norm(a - ref[k]) <= 1e-3 * max(np.linalg.norm(ref[k]), 1e-30), (k, n)
+    r.check_errors()
