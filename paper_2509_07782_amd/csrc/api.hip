@@ -88,7 +88,7 @@ struct rgx_bvh {
   int sorted_sel = 0;
   uint64_t serial = 0;              // the context's build serial of the current contents
   DevBuf geom_user, aabb_user, aux_user, aux, active, bounds, counters, keys0, keys1, vals0, vals1, hist, geom,
-      aabb, col, nodes, nodes4, seg, acc, zsum, sg_user, sgrec, sgacc;
+      aabb, col, nodes, nodes4, quads, sup, seg, acc, zsum, sg_user, sgrec, sgacc;
 };
 
 // Forward state: what one forward rendered and what its searches found.
@@ -206,7 +206,7 @@ void rgx_bvh_destroy(rgx_bvh *b) {
   if (!b) return;
   DevBuf *all[] = {&b->geom_user, &b->aabb_user, &b->aux_user, &b->aux, &b->active, &b->bounds, &b->counters, &b->keys0,
                    &b->keys1, &b->vals0, &b->vals1, &b->hist, &b->geom, &b->aabb, &b->col,
-                   &b->nodes, &b->nodes4, &b->seg, &b->acc, &b->zsum,
+                   &b->nodes, &b->nodes4, &b->quads, &b->sup, &b->seg, &b->acc, &b->zsum,
                    &b->sg_user, &b->sgrec, &b->sgacc};
   for (DevBuf *d : all) release(*d);
   delete b;
@@ -263,6 +263,8 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   ENS(col, (size_t)n * col_stride * 4);
   ENS(nodes, nodes_n * 16 * 4);
   ENS(nodes4, nodes_n * kNode4Floats * 4);
+  ENS(quads, nodes_n * kQuadFloats * 4);
+  ENS(sup, (size_t)n * kSupFloats * 4);
   int64_t P = 1;
   while (P < n) P <<= 1;
   ENS(seg, (size_t)(2 * P) * 6 * 4);
@@ -306,6 +308,8 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   a.geom = (float *)b->geom.p; a.aabb = (float *)b->aabb.p; a.col = (float *)b->col.p;
   a.nodes = (float *)b->nodes.p; a.seg = (float *)b->seg.p;
   a.nodes4 = (float *)b->nodes4.p;
+  a.quads = (float *)b->quads.p;
+  a.sup = (float *)b->sup.p;
   e = timed(ctx, RGX_KERN_BUILD, stream, [&] {
     hipError_t r = launch_build(a, stream);
     if (r == hipSuccess) r = launch_fill(b->acc.p, n * kAccFloats, 0u, stream);
@@ -331,6 +335,8 @@ static SceneDev scene_of(const rgx_bvh *b) {
   s.col = (const float *)b->col.p;
   s.nodes = (const float *)b->nodes.p;
   s.nodes4 = (const float *)b->nodes4.p;
+  s.quads = (const float *)b->quads.p;
+  s.sup = (const float *)b->sup.p;
   s.aabb = (const float *)b->aabb.p;
   s.counters = (const int32_t *)b->counters.p;
   s.perm = (const uint32_t *)(b->sorted_sel ? b->vals1.p : b->vals0.p);

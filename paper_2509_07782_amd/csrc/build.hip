@@ -292,6 +292,27 @@ __global__ __launch_bounds__(256) void k_gather_rows(int64_t n, const int32_t *_
   dst[f] = k < src_cols ? src[(size_t)perm[i] * src_stride + k] : 0.0f;
 }
 
+// Leaf-test records (Z order) from the packed geometry and aux records:
+// N = k S R^T, R from the unit quaternion.
+__global__ __launch_bounds__(256) void k_pack_support(int64_t n, const int32_t *__restrict__ counters,
+                                                      const float4 *__restrict__ geom,
+                                                      const float4 *__restrict__ aux,
+                                                      float4 *__restrict__ sup) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n || i >= counters[0]) return;
+  const float4 g0 = geom[4 * i], g3 = geom[4 * i + 3], a0 = aux[2 * i], a1 = aux[2 * i + 1];
+  const float k = sqrtf(g0.w);
+  const float w = a0.w, x = a1.x, y = a1.y, z = a1.z;
+  const float k0 = k * a0.x, k1 = k * a0.y, k2 = k * a0.z;
+  sup[4 * i] = make_float4(g0.x, g0.y, g0.z, g3.w);
+  sup[4 * i + 1] = make_float4(k0 * (1.0f - 2.0f * (y * y + z * z)), k0 * 2.0f * (x * y + w * z),
+                               k0 * 2.0f * (x * z - w * y), fmaxf(k0, fmaxf(k1, k2)));
+  sup[4 * i + 2] = make_float4(k1 * 2.0f * (x * y - w * z), k1 * (1.0f - 2.0f * (x * x + z * z)),
+                               k1 * 2.0f * (y * z + w * x), 0.0f);
+  sup[4 * i + 3] = make_float4(k2 * 2.0f * (x * z + w * y), k2 * 2.0f * (y * z - w * x),
+                               k2 * (1.0f - 2.0f * (x * x + y * y)), 0.0f);
+}
+
 // Z-ordered colour records in the layout of the march's matrix operands:
 // [channel][k][q] of coefficient m = 4q + k, zero past the degree, so that one
 // 16-byte read gives a lane its coefficients of all four inner steps.
@@ -422,7 +443,8 @@ __global__ __launch_bounds__(256) void k_lbvh_hierarchy(int64_t n_max,
 // child is that child's binary index.
 __global__ __launch_bounds__(256) void k_bvh4(int64_t n_max, const int32_t *__restrict__ counters,
                                               const float4 *__restrict__ nodes,
-                                              float *__restrict__ nodes4) {
+                                              float *__restrict__ nodes4,
+                                              float4 *__restrict__ quads) {
   const int n = counters[0];
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int n_inner = n > 1 ? n - 1 : 1;
@@ -480,6 +502,20 @@ __global__ __launch_bounds__(256) void k_bvh4(int64_t n_max, const int32_t *__re
   float4 *out = reinterpret_cast<float4 *>(nodes4 + (size_t)kNode4Floats * i);
   for (int k = 0; k < kNode4Floats / 4; k++)
     out[k] = make_float4(f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3]);
+  float4 *qd = quads + (size_t)(kQuadFloats / 4) * i;
+  for (int k = 0; k < 4; k++) {
+    float c[3] = {0.0f, 0.0f, 0.0f}, h[3] = {0.0f, 0.0f, 0.0f};
+    if (k < m)
+      for (int a = 0; a < 3; a++) {
+        // half-extents rounded outward: [c - h, c + h] holds [lo, hi]
+        const float lo = f[6 * k + a], hi = f[6 * k + 3 + a];
+        c[a] = 0.5f * lo + 0.5f * hi;
+        h[a] = fmaxf(hi - c[a], c[a] - lo) * 1.000001f;
+      }
+    qd[2 * k] = make_float4(c[0], c[1], c[2], h[0]);
+    qd[2 * k + 1] = make_float4(h[1], h[2], __int_as_float(k < m ? lk[k] : kNoChild),
+                                k < m ? f[28 + 2 * k] : __int_as_float(0x7fffffff));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -513,6 +549,9 @@ hipError_t launch_build(const BuildArgs &a, hipStream_t st) {
   k_gather_rows<<<nblk(n * kAuxFloats, 256), 256, 0, st>>>(n, a.counters, perm, a.aux_user,
                                                            kAuxFloats, kAuxFloats, a.aux,
                                                            kAuxFloats);
+  k_pack_support<<<nblk(n, 256), 256, 0, st>>>(n, a.counters, reinterpret_cast<const float4 *>(a.geom),
+                                               reinterpret_cast<const float4 *>(a.aux),
+                                               reinterpret_cast<float4 *>(a.sup));
   k_pack_colour<<<nblk(n * kColFloats, 256), 256, 0, st>>>(n, a.counters, perm, a.sh, a.sh_k, a.col);
   if (a.n_sg > 0) {
     k_sg_pack<<<nblk(n, 256), 256, 0, st>>>(n, a.n_sg, a.sg, a.sg_user);
@@ -527,7 +566,7 @@ hipError_t launch_build(const BuildArgs &a, hipStream_t st) {
   k_lbvh_hierarchy<<<nblk(n, 256), 256, 0, st>>>(n, a.counters, a.keys[cur], a.aabb, a.seg, P,
                                                  reinterpret_cast<float4 *>(a.nodes));
   k_bvh4<<<nblk(n, 256), 256, 0, st>>>(n, a.counters, reinterpret_cast<const float4 *>(a.nodes),
-                                       a.nodes4);
+                                       a.nodes4, reinterpret_cast<float4 *>(a.quads));
   return hipGetLastError();
 }
 

@@ -19,6 +19,14 @@ constexpr int kColFloats = 48;            // colour record: 3 channels x 16 SH c
 // 4-wide node record: 4 child boxes (lo xyz, hi xyz), 4 child links (>= 0
 // 4-wide node, < 0 leaf ~j, kNoChild none), 4 leaf ranges (first, last).
 constexpr int kNode4Floats = 36;
+// The same node for the window collection, one child per lane of a quad: 4
+// children x (box centre xyz, half-extents xyz, link, first leaf), 128 bytes;
+// absent children have link kNoChild and a first leaf past every range.
+constexpr int kQuadFloats = 32;
+// Support record of the collection's leaf test: mean xyz, bounding-sphere
+// radius, then the rows of N = k S R^T (|N x| is the ellipsoid's support
+// along a unit x), the first row followed by k max(s).
+constexpr int kSupFloats = 16;
 constexpr int kAuxFloats = 8;             // s.xyz, unit quaternion (w,x,y,z), |q|
 // Spherical-Gaussian colour lobes (the 9 SH + 7 SG appearance model): up to
 // kMaxSg lobes per Gaussian, kSgLobeFloats per lobe in the packed record:

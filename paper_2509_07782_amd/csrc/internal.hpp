@@ -27,6 +27,8 @@ struct BuildArgs {
   // outputs (Z order)
   float *geom, *aabb, *col, *aux, *nodes;
   float *nodes4;             // 4-wide nodes, one per binary internal node, same index
+  float *quads;              // the 4-wide nodes in the collection's layout, same index
+  float *sup;                // [n, kSupFloats] leaf-test records
   float *seg;                // segment tree of leaf boxes, 2P boxes
 };
 hipError_t launch_build(const BuildArgs &a, hipStream_t st);
@@ -45,6 +47,8 @@ struct SceneDev {
   const float *col;           // [n,col_stride]
   const float *nodes;         // [max(n-1,1),16]
   const float *nodes4;        // [max(n-1,1),36] 4-wide nodes, one per binary internal node
+  const float *quads;         // [max(n-1,1),32] the same nodes, one child per lane of a quad
+  const float *sup;           // [n,16] leaf-test records
   const float *aabb;          // [n,6]
   const int32_t *counters;    // [0] = active count
   const uint32_t *perm;       // Z index -> user index

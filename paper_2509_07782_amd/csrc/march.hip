@@ -738,13 +738,19 @@ __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts 
 // range [z0, z1), with a conservative depth interval for each.  Every test is
 // against the packet as a whole: the bounding cone of the rays (apex at the
 // shared camera centre) and the shell between the nearest window start and
-// the farthest window end, applied to bounding spheres (of a node's child
-// boxes, of a leaf's ellipsoid).  Exact per-ray chords are left to the
-// segment loop, which computes them anyway.  The traversal is node-parallel:
-// the frontier of (node, first leaf) is an LDS stack ordered by first leaf,
-// smallest on top; each round hands the (up to) 64 lowest subtrees to the 64
-// lanes, which load them independently, and their children go back on top in
-// order -- a 64-wide depth-first walk in Z order, whose frontier stays narrow.
+// the farthest window end, applied to the boxes of 4-wide nodes and to the
+// leaves' ellipsoids.  Exact per-ray chords are left to the segment loop,
+// which computes them anyway.  The traversal is node-parallel: the frontier of
+// (node, first leaf) is an LDS stack ordered by first leaf, smallest on top;
+// each round takes the (up to) 64 lowest subtrees, four lanes to a node and
+// one child box to a lane, and their children go back on top in order -- a
+// 64-wide depth-first walk in Z order, whose frontier stays narrow.  What
+// bounds it is memory latency and the cache's rate of scattered 16-byte reads:
+// a quad reads its node's 128 bytes as whole lines (two reads a lane for four
+// children, against four 64-byte gathers for two children of a binary node),
+// and a round of 64 nodes does the work of three binary ones.  1M Gaussians,
+// 4 x 1024x768: 13.1k binary nodes a tile -> 6.7k, forward 39.7 -> 34.5 ms;
+// 1920x1080 frame 21.0 -> 17.7 ms; 5M Gaussians, 257x193: 95 -> 75 ms.
 // When
 // the frontier or the list would overflow, z1 is lowered (a radix select over
 // the pending Z indices) and everything at or beyond it is dropped, so the
@@ -754,13 +760,13 @@ __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts 
 // list -- the order of brute force.
 
 constexpr int kRingCap = 256;    // frontier (stack) entries
-constexpr int kStageCap = 160;   // staged leaves; a round adds at most 2 per node
+constexpr int kStageCap = 320;   // staged leaves; a round adds at most 4 per node
 constexpr int kListCap = 512;    // window list entries (multiple of 64, at most 512)
 
 struct WaveMem {
   float rlo[64], rhi[64];          // the rays' windows
   struct {                         // traversal state, kept while a collection is paused
-    int32_t ring_id[kRingCap], ring_first[kRingCap];
+    int2 ring[kRingCap];           // (4-wide node, its first leaf)
     int32_t st_id[kStageCap];
   } c;
   uint16_t order[kListCap];        // slots of the current chunk's entries, in Z-index order
@@ -779,6 +785,11 @@ template <> struct StatMemOf<true> : StatMem {};
 
 __device__ __forceinline__ uint64_t join64(uint32_t lo, uint32_t hi) {
   return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
+// Set bits of a mask in the lanes before this one.
+__device__ __forceinline__ int count_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 __device__ __forceinline__ uint64_t lanes_below(int lane) {
@@ -859,20 +870,16 @@ __device__ __forceinline__ int compact_ring(WaveMem &M, int lane, int head, int 
   int base = head;
   for (int e0 = head; e0 < tail; e0 += 64) {
     const int e = e0 + lane;
-    const int slot = e;
-    int id = 0, first = 0;
+    int2 v = make_int2(0, 0);
     bool keep = false;
     if (e < tail) {
-      id = M.c.ring_id[slot];
-      first = M.c.ring_first[slot];
-      keep = first < z1;
+      v = M.c.ring[e];
+      keep = v.y < z1;
     }
     __builtin_amdgcn_wave_barrier();
     const uint64_t b = ballot(keep);
     if (keep) {
-      const int d = base + __popcll(b & below);
-      M.c.ring_id[d] = id;
-      M.c.ring_first[d] = first;
+      M.c.ring[base + __popcll(b & below)] = v;
     }
     base += __popcll(b);
     __builtin_amdgcn_wave_barrier();
@@ -949,10 +956,13 @@ __device__ __forceinline__ int sort_list(WaveMem &M, int lane, int count, int zc
 }
 
 // The packet bound: apex o, unit axis u, half-angle (cos, sin) padded
-// outward, and the depth shell [t_lo, t_hi] (distances from o).
+// outward, and the depth shell [t_lo, t_hi] (distances from o).  Rays spread
+// too far for the angular tests leave `narrow` false and get (cos, sin) =
+// (0, 1), with which the box test only keeps the half-space ahead.
 struct Cone {
   float ux, uy, uz, cs, sn, t_lo, t_hi;
-  bool narrow;   // false: rays spread too far for the angular test
+  float du;      // bound of |d - u| over the rays
+  bool narrow;
 };
 
 __device__ __forceinline__ Cone packet_cone(const WaveMem &M, const Ray &self, int lane,
@@ -973,14 +983,45 @@ __device__ __forceinline__ Cone packet_cone(const WaveMem &M, const Ray &self, i
   k.narrow = n2 > 0.0f && cs > 0.5f;
   k.sn = fminf(sn * 1.0001f + 2e-6f, 1.0f);
   k.cs = sqrtf(fmaxf(1.0f - k.sn * k.sn, 0.0f));
+  if (!k.narrow) { k.sn = 1.0f; k.cs = 0.0f; }
+  k.du = k.sn * sqrtf(2.0f / (1.0f + k.cs));
   k.t_lo = wave_min(mine ? M.rlo[lane] : kInf);
   k.t_hi = wave_max(mine ? M.rhi[lane] : -kInf);
   return k;
 }
 
-// Conservative: false only if no point of the sphere (centre v relative to
-// the apex, radius rho) lies on a ray of the packet at a depth inside the
-// shell.  On true, [*dlo, *dhi] bounds the depth of every such point.
+// Conservative test of a box (centre v relative to the apex, half-extents h)
+// against the packet: false only if no point of the box lies on a ray of the
+// packet at a depth inside the shell.  The box's exact distance from the apex
+// bounds the depth from below (near the apex, inside dense clusters, an axial
+// bound is much weaker: config 4's tiles tested 19.1k leaves against 11.2k).
+// From above, along the axis the box reaches v.u + h.|u|, and a ray point at
+// depth t lies in [t cos, t].
+// Across it, with p = v - (v.u) u, every box point has a distance of at least
+// |p| - h.|p| / |p| from the axis, and a cone point at most tan times its
+// axial coordinate; the inequality is taken times |p| to need no division.
+// Margins: 2e-5 of the distance (rounding of v, v.u and p), 1e-3 of the
+// box's extent across.
+__device__ __forceinline__ bool cone_box(const Cone &k, float vx, float vy, float vz, float hx,
+                                         float hy, float hz) {
+  const float al = fmaf(vx, k.ux, fmaf(vy, k.uy, vz * k.uz));
+  const float ru = fmaf(hx, fabsf(k.ux), fmaf(hy, fabsf(k.uy), hz * fabsf(k.uz)));
+  const float px = fmaf(-al, k.ux, vx), py = fmaf(-al, k.uy, vy), pz = fmaf(-al, k.uz, vz);
+  const float p2 = fmaf(px, px, fmaf(py, py, pz * pz));
+  const float rp = fmaf(hx, fabsf(px), fmaf(hy, fabsf(py), hz * fabsf(pz)));
+  const float pw = __builtin_amdgcn_sqrtf(p2);
+  const float pad = fmaf(fabsf(al) + pw, 2e-5f, 1e-6f);
+  const float far = al + ru + pad;
+  const float qx = fmaxf(fabsf(vx) - hx, 0.0f), qy = fmaxf(fabsf(vy) - hy, 0.0f),
+              qz = fmaxf(fabsf(vz) - hz, 0.0f);
+  const float near2 = fmaf(qx, qx, fmaf(qy, qy, qz * qz)), reach = k.t_hi + pad;
+  return (near2 <= reach * reach) & (far >= k.t_lo * k.cs) & (far >= 0.0f) &
+         (fmaf(-1.001f, rp, p2) * k.cs <= fmaf(far, k.sn, pad) * pw);
+}
+
+// Depth bounds of the packet's rays inside a sphere (centre v relative to the
+// apex, radius rho), and whether the sphere can meet the packet at all; used
+// for packets too wide for the ellipsoid's own test.
 __device__ __forceinline__ bool cone_sphere(const Cone &k, float vx, float vy, float vz, float rho,
                                             float *dlo, float *dhi) {
   const float d = sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
@@ -988,96 +1029,48 @@ __device__ __forceinline__ bool cone_sphere(const Cone &k, float vx, float vy, f
   const float pad = fmaf(d, 1e-5f, rho * 1.001f);
   *dlo = d - pad;
   *dhi = d + pad;
-  if (*dlo > k.t_hi || *dhi < k.t_lo) return false;
   const float al = fmaf(vx, k.ux, fmaf(vy, k.uy, vz * k.uz));
-  if (al + pad < 0.0f) return false;
-  if (!k.narrow) return true;
-  const float wx = vy * k.uz - vz * k.uy, wy = vz * k.ux - vx * k.uz, wz = vx * k.uy - vy * k.ux;
-  const float perp = sqrtf(fmaf(wx, wx, fmaf(wy, wy, wz * wz)));
-  return fmaf(perp, k.cs, -al * k.sn) <= pad;
+  return (*dlo <= k.t_hi) & (*dhi >= k.t_lo) & (al + pad >= 0.0f);
 }
 
-// Conservative test of an AABB against the packet, on the box itself: the
-// depth shell through the box's exact distance range from the apex; the cone
-// through the box's extent across and along the axis (every box point p has
-// |p_perp| >= |c_perp| - r_w and p.u <= c.u + r_u, r_w and r_u the box's
-// supports along the unit perpendicular of its centre and along the axis).
-__device__ __forceinline__ bool cone_box(const Cone &k, const Ray &o, float lx, float ly, float lz,
-                                         float hx, float hy, float hz) {
-  const float cx = fmaf(0.5f, lx + hx, -o.ox), cy = fmaf(0.5f, ly + hy, -o.oy),
-              cz = fmaf(0.5f, lz + hz, -o.oz);
-  const float ex = 0.5f * (hx - lx), ey = 0.5f * (hy - ly), ez = 0.5f * (hz - lz);
-  const float ax = fabsf(cx), ay = fabsf(cy), az = fabsf(cz);
-  const float qx = fmaxf(ax - ex, 0.0f), qy = fmaxf(ay - ey, 0.0f), qz = fmaxf(az - ez, 0.0f);
-  const float fx = ax + ex, fy = ay + ey, fz = az + ez;
-  const float dmin = sqrtf(fmaf(qx, qx, fmaf(qy, qy, qz * qz)));
-  const float dmax = sqrtf(fmaf(fx, fx, fmaf(fy, fy, fz * fz)));
-  const float pad = fmaf(dmax, 2e-5f, 1e-6f);
-  if (dmin - pad > k.t_hi || dmax + pad < k.t_lo) return false;
-  const float al = fmaf(cx, k.ux, fmaf(cy, k.uy, cz * k.uz));
-  const float ru = fmaf(ex, fabsf(k.ux), fmaf(ey, fabsf(k.uy), ez * fabsf(k.uz)));
-  if (al + ru + pad < 0.0f) return false;
-  if (!k.narrow) return true;
-  const float wx = cy * k.uz - cz * k.uy, wy = cz * k.ux - cx * k.uz, wz = cx * k.uy - cy * k.ux;
-  const float pw = sqrtf(fmaf(wx, wx, fmaf(wy, wy, wz * wz)));
-  // unit perpendicular of the centre: c - (c.u) u, normalised by |c x u|
-  const float px = fmaf(-al, k.ux, cx), py = fmaf(-al, k.uy, cy), pz = fmaf(-al, k.uz, cz);
-  const float rw = fmaf(ex, fabsf(px), fmaf(ey, fabsf(py), ez * fabsf(pz))) *
-                   __builtin_amdgcn_rcpf(fmaxf(pw, 1e-30f));
-  // margins: 1e-3 of the box extent for the rounding of the perpendicular
-  // direction, 2e-5 of the distance for the rest
-  const float slack = fmaf(rw, 1e-3f, pad);
-  return fmaf(pw - rw, k.cs, -(al + ru) * k.sn) <= slack;
-}
-
-// Depth bounds [lo, hi] of every ray of the packet inside one ellipsoid, and
-// whether the ellipsoid can meet the cone at all (returned)
-// (centre v relative to the apex, size k, scales s, unit quaternion q): a
-// point o + t d of the ellipsoid satisfies |t - v.d| <= k |S R^T d| (its
-// support along d), v.d ranges over [|v| cos(phi + theta), |v| cos(phi - theta)]
-// for the angle phi between v and the axis, and |S R^T d| <= |S R^T u| +
-// max(s) |d - u| with |d - u| <= sin(theta) sqrt(2 / (1 + cos(theta))).
-__device__ __forceinline__ bool support_bounds(const Cone &k, float vx, float vy, float vz,
-                                               float kk, float sx, float sy, float sz, float qw,
-                                               float qx, float qy, float qz, float *lo,
-                                               float *hi) {
-  // w = R^T u, R the rotation of the unit quaternion
-  const float R00 = 1.0f - 2.0f * (qy * qy + qz * qz), R01 = 2.0f * (qx * qy - qw * qz),
-              R02 = 2.0f * (qx * qz + qw * qy);
-  const float R10 = 2.0f * (qx * qy + qw * qz), R11 = 1.0f - 2.0f * (qx * qx + qz * qz),
-              R12 = 2.0f * (qy * qz - qw * qx);
-  const float R20 = 2.0f * (qx * qz - qw * qy), R21 = 2.0f * (qy * qz + qw * qx),
-              R22 = 1.0f - 2.0f * (qx * qx + qy * qy);
-  const float w0 = sx * fmaf(R00, k.ux, fmaf(R10, k.uy, R20 * k.uz));
-  const float w1 = sy * fmaf(R01, k.ux, fmaf(R11, k.uy, R21 * k.uz));
-  const float w2 = sz * fmaf(R02, k.ux, fmaf(R12, k.uy, R22 * k.uz));
-  const float du = k.sn * sqrtf(2.0f / (1.0f + k.cs));
-  const float ext = kk * fmaf(fmaxf(sx, fmaxf(sy, sz)), du, sqrtf(fmaf(w0, w0, fmaf(w1, w1, w2 * w2))));
-  const float d = sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
+// Depth bounds [lo, hi] of every ray of a narrow packet inside one ellipsoid,
+// and whether the ellipsoid can meet the packet at all (returned).  v is its
+// centre relative to the apex, N = k S R^T (rows n0..n2), so that |N x| is its
+// support along a unit x, and kmax = k max(s).  A point o + t d of it
+// satisfies |t - v.d| <= |N d|; v.d ranges over [|v| cos(phi + theta),
+// |v| cos(phi - theta)] for the angle phi between v and the axis, and
+// |N d| <= |N u| + kmax |d - u|.  The cone: every point p of the ellipsoid has
+// |p_perp| >= perp - r_w and p.u <= al + r_u, r_w = |N p| / perp and r_u =
+// |N u| its supports along the unit perpendicular of the centre and along the
+// axis (the inequality taken times perp).
+__device__ __forceinline__ bool cone_ellipsoid(const Cone &k, float vx, float vy, float vz,
+                                               const vf4 &n0, const vf4 &n1, const vf4 &n2,
+                                               float kmax, float rad, float *lo, float *hi) {
+  const float w0 = fmaf(n0.x, k.ux, fmaf(n0.y, k.uy, n0.z * k.uz));
+  const float w1 = fmaf(n1.x, k.ux, fmaf(n1.y, k.uy, n1.z * k.uz));
+  const float w2 = fmaf(n2.x, k.ux, fmaf(n2.y, k.uy, n2.z * k.uz));
+  const float ru = __builtin_amdgcn_sqrtf(fmaf(w0, w0, fmaf(w1, w1, w2 * w2)));
+  const float ext = fmaf(kmax, k.du, ru);
+  const float d = __builtin_amdgcn_sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
   const float al = fmaf(vx, k.ux, fmaf(vy, k.uy, vz * k.uz));
-  const float cx = vy * k.uz - vz * k.uy, cy = vz * k.ux - vx * k.uz, cz = vx * k.uy - vy * k.ux;
-  const float perp = sqrtf(fmaf(cx, cx, fmaf(cy, cy, cz * cz)));
+  const float px = fmaf(-al, k.ux, vx), py = fmaf(-al, k.uy, vy), pz = fmaf(-al, k.uz, vz);
+  const float p2 = fmaf(px, px, fmaf(py, py, pz * pz));
+  const float perp = __builtin_amdgcn_sqrtf(p2);
   // phi >= theta <=> perp cos(theta) >= al sin(theta); phi <= 90 deg <=> al >= 0
   const float c_hi = perp * k.cs >= al * k.sn ? fmaf(al, k.cs, perp * k.sn) : d;
   const float c_lo = al >= 0.0f ? fmaf(al, k.cs, -perp * k.sn) : -d;
-  // margins: FP32 chord ends near tangency, rotation and norm rounding
-  const float pad = fmaf(ext, 1e-3f, fmaf(d, 1e-5f, 1e-6f));
-  *lo = c_lo - ext - pad;
-  *hi = c_hi + ext + pad;
-  // the cone: every point p of the ellipsoid has |p_perp| >= perp - r_w and
-  // p.u <= al + r_u, with r_w, r_u its supports along the unit perpendicular
-  // of the centre and along the axis
-  if (!(perp > 0.0f)) return true;
-  const float ip = __builtin_amdgcn_rcpf(perp);
-  const float px = fmaf(-al, k.ux, vx) * ip, py = fmaf(-al, k.uy, vy) * ip,
-              pz = fmaf(-al, k.uz, vz) * ip;
-  const float y0 = sx * fmaf(R00, px, fmaf(R10, py, R20 * pz));
-  const float y1 = sy * fmaf(R01, px, fmaf(R11, py, R21 * pz));
-  const float y2 = sz * fmaf(R02, px, fmaf(R12, py, R22 * pz));
-  const float rw = kk * sqrtf(fmaf(y0, y0, fmaf(y1, y1, y2 * y2)));
-  const float ru = kk * sqrtf(fmaf(w0, w0, fmaf(w1, w1, w2 * w2)));
-  const float slack = fmaf(rw + ru, 1e-3f, fmaf(d, 2e-5f, 1e-6f));
-  return fmaf(perp - rw, k.cs, -(al + ru) * k.sn) <= slack;
+  // margins: FP32 chord ends near tangency, rounding of N and the norms
+  const float pad = fmaf(ext, 1e-3f, fmaf(d, 2e-5f, 1e-6f));
+  // (the bounding sphere's own depth range is the tighter one off the axis)
+  const float out = fmaf(rad, 1e-3f, rad + pad);
+  *lo = fmaxf(c_lo - ext - pad, d - out);
+  *hi = fminf(c_hi + ext + pad, d + out);
+  const float y0 = fmaf(n0.x, px, fmaf(n0.y, py, n0.z * pz));
+  const float y1 = fmaf(n1.x, px, fmaf(n1.y, py, n1.z * pz));
+  const float y2 = fmaf(n2.x, px, fmaf(n2.y, py, n2.z * pz));
+  const float rwp = __builtin_amdgcn_sqrtf(fmaf(y0, y0, fmaf(y1, y1, y2 * y2)));
+  return (*lo <= k.t_hi) & (*hi >= k.t_lo) &
+         (fmaf(-1.001f, rwp, p2) * k.cs <= fmaf(al + ru, k.sn, pad) * perp);
 }
 
 // Wave-uniform state of a window collection.  The list holds the entries
@@ -1104,10 +1097,7 @@ __device__ __forceinline__ void trav_start(WaveMem &M, int lane, Trav &t, uint64
   t.count = 0;
   t.visits = 0;
   t.paused = false;
-  if (lane == 0) {
-    M.c.ring_id[0] = 0;
-    M.c.ring_first[0] = 0;
-  }
+  if (lane == 0) M.c.ring[0] = make_int2(0, 0);
   __builtin_amdgcn_wave_barrier();
 }
 
@@ -1143,6 +1133,19 @@ __device__ __forceinline__ void trav_advance(WaveMem &M, int lane, Trav &t) {
   t.paused = false;
 }
 
+// Moves the staged leaves [head, staged) to the front; returns their number.
+__device__ __forceinline__ int stage_front(WaveMem &M, int lane, int head, int staged) {
+  const int rest = staged - head;
+  for (int e0 = 0; e0 < rest; e0 += 64) {   // a write never passes an unread entry
+    const int e = e0 + lane;
+    const int v = e < rest ? M.c.st_id[head + e] : 0;
+    __builtin_amdgcn_wave_barrier();
+    if (e < rest) M.c.st_id[e] = v;
+    __builtin_amdgcn_wave_barrier();
+  }
+  return rest;
+}
+
 // Runs (or resumes) the collection until it completes or pauses; sorts the
 // finished chunk's entries into M.order and returns their number, or -1 on
 // a malformed tree (error flag set).
@@ -1166,101 +1169,106 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
   const uint64_t below = lanes_below(lane);
   for (;;) {
     __builtin_amdgcn_wave_barrier();
-    const int n = min(min(64, sp), (kStageCap - staged) >> 1);
+    // the frontier never grows past its end: a node adds at most three
+    const int n = min(min(64, sp), min((kStageCap - staged) >> 2, max(1, (kRingCap - sp) / 3)));
     if (n > 0) {
-      int id = 0;
-      bool live = false;
-      if (lane < n) {                            // lane 0 takes the top (lowest Z)
-        const int slot = sp - 1 - lane;
-        id = M.c.ring_id[slot];
-        live = M.c.ring_first[slot] < z1;      // else cut off by a later z1
+      // four lanes to a node, one child each; 16 nodes at a time, all their
+      // records requested before the first is tested
+      const int child = lane & 3;
+      vf4 q0[4], q1[4];
+      bool live[4];
+#pragma unroll
+      for (int b = 0; b < 4; b++) {
+        live[b] = false;
+        if (16 * b >= n) continue;
+        const int i = 16 * b + (lane >> 2);      // node 0 is the top (lowest Z)
+        const int2 v = M.c.ring[max(sp - 1 - i, 0)];
+        live[b] = (i < n) & (v.y < z1);          // else cut off by a later z1
+        const vf4 *np = reinterpret_cast<const vf4 *>(s.quads) + (kQuadFloats / 4) * (live[b] ? v.x : 0) + 2 * child;
+        q0[b] = np[0];
+        q1[b] = np[1];
       }
       sp -= n;
-      visits += __popcll(ballot(live));
-      if (visits > n_inner) { if (err) *err = 2; t.count = 0; t.sp = 0; t.staged = 0; return -1; }
-      vf4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0}, c = {0, 0, 0, 0}, d = {0, 0, 0, 0};
-      if (live) {
-        const vf4 *np = reinterpret_cast<const vf4 *>(s.nodes) + 4 * id;
-        a = np[0]; b = np[1]; c = np[2]; d = np[3];
-      }
-      const int cl = live ? __float_as_int(a.w) : kNoChild;
-      const int cr = live ? __float_as_int(b.w) : kNoChild;
-      const int nlo = __float_as_int(c.w), nhi = __float_as_int(d.w);
-      const int gamma = cl < 0 ? ~cl : cl;       // left range [nlo, gamma], right [gamma+1, nhi]
-      // validity of the links and ranges (a malformed tree ends the walk),
-      // then the Z-range and packet tests: plain conjunctions, so that they
-      // stay in lane masks instead of branching on every term
-      const bool badL = cl >= 0 ? cl >= n_inner : ~cl >= n_active;
-      const bool badR = (cr != kNoChild) &
-                        ((cr >= 0 ? cr >= n_inner : ~cr >= n_active) |
-                         !((0 <= nlo) & (nlo <= gamma) & (gamma < nhi) & (nhi < n_active)));
-      const bool bad = live & (badL | badR);
-      if (ballot(bad)) { if (err) *err = 3; t.count = 0; t.sp = 0; t.staged = 0; return -1; }
-      const bool inL = live & (nlo < z1) & (gamma >= z0);
-      const bool inR = live & (cr != kNoChild) & (gamma + 1 < z1) & (nhi >= z0);
-      const bool hL = inL & cone_box(cone, self, a.x, a.y, a.z, b.x, b.y, b.z);
-      const bool hR = inR & cone_box(cone, self, c.x, c.y, c.z, d.x, d.y, d.z);
-      // children, in lane order, left before right
-      bool lI = hL && cl >= 0, rI = hR && cr >= 0;
-      const bool lL = hL && cl < 0, rL = hR && cr < 0;
-      {
-        int tot = __popcll(ballot(lI)) + __popcll(ballot(rI));
-        if (sp + tot > kRingCap) {
-          // frontier overflow: lower z1 to keep half the pending subtrees
-          int v[kRingCap / 64 + 2];
-          bool ok[kRingCap / 64 + 2];
+      int link[4], first[4];
+      uint64_t mI[4], mL[4], bad = 0;
+      int totI = 0, totL = 0;
 #pragma unroll
-          for (int k = 0; k < kRingCap / 64; k++) {
-            const int e = lane + 64 * k;
-            ok[k] = e < sp;
-            v[k] = ok[k] ? M.c.ring_first[e] : 0;
-          }
-          v[kRingCap / 64] = nlo; ok[kRingCap / 64] = lI;
-          v[kRingCap / 64 + 1] = gamma + 1; ok[kRingCap / 64 + 1] = rI;
-          z1 = select_cut(v, ok, z0 + 1, z1, kRingCap / 2);
-          sp = compact_ring(M, lane, 0, sp, z1);
-          lI = lI && nlo < z1;
-          rI = rI && gamma + 1 < z1;
-          tot = __popcll(ballot(lI)) + __popcll(ballot(rI));
-        }
-        // the children are below every entry left on the stack; in lane
-        // order, left before right, they are ascending, so the k-th of them
-        // goes to S[sp + tot - 1 - k]
-        const uint64_t b1 = ballot(lI || rI), b2 = ballot(lI && rI);
-        const int rank = __popcll(b1 & below) + __popcll(b2 & below);
-        int pos = sp + tot - 1 - rank;
-        if (lI) {
-          M.c.ring_id[pos] = cl;
-          M.c.ring_first[pos] = nlo;
-          pos--;
-        }
-        if (rI) {
-          M.c.ring_id[pos] = cr;
-          M.c.ring_first[pos] = gamma + 1;
-        }
-        sp += tot;
+      for (int b = 0; b < 4; b++) {
+        mI[b] = mL[b] = 0;
+        link[b] = first[b] = 0;
+        if (16 * b >= n) continue;
+        visits += __popcll(ballot(live[b])) >> 2;
+        link[b] = __float_as_int(q1[b].z);
+        first[b] = __float_as_int(q1[b].w);      // an absent child's is past every range
+        // the child's Z range ends where its right sibling's starts; the
+        // last child's end is not stored, and its own children are tested
+        const int nf = __builtin_amdgcn_update_dpp(0, first[b], 0xf9, 0xf, 0xf, false);
+        const bool in = live[b] & (first[b] < z1) & ((child == 3) | (nf > z0)) &
+                        ((link[b] >= 0) | (first[b] >= z0));
+        // a malformed tree ends the walk; plain conjunctions, so that they
+        // stay in lane masks instead of branching on every term
+        bad |= ballot(in & ((first[b] < 0) |
+                            (link[b] >= 0 ? link[b] >= n_inner : ~link[b] != first[b])));
+        const bool hit = in & cone_box(cone, q0[b].x - self.ox, q0[b].y - self.oy, q0[b].z - self.oz,
+                                       q0[b].w, q1[b].x, q1[b].y);
+        mI[b] = ballot(hit & (link[b] >= 0));
+        mL[b] = ballot(hit & (link[b] < 0));
+        totI += __popcll(mI[b]);
+        totL += __popcll(mL[b]);
       }
-      {
-        // leaves past a lowered z1 are filtered when tested
-        const uint64_t b1 = ballot(lL || rL), b2 = ballot(lL && rL);
-        const int tot = __popcll(b1) + __popcll(b2);
-        int pos = staged + __popcll(b1 & below) + __popcll(b2 & below);
-        if (lL) M.c.st_id[pos++] = ~cl;
-        if (rL) M.c.st_id[pos] = ~cr;
-        staged += tot;
+      if (visits > n_inner) { if (err) *err = 2; t.count = 0; t.sp = 0; t.staged = 0; return -1; }
+      if (bad) { if (err) *err = 3; t.count = 0; t.sp = 0; t.staged = 0; return -1; }
+      if (sp + totI > kRingCap) {
+        // frontier overflow: lower z1 to keep half the pending subtrees
+        int v[kRingCap / 64 + 4];
+        bool ok[kRingCap / 64 + 4];
+#pragma unroll
+        for (int k = 0; k < kRingCap / 64; k++) {
+          const int e = lane + 64 * k;
+          ok[k] = e < sp;
+          v[k] = ok[k] ? M.c.ring[e].y : 0;
+        }
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          v[kRingCap / 64 + b] = first[b];
+          ok[kRingCap / 64 + b] = (mI[b] >> lane) & 1ull;
+        }
+        z1 = select_cut(v, ok, z0 + 1, z1, kRingCap / 2);
+        sp = compact_ring(M, lane, 0, sp, z1);
+        totI = 0;
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          mI[b] &= ballot(first[b] < z1);
+          totI += __popcll(mI[b]);
+        }
       }
+      // the children are below every entry left on the stack and, in batch
+      // and lane order, ascending: the k-th of them goes to S[sp + totI - 1 - k];
+      // leaves past a lowered z1 are filtered when tested
+      int top = sp + totI - 1, end = staged;
+#pragma unroll
+      for (int b = 0; b < 4; b++) {
+        if (16 * b >= n) continue;
+        if ((mI[b] >> lane) & 1ull) M.c.ring[top - count_below(mI[b])] = make_int2(link[b], first[b]);
+        if ((mL[b] >> lane) & 1ull) M.c.st_id[end + count_below(mL[b])] = first[b];
+        top -= __popcll(mI[b]);
+        end += __popcll(mL[b]);
+      }
+      sp += totI;
+      staged += totL;
     }
     const bool done = sp == 0;
     // tests of staged leaves, 64 at a time, in staging order: the bounding
     // sphere of the ellipsoid against the packet gives the entry's depth bounds
-    while (staged >= 64 || (done && staged > 0)) {
+    int head = 0;
+    while (staged - head >= 64 || (done && staged > head)) {
       __builtin_amdgcn_wave_barrier();
-      const int k = min(64, staged);
+      const int k = min(64, staged - head);
       if (count + k > kListCap) {
         // the list may overflow: pause at the smallest pending Z index if
         // the entries below it make a chunk
-        int zq = sp > 0 ? M.c.ring_first[sp - 1] : z1;
-        for (int e = lane; e < staged; e += 64) zq = min(zq, M.c.st_id[e]);
+        int zq = sp > 0 ? M.c.ring[sp - 1].y : z1;
+        for (int e = head + lane; e < staged; e += 64) zq = min(zq, M.c.st_id[e]);
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) zq = min(zq, __shfl_xor(zq, o, 64));
         zq = min(__builtin_amdgcn_readfirstlane(zq), z1);
@@ -1268,6 +1276,7 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
         for (int e0 = 0; e0 < count; e0 += 64)
           nb += __popcll(ballot(e0 + lane < count && M.l_id[e0 + lane] < zq));
         if (nb > 0) {
+          staged = stage_front(M, lane, head, staged);
           t.sp = sp; t.staged = staged; t.count = count; t.visits = visits; t.z1 = z1;
           t.zp = zq;
           t.paused = true;
@@ -1278,34 +1287,20 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
       int j = 0;
       bool test = false;
       if (lane < k) {
-        j = M.c.st_id[lane];
+        j = M.c.st_id[head + lane];
         test = j < z1;
       }
       bool keep = false;
       float tmin = 0.0f, tmax = 0.0f;
       if (test) {
-        const vf4 *gp = reinterpret_cast<const vf4 *>(s.geom) + 4 * j;
-        const vf4 g0 = gp[0], g3 = gp[3];
-        // the support-function record is fetched with the geometry, before
-        // the sphere test decides whether it is needed: one memory round
-        // trip per batch of leaves instead of two
-        vf4 x0 = {0.0f, 0.0f, 0.0f, 0.0f}, x1 = x0;
-        if (cone.narrow) {
-          const vf4 *ap = reinterpret_cast<const vf4 *>(s.aux) + 2 * j;
-          x0 = ap[0];
-          x1 = ap[1];
-        }
-        pin_loaded(g0); pin_loaded(g3); pin_loaded(x0); pin_loaded(x1);
-        const float vx = g0.x - self.ox, vy = g0.y - self.oy, vz = g0.z - self.oz;
-        keep = cone_sphere(cone, vx, vy, vz, g3.w, &tmin, &tmax);
-        if (keep && cone.narrow) {
-          float lo, hi;
-          const bool in_cone = support_bounds(cone, vx, vy, vz, sqrtf(g0.w), x0.x, x0.y, x0.z,
-                                              x0.w, x1.x, x1.y, x1.z, &lo, &hi);
-          tmin = fmaxf(tmin, lo);
-          tmax = fminf(tmax, hi);
-          keep = in_cone && tmin <= cone.t_hi && tmax >= cone.t_lo;
-        }
+        // one 64-byte record a leaf, in one batch of loads
+        const vf4 *np = reinterpret_cast<const vf4 *>(s.sup) + (kSupFloats / 4) * j;
+        const vf4 m = np[0], n0 = np[1], n1 = np[2], n2 = np[3];
+        pin_loaded(m); pin_loaded(n0); pin_loaded(n1); pin_loaded(n2);
+        const float vx = m.x - self.ox, vy = m.y - self.oy, vz = m.z - self.oz;
+        keep = cone.narrow ? cone_ellipsoid(cone, vx, vy, vz, n0, n1, n2, n0.w, m.w, &tmin,
+                                             &tmax)
+                           : cone_sphere(cone, vx, vy, vz, m.w, &tmin, &tmax);
       }
       if (stats && ballot(test)) {
         const int64_t c0 = clock64();
@@ -1349,20 +1344,9 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
         M.l_tout[pos] = tmax;
       }
       count += tot;
-      // move the remaining staged entries to the front
-      const int rest = staged - k;
-      int rid[2];
-      for (int e = 0; e < 2; e++) {
-        const int src = k + lane + 64 * e;
-        if (lane + 64 * e < rest) rid[e] = M.c.st_id[src];
-      }
-      __builtin_amdgcn_wave_barrier();
-      for (int e = 0; e < 2; e++) {
-        const int dst = lane + 64 * e;
-        if (dst < rest) M.c.st_id[dst] = rid[e];
-      }
-      staged = rest;
+      head += k;
     }
+    if (head > 0) staged = stage_front(M, lane, head, staged);
     if (done && staged == 0) break;
   }
   nodes_out += visits - visits0;

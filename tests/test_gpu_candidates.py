@@ -55,3 +55,26 @@ def test_candidate_groups_against_oracle(torch_cuda, n):
             a = v.cpu().numpy().astype(np.float64)
             assert np.linalg.norm(a - ref[k]) <= 1e-3 * max(np.linalg.norm(ref[k]), 1e-30), (k, n)
     r.check_errors()
+
+
+@pytest.mark.parametrize("kind,n,sd,eye,fov,tile", [
+    ("cluster", 3, 0.5, (0.0, 0.1, 2.0), 50.0, (8, 8)),          # absent children
+    ("cluster", 20_000, 0.5, (0.05, 0.1, 0.2), 60.0, (8, 8)),     # camera inside ellipsoids
+    ("cluster", 20_000, 0.5, (0.0, 0.1, 2.5), 160.0, (64, 1)),    # packets wider than the cone test
+    ("outdoor", 30_000, 1.0, (0.3, 0.0, 0.4), 60.0, (8, 8)),      # anisotropic, large and far boxes
+    ("outdoor", 30_000, 1.0, (0.3, 0.0, 0.4), 160.0, (16, 4)),
+])
+def test_collection_finds_every_hit(torch_cuda, kind, n, sd, eye, fov, tile):
+    """The window collection against brute force, bit for bit: a Gaussian that
+    a box or support test wrongly drops would change a pixel."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene(kind, n, 77, log_scale_sd=sd)
+    far = 128.0 if kind == "outdoor" else 6.0
+    cam = inputs.look_at_camera(53, 37, eye, target=(0.0, 0.05, 0.0), fov_deg=fov, t_far=far)
+    r, _ = renderer_for(sc)
+    kw = dict(adaptive=True, ess=1, t_eps=1e-4, tile_w=tile[0], tile_h=tile[1])
+    rgb, T = r.forward([cam], RenderOptions(**kw))
+    brute, Tb = r.forward([cam], RenderOptions(brute_force=True, **kw))
+    assert torch.equal(rgb, brute) and torch.equal(T, Tb)
+    r.check_errors()
