@@ -91,6 +91,11 @@ struct rgx_bvh {
       aabb, col, nodes, nodes4, quads, sup, seg, acc, zsum, sg_user, sgrec, sgacc;
 };
 
+// Lanes per ray (choose_split).
+struct Split {
+  int outside = 1, inside = 1;   // views whose camera is outside / inside the means' bounds
+};
+
 // Forward state: what one forward rendered and what its searches found.
 struct rgx_fwd {
   rgx_context *ctx = nullptr;       // compared only: the state may outlive its context
@@ -100,11 +105,13 @@ struct rgx_fwd {
   int64_t n = 0;                    // Gaussians of that build
   std::vector<rgx_camera> cams;
   rgx_render_opts opts;
+  Split split;                      // lanes per ray of that forward: its records are per tile
   int64_t rays = 0, tiles = 0;
   bool recorded = false;            // closest hits and window lists recorded
   bool has_totals = false;          // statistics totals reduced into `totals`
   DevBuf replay;                    // [rays][kReplayK] closest-hit results
   DevBuf wrec;                      // window-list pool (64-bit counter first)
+  uint32_t wrec_cap = 0;            // dwords of it that forward could use
   DevBuf wrec_tile;                 // per tile: (complete, first record)
   DevBuf totals;                    // int64 [RGX_NTOT]
   std::vector<void *> retired;      // outgrown buffers: a captured graph may still use them
@@ -339,6 +346,7 @@ static SceneDev scene_of(const rgx_bvh *b) {
   s.sup = (const float *)b->sup.p;
   s.aabb = (const float *)b->aabb.p;
   s.counters = (const int32_t *)b->counters.p;
+  s.bounds = (const uint32_t *)b->bounds.p;
   s.perm = (const uint32_t *)(b->sorted_sel ? b->vals1.p : b->vals0.p);
   s.aux = (const float *)b->aux.p;
   s.sg = b->n_sg > 0 ? (const float *)b->sgrec.p : nullptr;
@@ -386,6 +394,7 @@ static rgx_status make_opts(rgx_context *ctx, const rgx_bvh *b, const rgx_render
   m.tile_w = tw;
   m.tile_h = th;
   m.tile_w_log2 = ilog2(tw);
+  m.split = 1;
   m.persistent = o->persistent ? 1 : 0;
   if (o->window_segments < 0 || o->window_segments > 64)
     return fail(ctx, RGX_ERR_INVALID_ARG, "window_segments must be 0..64");
@@ -396,6 +405,17 @@ static rgx_status make_opts(rgx_context *ctx, const rgx_bvh *b, const rgx_render
   if (b->n_sg > 0 && m.n_s != 8)
     return fail(ctx, RGX_ERR_UNSUPPORTED, "spherical-Gaussian colour lobes need n_s = 8");
   return RGX_OK;
+}
+
+// Tiles of 64 / split rays: the tile shape loses its longer side's half per
+// factor of two.
+static void set_split(MarchOpts &m, int split) {
+  m.split = split;
+  for (int k = split; k > 1; k >>= 1) {
+    if (m.tile_h >= m.tile_w) m.tile_h >>= 1;
+    else m.tile_w >>= 1;
+  }
+  m.tile_w_log2 = ilog2(m.tile_w);
 }
 
 static rgx_status check_camera(rgx_context *ctx, const rgx_camera &c) {
@@ -441,9 +461,9 @@ static rgx_status tile_order(rgx_context *ctx, int W, int H, int tw, int th, con
 // Split the views into launches of at most kMaxViewsPerLaunch.
 static rgx_status view_tables(rgx_context *ctx, const rgx_camera *cams, int n_views,
                               const MarchOpts &m, std::vector<ViewTable> &tabs,
-                              int64_t ray0 = 0, int64_t tile0 = 0) {
+                              int64_t tile0 = 0) {
   if (!cams || n_views <= 0) return fail(ctx, RGX_ERR_INVALID_ARG, "no views");
-  int64_t ray = ray0, tile_base = tile0;
+  int64_t ray = 0, tile_base = tile0;
   for (int v0 = 0; v0 < n_views; v0 += kMaxViewsPerLaunch) {
     ViewTable t;
     memset(&t, 0, sizeof t);
@@ -456,7 +476,7 @@ static rgx_status view_tables(rgx_context *ctx, const rgx_camera *cams, int n_vi
       V.width = c.width;
       V.height = c.height;
       if (m.ray_order == 0) {
-        V.tiles_x = (c.width * c.height + 63) / 64;
+        V.tiles_x = (c.width * c.height + 64 / m.split - 1) / (64 / m.split);
         V.tiles_y = 1;
         V.tile_order = nullptr;
       } else {
@@ -499,6 +519,20 @@ static rgx_status view_tables(rgx_context *ctx, const rgx_camera *cams, int n_vi
   return RGX_OK;
 }
 
+// The table of one view of a call (its rays and tiles keep their numbers).
+static ViewTable one_view(const std::vector<ViewTable> &tabs, int v) {
+  const ViewTable &t = tabs[v / kMaxViewsPerLaunch];
+  const int i = v % kMaxViewsPerLaunch;
+  ViewTable o;
+  memset(&o, 0, sizeof o);
+  o.n_views = 1;
+  o.v[0] = t.v[i];
+  o.v[0].tile_begin = 0;
+  o.n_tiles = t.v[i].tiles_x * t.v[i].tiles_y;
+  o.tile0 = t.tile0 + t.v[i].tile_begin;
+  return o;
+}
+
 // Grows a state's record buffer to at least `need` bytes; an outgrown buffer
 // is kept until rgx_fwd_destroy (a captured graph may hold its address).
 static bool grow_record(rgx_fwd *f, DevBuf &b, size_t need) {
@@ -519,6 +553,68 @@ static int64_t total_rays(const rgx_camera *cams, int32_t n_views) {
   int64_t r = 0;
   for (int v = 0; v < n_views; v++) r += (int64_t)cams[v].width * cams[v].height;
   return r;
+}
+
+// How a call's views are marched: one launch per part, all of the same rays'
+// tables.  Part 0 covers the views its `views` names, with its own tile shape.
+struct MarchPlan {
+  struct Part {
+    MarchOpts m;
+    std::vector<ViewTable> tabs;
+  };
+  std::vector<Part> parts;
+  int64_t tiles = 0;       // record slots: the parts' tiles one after another
+};
+
+// How many lanes share a ray.  A 64-ray tile is one wave's serial march, and a
+// few tiles at a scene's silhouette take many times the mean, so a launch too
+// small to keep the chip busy beside them lasts as long as they do; tiles of
+// 16 or 32 rays shorten every march, at 2.5 or 1.5 times the total work.  The
+// lines lie where both sides were measured (ms forward, 1 / 2 / 4 lanes a
+// ray): 100k Gaussians, cluster, 512 tiles 5.4 / 3.4 / 1.7, 1536 tiles 3.9 /
+// 2.6 / 2.0, 2048 tiles 3.0 / 2.4 / 2.6, 4096 tiles 2.8 / 2.7 / 3.9, 6144 tiles
+// 2.8 / 3.5 / 5.3; 1M, 4096 tiles 12.8 / 9.9 / 9.2, 8192 tiles 11.8 / 10.7 /
+// 12.3, 12288 tiles 11.7 / 11.9 / 14.9; 5k large ones, 512 tiles 2.3 / 1.4 /
+// 1.3, 1024 tiles 1.9 / 1.8 / 2.3, 1536 tiles 1.8 / 2.2 / 3.0.  Where the
+// camera stands inside a dense scene every ray starts in the medium and the
+// tiles are alike (outdoor layout, forward + backward, 256 tiles: 300k 1.5 /
+// 1.3 / 1.3, 3M 5.1 / 4.4 / 5.2; 512 tiles: 2.5k 4.9 / 3.8 / 4.2, 100k 1.65 /
+// 1.59 / 1.79, 300k 1.45 / 1.52 / 1.69, 3M 5.2 / 5.9 / 6.8; 1024 tiles: 2.5k 4.6
+// / 4.8 / 6.2, 300k 1.7 / 1.9 / 2.6), so those views have lines of their own.
+static Split choose_split(const rgx_context *ctx, const rgx_bvh *b, const MarchOpts &m, int64_t tiles) {
+  Split s;
+  if (m.n_s < 4 || m.brute_force) return s;
+  const int64_t cu = ctx->n_cu;
+  if (tiles <= 2 * cu || (tiles <= 16 * cu && b->n >= 50 * tiles)) s.outside = 4;
+  else if (tiles <= 4 * cu || (tiles <= 32 * cu && b->n >= 24 * tiles)) s.outside = 2;
+  if (tiles <= cu) s.inside = 4;
+  else if (tiles <= 2 * cu && b->n <= 400 * tiles) s.inside = 2;
+  return s;
+}
+
+static int64_t count_tiles64(const rgx_camera *cams, int32_t n_views) {
+  int64_t t = 0;
+  for (int v = 0; v < n_views; v++) t += ((int64_t)cams[v].width * cams[v].height + 63) / 64;
+  return t;
+}
+
+// Fills the parts.  Which views lie inside the scene is known on the device
+// only: where the two differ both kinds of launch go out, and a wave leaves
+// the tiles of the other's views alone.
+static rgx_status make_plan(rgx_context *ctx, const MarchOpts &m, Split split, const rgx_camera *cams,
+                            int32_t n_views, MarchPlan &p) {
+  const bool both = split.outside != split.inside;
+  for (int k = 0; k < (both ? 2 : 1); k++) {
+    MarchPlan::Part part;
+    part.m = m;
+    part.m.views = !both ? VIEWS_ALL : k == 0 ? VIEWS_OUTSIDE : VIEWS_INSIDE;
+    set_split(part.m, k == 0 ? split.outside : split.inside);
+    const rgx_status s = view_tables(ctx, cams, n_views, part.m, part.tabs, p.tiles);
+    if (s != RGX_OK) return s;
+    for (const ViewTable &t : part.tabs) p.tiles += t.n_tiles;
+    p.parts.push_back(std::move(part));
+  }
+  return RGX_OK;
 }
 
 // waves_per_cu: how many of the kernel's one-wave workgroups fit on a CU
@@ -545,16 +641,21 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
   rgx_status s = make_opts(ctx, bvh, opts, m);
   if (s != RGX_OK) return s;
   HIP_TRY(ctx, enter(ctx->device));
-  std::vector<ViewTable> tabs;
-  if ((s = view_tables(ctx, cams, n_views, m, tabs)) != RGX_OK) return s;
+  if (!cams || n_views <= 0) return fail(ctx, RGX_ERR_INVALID_ARG, "no views");
+  for (int v = 0; v < n_views; v++)
+    if ((s = check_camera(ctx, cams[v])) != RGX_OK) return s;
+  // (the statistics are those of 64-ray waves)
+  const int64_t tiles64 = count_tiles64(cams, n_views);
+  const Split split = stats ? Split() : choose_split(ctx, bvh, m, tiles64);
+  MarchPlan plan;
+  if ((s = make_plan(ctx, m, split, cams, n_views, plan)) != RGX_OK) return s;
   const SceneDev sd = scene_of(bvh);
   FwdOut out;
   memset(&out, 0, sizeof out);
   out.rgb = out_rgb;
   out.T = out_T;
   out.stats = stats;
-  int64_t tiles = 0;
-  for (const ViewTable &t : tabs) tiles += t.n_tiles;
+  const int64_t tiles = plan.tiles;
   const int64_t rays = total_rays(cams, n_views);
   rgx_fwd *f = nullptr;
   if (state) {
@@ -566,6 +667,7 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
     f->n = bvh->n;
     f->cams.assign(cams, cams + n_views);
     f->opts = *opts;
+    f->split = split;
     f->rays = rays;
     f->tiles = tiles;
     f->recorded = false;
@@ -581,8 +683,10 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
     const bool samples = !opts->no_sample_record;
     const size_t per_tile = (size_t)kWrecDwordsPerTile +
                             (samples ? (size_t)kSrecDwordsPerTile * (m.n_s > 8 ? 2 : 1) : 0);
+    // (tiles of fewer rays share less: twice as much for both kinds of them)
     size_t pool = std::min<size_t>(
-        std::max<size_t>(2 + (size_t)tiles * per_tile, (size_t)1 << 24), 0xfffffff0u);
+        std::max<size_t>(2 + (size_t)tiles64 * per_tile * (split.outside > 1 || split.inside > 1 ? 2 : 1), (size_t)1 << 24),
+        0xfffffff0u);
     // a caller's cap (the two counter dwords always fit)
     if (ctx->record_limit > 0)
       pool = std::max<size_t>(std::min<size_t>(pool, (size_t)ctx->record_limit / sizeof(uint32_t)), 2);
@@ -593,7 +697,7 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
       m.replay = (float *)f->replay.p;
       m.wrec = (uint32_t *)f->wrec.p;
       m.wrec_tile = (uint32_t *)f->wrec_tile.p;
-      m.wrec_cap = (uint32_t)pool;
+      m.wrec_cap = f->wrec_cap = (uint32_t)pool;
       m.sample_rec = samples ? 1 : 0;
       // the pool's 64-bit allocation counter (dwords 0-1) starts past itself
       // (fill kernels, not memset nodes, so the call can be captured)
@@ -611,10 +715,24 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
     }
     *state = f;
   }
-  for (const ViewTable &t : tabs) {
-    if (t.n_tiles == 0) continue;
-    HIP_TRY(ctx, timed(ctx, RGX_KERN_FORWARD, stream,
-                       [&] { return launch_forward(sd, t, m, out, shape_for(ctx, m, t.n_tiles, fwd_waves_per_cu(m)), stream); }));
+  for (size_t k = 0; k < plan.parts[0].tabs.size(); k++) {
+    if (plan.parts[0].tabs[k].n_tiles == 0) continue;
+    HIP_TRY(ctx, timed(ctx, RGX_KERN_FORWARD, stream, [&] {
+      hipError_t e = hipSuccess;
+      for (MarchPlan::Part &part : plan.parts) {
+        MarchOpts &pm = part.m;
+        pm.replay_mode = m.replay_mode;
+        pm.replay = m.replay;
+        pm.wrec = m.wrec;
+        pm.wrec_tile = m.wrec_tile;
+        pm.wrec_cap = m.wrec_cap;
+        pm.sample_rec = m.sample_rec;
+        const ViewTable &t = part.tabs[k];
+        if (e == hipSuccess)
+          e = launch_forward(sd, t, pm, out, shape_for(ctx, pm, t.n_tiles, fwd_waves_per_cu(pm)), stream);
+      }
+      return e;
+    }));
   }
   if (f && stats) {
     HIP_TRY(ctx, launch_stat_totals(stats, rays, sd, f->recorded ? (const uint32_t *)f->wrec_tile.p : nullptr,
@@ -642,8 +760,7 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
   rgx_status s = make_opts(ctx, bvh, &f->opts, m);
   if (s != RGX_OK) return s;
   HIP_TRY(ctx, enter(ctx->device));
-  std::vector<ViewTable> tabs;
-  if ((s = view_tables(ctx, cams, n_views, m, tabs)) != RGX_OK) return s;
+  MarchPlan plan;
   const SceneDev sd = scene_of(bvh);
   // the accumulators are zero: cleared by the build and by every finalisation
   ctx->replayed = 0;
@@ -652,10 +769,11 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
     m.replay = (float *)f->replay.p;
     m.wrec = (uint32_t *)f->wrec.p;
     m.wrec_tile = (uint32_t *)f->wrec_tile.p;
-    m.wrec_cap = (uint32_t)std::min<size_t>(f->wrec.bytes / sizeof(uint32_t), 0xfffffff0u);
+    m.wrec_cap = f->wrec_cap;
     m.sample_rec = f->opts.no_sample_record ? 0 : 1;
     ctx->replayed = 1;
   }
+  if ((s = make_plan(ctx, m, f->split, cams, n_views, plan)) != RGX_OK) return s;
   BwdIn in;
   in.rgb = out_rgb;
   in.T = out_T;
@@ -664,10 +782,17 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
   in.acc = (float *)bvh->acc.p;
   in.sgacc = bvh->n_sg > 0 ? (float *)bvh->sgacc.p : nullptr;
   if (!grads->densify) {
-    for (const ViewTable &t : tabs) {
-      if (t.n_tiles == 0) continue;
-      HIP_TRY(ctx, timed(ctx, RGX_KERN_BACKWARD, stream,
-                         [&] { return launch_backward(sd, t, m, in, shape_for(ctx, m, t.n_tiles, bwd_waves_per_cu(m)), stream); }));
+    for (size_t k = 0; k < plan.parts[0].tabs.size(); k++) {
+      if (plan.parts[0].tabs[k].n_tiles == 0) continue;
+      HIP_TRY(ctx, timed(ctx, RGX_KERN_BACKWARD, stream, [&] {
+        hipError_t e = hipSuccess;
+        for (const MarchPlan::Part &part : plan.parts) {
+          const ViewTable &t = part.tabs[k];
+          if (e == hipSuccess)
+            e = launch_backward(sd, t, part.m, in, shape_for(ctx, part.m, t.n_tiles, bwd_waves_per_cu()), stream);
+        }
+        return e;
+      }));
     }
   } else {
     // one view at a time: each view's mean gradient is the change of the
@@ -676,17 +801,16 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
     rgx_bvh *mb = const_cast<rgx_bvh *>(bvh);
     HIP_TRY(ctx, ensure(mb->zsum, (size_t)bvh->n * 3 * sizeof(float)));
     HIP_TRY(ctx, launch_fill(mb->zsum.p, bvh->n * 3, 0u, stream));
-    int64_t ray0 = 0, tile0 = 0;
     for (int v = 0; v < n_views; v++) {
-      std::vector<ViewTable> one;
-      if ((s = view_tables(ctx, cams + v, 1, m, one, ray0, tile0)) != RGX_OK) return s;
-      ray0 += (int64_t)cams[v].width * cams[v].height;
-      tile0 += one[0].n_tiles;
-      for (const ViewTable &t : one) {
-        if (t.n_tiles == 0) continue;
-        HIP_TRY(ctx, timed(ctx, RGX_KERN_BACKWARD, stream,
-                           [&] { return launch_backward(sd, t, m, in, shape_for(ctx, m, t.n_tiles, bwd_waves_per_cu(m)), stream); }));
-      }
+      HIP_TRY(ctx, timed(ctx, RGX_KERN_BACKWARD, stream, [&] {
+        hipError_t e = hipSuccess;
+        for (const MarchPlan::Part &part : plan.parts) {
+          const ViewTable t = one_view(part.tabs, v);
+          if (e == hipSuccess)
+            e = launch_backward(sd, t, part.m, in, shape_for(ctx, part.m, t.n_tiles, bwd_waves_per_cu()), stream);
+        }
+        return e;
+      }));
       const float *c2w = cams[v].cam_to_world;
       HIP_TRY(ctx, launch_densify(sd, (float *)bvh->acc.p, (float *)mb->zsum.p, c2w[3], c2w[7],
                                   c2w[11], cams[v].fx, grads->densify, grads->densify_views, stream));

@@ -7,16 +7,6 @@
 
 namespace rgx {
 
-// ---------------------------------------------------------------------------
-// Order-preserving float <-> uint32 map for atomic min/max of floats.
-__device__ __forceinline__ uint32_t f2ord(float f) {
-  uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float ord2f(uint32_t u) {
-  return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
-}
-
 __global__ void k_build_init(uint32_t *bounds, int32_t *counters) {
   int t = threadIdx.x;
   if (t < 3) bounds[t] = 0xffffffffu;        // min
@@ -510,7 +500,7 @@ __global__ __launch_bounds__(256) void k_bvh4(int64_t n_max, const int32_t *__re
         // half-extents rounded outward: [c - h, c + h] holds [lo, hi]
         const float lo = f[6 * k + a], hi = f[6 * k + 3 + a];
         c[a] = 0.5f * lo + 0.5f * hi;
-        h[a] = fmaxf(hi - c[a], c[a] - lo) * 1.000001f;
+        h[a] = fmaf(fabsf(c[a]), 4e-7f, fmaxf(hi - c[a], c[a] - lo) * 1.000002f);
       }
     qd[2 * k] = make_float4(c[0], c[1], c[2], h[0]);
     qd[2 * k + 1] = make_float4(h[1], h[2], __int_as_float(k < m ? lk[k] : kNoChild),

@@ -10,9 +10,9 @@ constexpr int kBlock = 256;               // 4 waves, each owning its own 64-ray
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxViewsPerLaunch = 24;    // view table travels as a kernel argument
 constexpr int kGeomFloats = 16;           // packed geometry record (64 B)
-// Per-Gaussian gradient accumulator (256 B): slots 0..2 first moment of dq
-// over the local offsets z, 3..8 second moment (xx xy xz yy yz zz), 9 sum of
-// w dL/dw, 16.. SH coefficients [channel][16].
+// Per-Gaussian gradient accumulator (256 B): slots 0..2 sum of dq z (z the
+// local offset), 3..11 of dq z x^T (x the world offset), 12..14 of dq z_i^2, 15
+// of w dL/dw, 16.. SH coefficients [channel][16].
 constexpr int kAccFloats = 64;
 constexpr int kColFloats = 48;            // colour record: 3 channels x 16 SH coefficients, zero past the degree,
                                           // [channel][k][q] for coefficient 4q + k
@@ -76,6 +76,8 @@ struct MarchOpts {
   int32_t brute_force;
   int32_t ray_order;
   int32_t tile_w, tile_h, tile_w_log2;
+  int32_t split;          // lanes per ray (1, 2, 4): a tile holds 64 / split rays
+  int32_t views;          // VIEWS_*: which of the table's views this launch marches
   int32_t persistent;
   int32_t window_segments;
   float bg[3];
@@ -89,7 +91,10 @@ struct MarchOpts {
   uint32_t *wrec_tile;    // per tile of the call: (complete, first chunk offset)
   uint32_t wrec_cap;      // pool size in dwords
   int32_t sample_rec;     // the record also holds each segment step's per-sample sums
+  int32_t rest;           // backward: this launch takes the tiles a replaying one left
 };
+// all views, or those whose camera lies inside / outside the bounds of the means
+enum { VIEWS_ALL = 0, VIEWS_INSIDE, VIEWS_OUTSIDE };
 constexpr int kReplayK = 4;
 // Window-list record: every collection of a tile appends one chunk to a
 // shared pool (offsets in dwords): a header (count returned, paused, z0, z1,
@@ -157,6 +162,15 @@ __device__ __forceinline__ void sh_basis(int k, float x, float y, float z, float
   Y[13] = -0.45704579946446572f * x * (4.0f * zz - xx - yy);
   Y[14] = 1.4453057213202769f * z * (xx - yy);
   Y[15] = -0.59004358992664352f * x * (xx - 3.0f * yy);
+}
+
+// Order-preserving float <-> uint32 map for atomic min/max of floats.
+__device__ __forceinline__ uint32_t f2ord(float f) {
+  uint32_t u = __float_as_uint(f);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float ord2f(uint32_t u) {
+  return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
 
 constexpr float kLog2e = 1.4426950408889634f;

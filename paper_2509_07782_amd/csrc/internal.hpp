@@ -51,6 +51,7 @@ struct SceneDev {
   const float *sup;           // [n,16] leaf-test records
   const float *aabb;          // [n,6]
   const int32_t *counters;    // [0] = active count
+  const uint32_t *bounds;     // [6] bounds of the active means, ordered floats (lo xyz, hi xyz)
   const uint32_t *perm;       // Z index -> user index
   const float *aux;           // [n,8] s.xyz, unit quaternion wxyz, |q| (Z order)
   const float *sg;            // [n, kSgFloats] packed lobes (Z order), nullptr without lobes
@@ -83,7 +84,7 @@ struct LaunchShape {
 // Resident one-wave workgroups per CU of the march kernels (their launch
 // bounds and LDS use), used to size persistent grids.
 inline int fwd_waves_per_cu(const MarchOpts &m) { return m.n_s <= 8 ? 12 : 8; }
-inline int bwd_waves_per_cu(const MarchOpts &) { return 8; }
+inline int bwd_waves_per_cu() { return 8; }
 hipError_t launch_forward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
                           const FwdOut &out, const LaunchShape &ls, hipStream_t st);
 hipError_t launch_backward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,

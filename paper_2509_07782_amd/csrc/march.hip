@@ -21,6 +21,8 @@
 // chunks are sorted, brute force counts up), whatever packet, window, tile
 // shape or ray order is used; the images of all these variants are
 // therefore bit-identical.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -68,6 +70,18 @@ __device__ __forceinline__ float box_entry(float lx, float ly, float lz, float h
   bmax = fmaf(fabsf(bmax), 1e-6f, bmax);
   const float e = fmaxf(bmin, lo);
   return e <= fminf(bmax, hi) ? e : kInf;
+}
+
+// The same for a box of the collection's node layout (centre, half-extents),
+// widened by 1e-6 of the distances involved.
+__device__ __forceinline__ float ray_box_entry(const vf4 &q0, const vf4 &q1, const Ray &r, float lo,
+                                               float hi) {
+  const float tx = (q0.x - r.ox) * r.ix, ty = (q0.y - r.oy) * r.iy, tz = (q0.z - r.oz) * r.iz;
+  const float ex = fmaf(fabsf(tx), 1e-6f, q0.w * fabsf(r.ix)),
+              ey = fmaf(fabsf(ty), 1e-6f, q1.x * fabsf(r.iy)),
+              ez = fmaf(fabsf(tz), 1e-6f, q1.y * fabsf(r.iz));
+  const float e = fmaxf(fmaxf(tx - ex, ty - ey), fmaxf(tz - ez, lo));
+  return e <= fminf(fminf(tx + ex, ty + ey), fminf(tz + ez, hi)) ? e : kInf;
 }
 
 // Geometry of one Gaussian (wave-uniform, from the scalar cache).
@@ -240,8 +254,9 @@ struct Pixel {
   bool valid;
 };
 
+// `lane` is the ray's number in its tile of `rays` rays.
 __device__ __forceinline__ Pixel tile_pixel(const ViewTable &vt, const MarchOpts &op, int w,
-                                            int lane) {
+                                            int lane, int rays) {
   int v = 0;
   while (v + 1 < vt.n_views && vt.v[v + 1].tile_begin <= w) v++;
   const View &V = vt.v[v];
@@ -249,7 +264,7 @@ __device__ __forceinline__ Pixel tile_pixel(const ViewTable &vt, const MarchOpts
   Pixel p;
   p.view = v;
   if (op.ray_order == 0) {
-    const int r = t * 64 + lane;
+    const int r = t * rays + lane;
     p.valid = r < V.width * V.height;
     p.px = r % V.width;
     p.py = r / V.width;
@@ -262,6 +277,24 @@ __device__ __forceinline__ Pixel tile_pixel(const ViewTable &vt, const MarchOpts
   }
   p.ray = V.ray_begin + p.py * V.width + p.px;
   return p;
+}
+
+// Whether this launch marches the view (the same answer in every wave, and in
+// the backward of the same structure build).
+__device__ __forceinline__ bool marches_view(const SceneDev &s, const MarchOpts &op, const View &V) {
+  if (op.views == VIEWS_ALL) return true;
+  bool inside = true;
+#pragma unroll
+  for (int k = 0; k < 3; k++)
+    inside = inside && V.c2w[4 * k + 3] >= ord2f(s.bounds[k]) && V.c2w[4 * k + 3] <= ord2f(s.bounds[3 + k]);
+  return uniform_int(inside ? 1 : 0) == (op.views == VIEWS_INSIDE ? 1 : 0);
+}
+
+__device__ __forceinline__ bool marches_any(const SceneDev &s, const MarchOpts &op, const ViewTable &vt) {
+  if (op.views == VIEWS_ALL) return true;
+  for (int v = 0; v < vt.n_views; v++)
+    if (marches_view(s, op, vt.v[v])) return true;
+  return false;
 }
 
 // A wave-uniform value held in a vector register: the camera centre is read
@@ -344,6 +377,8 @@ struct SampleExp {
   __device__ __forceinline__ float at(int k) const {
     return k == 0 ? e0 : fmaf((float)(k * k), e2, fmaf((float)k, e1, e0));
   }
+  // a per-lane sample index (the same value at the same index)
+  __device__ __forceinline__ float at(float k) const { return fmaf(k * k, e2, fmaf(k, e1, e0)); }
 };
 
 __device__ __forceinline__ SampleExp sample_exp(float k2, float l2sig, const Chord &c,
@@ -425,6 +460,29 @@ __device__ __forceinline__ void transpose_rows(float (&x)[4]) {
 #pragma unroll
   for (int g = 0; g < 4; g++) x[g] = __uint_as_float(u[g]);
 }
+// A tile of 64 / S rays: the lanes ray, ray + 64 / S, ... hold one ray, each
+// some of its samples.  out[i] is the value of the ray's lane i, in all of
+// its lanes.
+template <int S>
+__device__ __forceinline__ void ray_lanes(float x, float (&out)[S]) {
+  if constexpr (S == 1) {
+    out[0] = x;
+  } else {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                    false);
+    if constexpr (S == 2) {
+      out[0] = __uint_as_float(p[0]);
+      out[1] = __uint_as_float(p[1]);
+    } else {
+      const auto a = __builtin_amdgcn_permlane16_swap(p[0], p[0], false, false);
+      const auto b = __builtin_amdgcn_permlane16_swap(p[1], p[1], false, false);
+      out[0] = __uint_as_float(a[0]);
+      out[1] = __uint_as_float(a[1]);
+      out[2] = __uint_as_float(b[0]);
+      out[3] = __uint_as_float(b[1]);
+    }
+  }
+}
 __device__ __forceinline__ float uniform_lane(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
@@ -489,41 +547,11 @@ __device__ __forceinline__ float wave_sum_slots16(const float *g, int lane) {
   return u;
 }
 
-// Sum over the wave of the kGeomSlots = 10 geometry and density slots of one
-// Gaussian, in 25 instructions: the same stages as above on five pairs of
-// slots (i, i + 5), the fifth pair carried along without a partner where
-// there is none.  slot_of_lane gives the slot a lane's result belongs to, or
-// -1 where another lane holds the same total.
-constexpr int kGeomSlots = 10;
-__device__ __forceinline__ float wave_sum_slots10(const float *g, int lane) {
-  float y[5], z[2];
-#pragma unroll
-  for (int i = 0; i < 5; i++) y[i] = swap32_sum(g[i], g[i + 5]);   // bit 5: i or i + 5
-  z[0] = swap16_sum(y[0], y[1]);                                   // bit 4: 0 or 1
-  z[1] = swap16_sum(y[2], y[3]);                                   // bit 4: 2 or 3
-  float x[2];
-  x[1] = swap16_sum(y[4], y[4]);
-  dpp_stage_bit<1, 0x140, 8>(z, lane);                             // bit 3: {0, 1} or {2, 3}
-  x[0] = z[0];
-  x[1] += dpp<0x140>(x[1]);
-  dpp_stage_bit<1, 0x141, 4>(x, lane);                             // bit 2: {0 .. 3} or 4
-  float u = x[0];
-  u += dpp<0xb1>(u);
-  u += dpp<0x4e>(u);
-  return u;
-}
-__device__ __forceinline__ int slot_of_lane(int lane) {
-  const int hi = (lane >> 5) * 5;
-  if (lane & 3) return -1;
-  if (lane & 4) return (lane & 24) == 0 ? 4 + hi : -1;
-  return ((lane >> 4) & 1) + 2 * ((lane >> 3) & 1) + hi;
-}
-
 // SH-coefficient gradients of a batch of up to 16 Gaussians, a small dense
 // product on the matrix cores.  For Gaussian b of the batch and channel c,
 // dL/df_{m,c} = sum over the tile's rays r of Y_m(d_r) G_c(r) S_b(r), S_b(r)
 // the ray's sum over samples of w_k T_k phi_k (zero where the ray misses b).
-// With A_c[m][r] = Y_m(d_r) G_c(r) fixed for the tile (held in registers)
+// With A_c[m][r] = Y_m(d_r) G_c(r) (Y held in registers, G in LDS)
 // and B[r][b] = S_b(r) staged in LDS, each channel is 16 chained 16x16x4 FP32
 // MFMAs over the 64 rays, computed transposed: D_c = B^T A_c^T, so that the
 // result holds Gaussians in rows and coefficients in columns.  Operand
@@ -533,35 +561,66 @@ __device__ __forceinline__ int slot_of_lane(int lane) {
 // floats (one 64-byte line) to each of 4 Gaussians' rows.
 constexpr int kSbStride = 66;   // floats per staged row: transposed reads hit distinct banks
 
+constexpr int kRowStride = 17;   // floats per lane of the transposition: distinct banks both ways
+
+// Sums of 16 slots over the 16 lanes of each row: lane L returns slot L & 15
+// summed over row L >> 4.  Through LDS, 16 writes and 16 reads that cost the
+// vector units 15 additions: in registers (two half-wave swaps, two in-row
+// stages, a quad sum) a Gaussian's 16 slots took 12 row swaps of 8 cycles and
+// 23 other instructions, 76 ns of a full SIMD against about 20.
+__device__ __forceinline__ float sum_rows16(float *buf, const float *v, int lane) {
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int e = 0; e < 16; e++) buf[lane * kRowStride + e] = v[e];
+  __builtin_amdgcn_wave_barrier();
+  const float *p = buf + (lane & 48) * kRowStride + (lane & 15);
+  float x[16];
+#pragma unroll
+  for (int i = 0; i < 16; i++) x[i] = p[i * kRowStride];
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int h = 8; h >= 1; h >>= 1)
+#pragma unroll
+    for (int i = 0; i < h; i++) x[i] += x[i + h];
+  return x[0];
+}
+
 struct ShBatch {
-  float a[3][16];   // A_c for rays 4q + (lane >> 4), row m = lane & 15
+  float y[16];      // Y_m of rays 4q + (lane >> 4), row m = lane & 15
   int n = 0;        // uniform: staged Gaussians
   int id = 0;       // lane b < 16: the Gaussian staged in row b
 };
 
-// A_c of a new tile; `tmp` is 192 floats of LDS free at that point.
-__device__ __forceinline__ void sh_batch_start(ShBatch &B, float *sb, float *tmp, const float *Y,
-                                               float g0, float g1, float g2, int lane) {
+// LDS of the batch: the staged S rows and the tile's G, channel by channel.
+// A_c is formed from Y and G at every product (one multiplication beside
+// three matrix instructions): held whole it took 32 more registers, and the
+// kernel spilled.
+template <int S>
+struct ShMem {
+  float s[16 * kSbStride];
+  float g[3][64];
+  float r[S == 1 ? 64 * kRowStride : 1];   // a Gaussian's slots, lane by lane (sum_rows16)
+};
+
+// Y and G of a new tile.
+template <int S>
+__device__ __forceinline__ void sh_batch_start(ShBatch &B, ShMem<S> &sm, const float *Y, float g0,
+                                               float g1, float g2, int lane) {
 #pragma unroll
-  for (int m = 0; m < 16; m++) sb[m * kSbStride + lane] = Y[m];
-  tmp[lane] = g0;
-  tmp[64 + lane] = g1;
-  tmp[128 + lane] = g2;
+  for (int m = 0; m < 16; m++) sm.s[m * kSbStride + lane] = Y[m];
+  sm.g[0][lane] = g0;
+  sm.g[1][lane] = g1;
+  sm.g[2][lane] = g2;
   __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int q = 0; q < 16; q++) {
-    const int ray = 4 * q + (lane >> 4);
-    const float y = sb[(lane & 15) * kSbStride + ray];
-    B.a[0][q] = y * tmp[ray];
-    B.a[1][q] = y * tmp[64 + ray];
-    B.a[2][q] = y * tmp[128 + ray];
-  }
+  for (int q = 0; q < 16; q++) B.y[q] = sm.s[(lane & 15) * kSbStride + 4 * q + (lane >> 4)];
   __builtin_amdgcn_wave_barrier();
   B.n = 0;
 }
 
 // Multiplies out the staged batch and adds it to the accumulators.
-__device__ __forceinline__ void sh_batch_flush(ShBatch &B, const float *sb, float *acc, int sh_k,
+template <int S>
+__device__ __forceinline__ void sh_batch_flush(ShBatch &B, const ShMem<S> &sm, float *acc, int sh_k,
                                                int lane) {
   if (B.n == 0) return;
   __builtin_amdgcn_wave_barrier();
@@ -569,10 +628,11 @@ __device__ __forceinline__ void sh_batch_flush(ShBatch &B, const float *sb, floa
 #pragma unroll
   for (int q = 0; q < 16; q++) {
     // S_b(r) for Gaussian b = lane & 15 and ray r = 4q + (lane >> 4)
-    const float sv = sb[(lane & 15) * kSbStride + 4 * q + (lane >> 4)];
-    d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sv, B.a[0][q], d0, 0, 0, 0);
-    d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sv, B.a[1][q], d1, 0, 0, 0);
-    d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(sv, B.a[2][q], d2, 0, 0, 0);
+    const int ray = 4 * q + (lane >> 4);
+    const float sv = sm.s[(lane & 15) * kSbStride + ray];
+    d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sv, B.y[q] * sm.g[0][ray], d0, 0, 0, 0);
+    d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sv, B.y[q] * sm.g[1][ray], d1, 0, 0, 0);
+    d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(sv, B.y[q] * sm.g[2][ray], d2, 0, 0, 0);
   }
   // lane: coefficient m = lane & 15 of Gaussians 4 (lane >> 4) + i
   const int m = lane & 15;
@@ -627,11 +687,13 @@ __device__ __forceinline__ float wave_max(float v) {
 // so far and prunes.  A minimum does not depend on the visiting order.
 // Query qn of ray `ray`: recorded into (or, for q < kReplayK, replayed from)
 // op.replay when op.replay_mode asks for it.
+template <int S>
 __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts &op, int n_active,
                                              const Ray &r, float tn, float tf, float dS,
                                              SegState &ss, int32_t *err, int32_t *st_closest,
                                              int &qn, int64_t ray) {
   if (ballot(ss.pending) == 0) return;
+  const int st_lane = __lane_id();
   const bool replayed = op.replay_mode == 2 && ss.pending && qn < kReplayK;
   const float rbest = replayed ? op.replay[ray * kReplayK + qn] : kInf;
   const bool search = ss.pending && !replayed;
@@ -657,7 +719,7 @@ __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts 
   } else if (n_active > 0) {
     const int n_inner = n_active > 1 ? n_active - 1 : 1;
     WaveStack st;
-    st.lane = __lane_id();
+    st.lane = st_lane;
     st.sp = 0;
     int node = 0, visits = 0;
     for (;;) {
@@ -669,27 +731,56 @@ __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts 
         node = v;
       }
       if (++visits > n_inner) { if (err) *err = 2; break; }
-      cfloat4p np = as_const4(s.nodes4) + (kNode4Floats / 4) * node;
-      float f[kNode4Floats];
-#pragma unroll
-      for (int q = 0; q < kNode4Floats / 4; q++) {
-        const vf4 x = np[q];
-        f[4 * q] = x.x; f[4 * q + 1] = x.y; f[4 * q + 2] = x.z; f[4 * q + 3] = x.w;
-      }
-      // the boxes and links go out as one batch of loads: the box tests and
-      // the link checks below would otherwise each wait for a load of their
-      // own
-#pragma unroll
-      for (int q = 0; q < 24 + 4; q++) pin_uniform(f[q]);
       int link[4];
       float e[4];
+      if constexpr (S > 1) {
+        // the lanes of a ray take the four children between them
+        const int child = st_lane / (64 / S);
+        const vf4 *np = reinterpret_cast<const vf4 *>(s.quads) + (kQuadFloats / 4) * (size_t)node;
+        vf4 q0[4 / S], q1[4 / S];
 #pragma unroll
-      for (int k = 0; k < 4; k++) {
-        link[k] = __float_as_int(f[24 + k]);
-        e[k] = link[k] != kNoChild
-                   ? wave_min_nonneg_dpp(box_entry(f[6 * k], f[6 * k + 1], f[6 * k + 2], f[6 * k + 3],
-                                                   f[6 * k + 4], f[6 * k + 5], r, lo, hi))
-                   : kInf;
+        for (int t = 0; t < 4 / S; t++) {
+          q0[t] = np[2 * (child + S * t)];
+          q1[t] = np[2 * (child + S * t) + 1];
+        }
+#pragma unroll
+        for (int t = 0; t < 4 / S; t++) {
+          float x = ray_box_entry(q0[t], q1[t], r, lo, hi);
+          x = fminf(x, dpp_or<0xb1>(x, kInf));
+          x = fminf(x, dpp_or<0x4e>(x, kInf));
+          x = fminf(x, dpp_or<0x141>(x, kInf));
+          x = fminf(x, dpp_or<0x140>(x, kInf));
+#pragma unroll
+          for (int c = 0; c < S; c++) {
+            constexpr int kR = 64 / S;
+            const int ch = c + S * t;
+            link[ch] = __builtin_amdgcn_readlane(__float_as_int(q1[t].z), kR * c);
+            e[ch] = uniform_lane(x, kR * c);
+            if constexpr (S == 2) e[ch] = fminf(e[ch], uniform_lane(x, kR * c + 16));
+            if (link[ch] == kNoChild) e[ch] = kInf;
+          }
+        }
+      } else {
+        cfloat4p np = as_const4(s.nodes4) + (kNode4Floats / 4) * node;
+        float f[kNode4Floats];
+#pragma unroll
+        for (int q = 0; q < kNode4Floats / 4; q++) {
+          const vf4 x = np[q];
+          f[4 * q] = x.x; f[4 * q + 1] = x.y; f[4 * q + 2] = x.z; f[4 * q + 3] = x.w;
+        }
+        // the boxes and links go out as one batch of loads: the box tests and
+        // the link checks below would otherwise each wait for a load of their
+        // own
+#pragma unroll
+        for (int q = 0; q < 24 + 4; q++) pin_uniform(f[q]);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          link[k] = __float_as_int(f[24 + k]);
+          e[k] = link[k] != kNoChild
+                     ? wave_min_nonneg_dpp(box_entry(f[6 * k], f[6 * k + 1], f[6 * k + 2], f[6 * k + 3],
+                                                     f[6 * k + 4], f[6 * k + 5], r, lo, hi))
+                     : kInf;
+        }
       }
       // links out of range (a malformed tree) end the walk; checked after
       // the box tests, which do not need them, in one branch-free test
@@ -723,7 +814,7 @@ __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts 
   __builtin_amdgcn_s_setprio(0);
   if (ss.pending) {
     if (replayed) best = rbest;
-    else if (op.replay_mode == 1 && qn < kReplayK) op.replay[ray * kReplayK + qn] = best;
+    else if (op.replay_mode == 1 && qn < kReplayK && st_lane < 64 / S) op.replay[ray * kReplayK + qn] = best;
     qn++;
     if (st_closest) (*st_closest)++;
     if (!(best < kInf)) ss.alive = false;
@@ -763,16 +854,19 @@ constexpr int kRingCap = 256;    // frontier (stack) entries
 constexpr int kStageCap = 320;   // staged leaves; a round adds at most 4 per node
 constexpr int kListCap = 512;    // window list entries (multiple of 64, at most 512)
 
-struct WaveMem {
+struct ListMem {
+  uint16_t order[kListCap];        // slots of the current chunk's entries, in Z-index order
+  int32_t l_id[kListCap];
+  float l_tin[kListCap], l_tout[kListCap];
+  int32_t cand[64];                // a block's candidates, packed to the front
+};
+
+struct WaveMem : ListMem {
   float rlo[64], rhi[64];          // the rays' windows
   struct {                         // traversal state, kept while a collection is paused
     int2 ring[kRingCap];           // (4-wide node, its first leaf)
     int32_t st_id[kStageCap];
   } c;
-  uint16_t order[kListCap];        // slots of the current chunk's entries, in Z-index order
-  int32_t l_id[kListCap];
-  float l_tin[kListCap], l_tout[kListCap];
-  int32_t cand[64];                // a block's candidates, packed to the front
 };
 
 // Statistics only: the tile's rays and their AABB-only leaf counts.
@@ -1394,18 +1488,19 @@ enum CandMode { CAND_ALL = 0, CAND_MARK = 1, CAND_FILTER = 2 };
 // every candidate.  In the forward, where half the candidates are hit by no
 // lane, the colour therefore stays with the vector units; the backward's
 // candidates are the hit ones.  1M Gaussians, 4 x 1024x768: forward 41.5 ->
-// 39.7 ms (43.2 with the colour here too), backward 32.4 -> 27.5 ms (with the
-// ten-slot reduction).
+// 39.7 ms (43.2 with the colour here too), backward 32.4 -> 30.3 ms (with sum_rows16).
+template <int S>
 struct TileOps {
-  float d[4];      // direction operand of rays 16g .. 16g + 15: k = 0, 1, 2 -> z, y, x; 3 -> 0
-  float y[4][4];   // basis operand, [ray group][4 coefficients 4q .. 4q + 3] (COL)
+  static constexpr int kGroups = 4 / S;   // ray groups of 16
+  float d[kGroups];      // direction operand of rays 16g .. 16g + 15: k = 0, 1, 2 -> z, y, x; 3 -> 0
+  float y[kGroups][4];   // basis operand, [ray group][4 coefficients 4q .. 4q + 3] (COL)
 };
 
-template <bool COL>
-__device__ __forceinline__ void tile_ops(TileOps &o, const Ray &r, const float *Y, int lane) {
+template <bool COL, int S>
+__device__ __forceinline__ void tile_ops(TileOps<S> &o, const Ray &r, const float *Y, int lane) {
   const int k = lane >> 4;
 #pragma unroll
-  for (int g = 0; g < 4; g++) {
+  for (int g = 0; g < TileOps<S>::kGroups; g++) {
     const int src = 16 * g + (lane & 15);
     const float x = __shfl(r.dx, src, 64), y = __shfl(r.dy, src, 64), z = __shfl(r.dz, src, 64);
     o.d[g] = k == 0 ? z : k == 1 ? y : k == 2 ? x : 0.0f;
@@ -1426,6 +1521,7 @@ struct Cand {
   float k2, l2sig;          // uniform
   Chord ch;
   float ox, oy, oz;         // uniform
+  float ex, ey, ez;         // uniform: camera centre minus mean
   float dx, dy, dz;
   float cr, cg, cb;
 };
@@ -1469,18 +1565,19 @@ __device__ __forceinline__ void cand_pin(const CandOps &G) {
 // chords are one branch-free run of vector work, so that the four dependent
 // chains (with a reciprocal and a square root each) overlap; the colour's
 // matrix instructions are spread through it.
-// after(c, j) runs for the hit candidates of a group once the next operands
-// have arrived: memory operations that count against the same counter
+// after(ids, first, hits) runs once per group when the next operands have
+// arrived (candidate c is lane first + c of `ids`, bit c of `hits` says whether
+// some lane hit it): memory operations that count against the same counter
 // (atomics) belong there, or the wait for the loads would wait for them too.
 // CAND_MARK: a visited entry's mark is set to whether some lane hit it.  With
 // use_marks, a CAND_MARK pass trusts the marks already set (from a record of
 // the same pass) and visits only the marked entries, and a CAND_FILTER pass
 // visits only the marked entries (list source only; the brute-force source
 // visits everything).
-template <int MODE, bool COL, class Visit, class Fn, class After>
-__device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, WaveMem &M,
+template <int MODE, bool COL, int S, class Visit, class Fn, class After>
+__device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, ListMem &M,
                                                    int count, int lane, float a_min, float b_max,
-                                                   int n_active, const Ray &r, const TileOps &ops,
+                                                   int n_active, const Ray &r, const TileOps<S> &ops,
                                                    bool want, float lo, float hi, Visit &&visit,
                                                    Fn &&fn, After &&after, bool use_marks = false) {
   const bool list = kind == SRC_LIST;
@@ -1522,10 +1619,11 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
     for (int first = 0; first < n; first += 4) {
       // d' of the group's candidates, transposed to the lanes; the next
       // group's loads and the readlanes run beside the matrix instructions
-      f4v acc[4];
+      constexpr int kG = TileOps<S>::kGroups;
+      f4v acc[kG];
       const float mm = lane < 48 ? cur.m : 0.0f;
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
+      for (int g = 0; g < kG; g++) {
         const f4v z = {0.0f, 0.0f, 0.0f, 0.0f};
         acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(mm, ops.d[g], z, 0, 0, 0);
       }
@@ -1538,6 +1636,11 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
         g[c].oz = uniform_lane(mine.oz, first + c);
         g[c].k2 = uniform_lane(mine.k2, first + c);
         g[c].l2sig = uniform_lane(mine.l2sig, first + c);
+        if constexpr (MODE == CAND_FILTER) {   // (pass B)
+          g[c].ex = uniform_lane(r.ox - mine.mx, first + c);
+          g[c].ey = uniform_lane(r.oy - mine.my, first + c);
+          g[c].ez = uniform_lane(r.oz - mine.mz, first + c);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       next_id = __shfl(cid, first + 8 + ((lane >> 2) & 3), 64);
@@ -1546,7 +1649,7 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
 #pragma unroll
         for (int i = 0; i < 3; i++) {
 #pragma unroll
-          for (int q = 0; q < 4; q++) d[i][q] = acc[q][i];
+          for (int q = 0; q < 4; q++) d[i][q] = acc[q % kG][i];
           transpose_rows(d[i]);
         }
 #pragma unroll
@@ -1557,14 +1660,16 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
       // the order, which the compiler's scheduler would undo
       if constexpr (COL) {
 #pragma unroll
-        for (int p = 0; p < 4; p++) acc[p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int p = 0; p < kG; p++) acc[p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
       }
-      auto mm_step = [&](int i) {
+      auto mm_step = [&](int i) {   // (16 steps; every S-th carries an instruction)
         if constexpr (COL) {
-          __builtin_amdgcn_sched_barrier(0);
-          acc[i & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.f[i >> 2], ops.y[i & 3][i >> 2],
-                                                           acc[i & 3], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
+          if (i % S == 0) {
+            const int q = i / 4, p = (i / S) % kG;
+            __builtin_amdgcn_sched_barrier(0);
+            acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.f[q], ops.y[p][q], acc[p], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       };
       float B[4], rA[4], x[4], w[4];
@@ -1611,7 +1716,7 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
 #pragma unroll
         for (int i = 0; i < 3; i++) {
 #pragma unroll
-          for (int q = 0; q < 4; q++) col[i][q] = acc[q][i];
+          for (int q = 0; q < 4; q++) col[i][q] = acc[q % kG][i];
           transpose_rows(col[i]);
         }
       }
@@ -1626,9 +1731,8 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
         }
       }
       cand_pin<COL>(nxt);
-#pragma unroll
-      for (int c = 0; c < 4; c++)
-        if (any[c] != 0) after(c, __builtin_amdgcn_readlane(cid, first + c));
+      after(cid, first, (any[0] != 0 ? 1u : 0u) | (any[1] != 0 ? 2u : 0u) | (any[2] != 0 ? 4u : 0u) |
+                            (any[3] != 0 ? 8u : 0u));
       cur = nxt;
     }
     if (MODE == CAND_MARK && list && !use_marks && keep)
@@ -1698,7 +1802,7 @@ __device__ __forceinline__ bool rec_fits(const MarchOpts &op, uint32_t off, uint
   return off < op.wrec_cap && (uint64_t)off + size <= op.wrec_cap;
 }
 
-__device__ __forceinline__ void rec_put(WinRec &R, const MarchOpts &op, const WaveMem &M,
+__device__ __forceinline__ void rec_put(WinRec &R, const MarchOpts &op, const ListMem &M,
                                         const Trav &t, int cnt, int lane) {
   if (!R.ok) return;
   const int n = cnt > 0 ? cnt : 0;
@@ -1719,7 +1823,7 @@ __device__ __forceinline__ void rec_put(WinRec &R, const MarchOpts &op, const Wa
 
 // The marks of the current list's `count` entries after a pass: [next, count,
 // then one 64-bit ballot per 64 entries].
-__device__ __forceinline__ void rec_put_marks(WinRec &R, const MarchOpts &op, const WaveMem &M,
+__device__ __forceinline__ void rec_put_marks(WinRec &R, const MarchOpts &op, const ListMem &M,
                                               int count, int lane) {
   if (!R.ok) return;
   const int words = (count + 63) >> 6;
@@ -1826,7 +1930,7 @@ __device__ __forceinline__ bool rec_get_samples(WinRec &R, const MarchOpts &op, 
 
 // Loads the chunk at pool offset `off` into the list (identity order, no
 // marks); returns its collection's result and the next record in *next.
-__device__ __forceinline__ int rec_load(const MarchOpts &op, WaveMem &M, uint32_t off, int lane,
+__device__ __forceinline__ int rec_load(const MarchOpts &op, ListMem &M, uint32_t off, int lane,
                                         uint32_t *next) {
   // a record always fits the pool and the list; anything else is reported
   if (!rec_fits(op, off, kWrecHeader)) { *next = kWrecNone; return -1; }
@@ -1851,7 +1955,7 @@ __device__ __forceinline__ int rec_load(const MarchOpts &op, WaveMem &M, uint32_
 
 // Sets the list's marks from the marks record at `off` (which must cover
 // `count` entries); false on a broken record.
-__device__ __forceinline__ bool rec_load_marks(const MarchOpts &op, WaveMem &M, uint32_t off,
+__device__ __forceinline__ bool rec_load_marks(const MarchOpts &op, ListMem &M, uint32_t off,
                                                int count, int lane, uint32_t *next) {
   const int words = (count + 63) >> 6;
   if (!rec_fits(op, off, 2 + 2 * (uint64_t)words)) { *next = kWrecNone; return false; }
@@ -1885,7 +1989,7 @@ __device__ __forceinline__ bool rec_load_marks(const MarchOpts &op, WaveMem &M, 
 
 // Backward pass over the current list: in a replayed tile, the forward's
 // marks of this pass (true: visit only those), else false (mark as it goes).
-__device__ __forceinline__ bool rec_next_marks(WinRec &R, const MarchOpts &op, WaveMem &M,
+__device__ __forceinline__ bool rec_next_marks(WinRec &R, const MarchOpts &op, ListMem &M,
                                                int count, int kind, int lane, int32_t *err) {
   if (!(op.replay_mode == 2 && R.ok) || kind != SRC_LIST) return false;
   uint32_t next;
@@ -1903,15 +2007,16 @@ __device__ __forceinline__ bool rec_next_marks(WinRec &R, const MarchOpts &op, W
 // One collection: the tree walk (recorded in a recording forward) or, in a
 // replaying backward of a complete tile, the recorded chunk and state.
 // *start receives the chunk's record offset.
-// REPLAY false (the forward kernel) compiles the replay branch out: a
-// forward never reads a record, and the branch's registers would count
-// against the whole kernel.
-template <bool REPLAY>
-__device__ __forceinline__ int collect(const SceneDev &s, const MarchOpts &op, WaveMem &M,
+// A forward (WIN_SEARCH) never reads a record and a replaying backward
+// (WIN_REPLAY) never walks the tree: the other branch is compiled out, as its
+// registers would count against the whole kernel.
+enum WinMode { WIN_SEARCH = 0, WIN_BOTH, WIN_REPLAY };
+template <int MODE, class Mem>
+__device__ __forceinline__ int collect(const SceneDev &s, const MarchOpts &op, Mem &M,
                                        const Ray &r, int lane, Trav &t, int n_active, StatMem *stats,
                                        int32_t *err, int32_t &nodes, int32_t &leaves,
                                        int64_t *cyc_excl, WinRec &R, uint32_t *start) {
-  if (REPLAY && op.replay_mode == 2 && R.ok) {
+  if (MODE == WIN_REPLAY || (MODE == WIN_BOTH && op.replay_mode == 2 && R.ok)) {
     if (R.cur == kWrecNone || !rec_fits(op, R.cur, kWrecHeader)) {   // a broken record
       if (err) *err = 5;
       t.count = 0;
@@ -1931,14 +2036,17 @@ __device__ __forceinline__ int collect(const SceneDev &s, const MarchOpts &op, W
     R.cur = next;
     return cnt;
   }
-  // the walk is a chain of dependent loads and short bursts of work: while
-  // it runs, the wave's instructions issue ahead of other waves' long
-  // arithmetic runs on the same SIMD (wave priority, not a queue priority)
-  __builtin_amdgcn_s_setprio(3);
-  const int cnt = trav_run(s, M, r, lane, t, n_active, stats, err, nodes, leaves, cyc_excl);
-  __builtin_amdgcn_s_setprio(0);
-  if (op.replay_mode == 1) rec_put(R, op, M, t, cnt, lane);
-  *start = R.cur;
+  int cnt = -1;
+  if constexpr (MODE != WIN_REPLAY) {
+    // the walk is a chain of dependent loads and short bursts of work: while
+    // it runs, the wave's instructions issue ahead of other waves' long
+    // arithmetic runs on the same SIMD (wave priority, not a queue priority)
+    __builtin_amdgcn_s_setprio(3);
+    cnt = trav_run(s, M, r, lane, t, n_active, stats, err, nodes, leaves, cyc_excl);
+    __builtin_amdgcn_s_setprio(0);
+    if (op.replay_mode == 1) rec_put(R, op, M, t, cnt, lane);
+    *start = R.cur;
+  }
   return cnt;
 }
 
@@ -1959,14 +2067,14 @@ struct Window {
 // no live lane can, collects a new window for all live lanes.  A window that
 // could not be collected whole serves the current segment only, chunk by
 // chunk.
-template <bool REPLAY>
-__device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts &op, WaveMem &M,
+template <int MODE, class Mem>
+__device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts &op, Mem &M,
                                               const Ray &r, int lane, int n_active, bool alive,
                                               float a, float b, Window &w, StatMem *stats,
                                               int32_t *err, int32_t &nodes, int32_t &leaves,
                                               int32_t &windows, bool &fits, WinRec &R,
                                               int64_t *cyc_excl = nullptr) {
-  if (op.brute_force) {
+  if (MODE != WIN_REPLAY && op.brute_force) {
     w.kind = SRC_BRUTE;
     w.chunked = false;
     fits = alive;
@@ -1979,12 +2087,14 @@ __device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts
   }
   const uint64_t rays = ballot(alive);
   const float hi = alive ? fmaxf(a + w.len, b) : -kInf;
-  M.rlo[lane] = alive ? a : kInf;
-  M.rhi[lane] = hi;
-  windows++;
-  trav_start(M, lane, w.t, rays, 0, n_active);
+  if constexpr (MODE != WIN_REPLAY) {
+    M.rlo[lane] = alive ? a : kInf;
+    M.rhi[lane] = hi;
+    windows++;
+    trav_start(M, lane, w.t, rays, 0, n_active);
+  }
   w.zend = n_active;
-  const int cnt = collect<REPLAY>(s, op, M, r, lane, w.t, n_active, stats, err, nodes, leaves,
+  const int cnt = collect<MODE>(s, op, M, r, lane, w.t, n_active, stats, err, nodes, leaves,
                                   cyc_excl, R, &w.rec_first);
   w.rec_last = w.rec_first;
   w.kind = SRC_LIST;
@@ -2001,7 +2111,7 @@ __device__ __forceinline__ void ensure_window(const SceneDev &s, const MarchOpts
     // needs no longer window (3M Gaussians, camera inside the dense part, an
     // initial window of four segments: 17.8k -> 11.6k leaf tests a tile,
     // forward 28.3 -> 23.7 ms)
-    M.rhi[lane] = alive ? b : -kInf;
+    if constexpr (MODE != WIN_REPLAY) M.rhi[lane] = alive ? b : -kInf;
   }
   fits = alive;
 }
@@ -2026,25 +2136,28 @@ __device__ __forceinline__ void first_chunk(const SceneDev &s, WaveMem &M, const
 // paused collection, or after a cut at z1 collects again from z1 for the
 // lanes in `lanes` over their segments [a, b].  False when the segment's
 // candidates are exhausted.
-template <bool REPLAY>
-__device__ __forceinline__ bool next_chunk(const SceneDev &s, const MarchOpts &op, WaveMem &M,
+template <int MODE, class Mem>
+__device__ __forceinline__ bool next_chunk(const SceneDev &s, const MarchOpts &op, Mem &M,
                                            const Ray &r, int lane, int n_active, bool lanes,
                                            float a, float b, Window &w, StatMem *stats, int32_t *err,
                                            int32_t &nodes, int32_t &leaves, int32_t &windows,
                                            WinRec &R, int64_t *cyc_excl = nullptr) {
   if (!w.chunked) return false;
   if (w.t.paused) {
-    if (!(REPLAY && op.replay_mode == 2 && R.ok)) trav_advance(M, lane, w.t);
+    if constexpr (MODE != WIN_REPLAY)
+      if (!(MODE == WIN_BOTH && op.replay_mode == 2 && R.ok)) trav_advance(M, lane, w.t);
   } else {
     if (w.t.z1 >= w.zend) return false;
     const uint64_t rays = ballot(lanes);
     if (rays == 0) return false;
-    M.rlo[lane] = lanes ? a : kInf;
-    M.rhi[lane] = lanes ? b : -kInf;
-    windows++;
-    trav_start(M, lane, w.t, rays, w.t.z1, w.zend);
+    if constexpr (MODE != WIN_REPLAY) {
+      M.rlo[lane] = lanes ? a : kInf;
+      M.rhi[lane] = lanes ? b : -kInf;
+      windows++;
+      trav_start(M, lane, w.t, rays, w.t.z1, w.zend);
+    }
   }
-  const int cnt = collect<REPLAY>(s, op, M, r, lane, w.t, n_active, stats, err, nodes, leaves,
+  const int cnt = collect<MODE>(s, op, M, r, lane, w.t, n_active, stats, err, nodes, leaves,
                                   cyc_excl, R, &w.rec_last);
   if (cnt < 0) {
     w.count = 0;
@@ -2058,17 +2171,20 @@ __device__ __forceinline__ bool next_chunk(const SceneDev &s, const MarchOpts &o
 // ---------------------------------------------------------------------------
 // Forward kernel (and the hit-dump variant).
 
-template <int NS, bool DUMP, bool STATS, bool SG = false>
-__global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, ViewTable vt, MarchOpts op,
+template <int NS, int S, bool DUMP, bool STATS, bool SG = false>
+__global__ __launch_bounds__(kWave, NS / S <= 8 ? 3 : 2) void k_forward(SceneDev s, ViewTable vt, MarchOpts op,
                                                    FwdOut out, LaunchShape ls) {
   __shared__ WaveMem M;
   __shared__ StatMemOf<STATS> SM;
   StatMem *sm = nullptr;
   if constexpr (STATS) sm = &SM;
+  constexpr int kRays = 64 / S, NL = NS / S;   // rays of the tile; samples of a ray per lane
   const int lane = threadIdx.x;
+  const int sub = lane / kRays;                // this lane's samples: sub, sub + S, ...
   const int n_active = uniform_int(s.counters[0]);
   const bool grid = !op.adaptive && op.ess != 2;
   constexpr bool stats = STATS;
+  if (!DUMP && !marches_any(s, op, vt)) return;
   bool first = true;
   for (;;) {
     int w;
@@ -2093,9 +2209,10 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
       px.py = pix / vt.v[0].width;
       px.ray = dump_slot;
     } else {
-      px = tile_pixel(vt, op, w, lane);
+      px = tile_pixel(vt, op, w, lane & (kRays - 1), kRays);
     }
     const View &V = vt.v[px.view];
+    if (!DUMP && !marches_view(s, op, V)) continue;
     const Ray r = make_ray(V, px.px, px.py);
     if constexpr (STATS) {
       sm->rdx[lane] = r.dx; sm->rdy[lane] = r.dy; sm->rdz[lane] = r.dz;
@@ -2105,8 +2222,8 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
     const float tn = V.t_near, tf = V.t_far;
     float Y[16];
     sh_basis(op.sh_k, r.dx, r.dy, r.dz, Y);
-    TileOps ops;
-    tile_ops<false>(ops, r, Y, lane);
+    TileOps<S> ops;
+    tile_ops<(S > 1)>(ops, r, Y, lane);
 
     SegState ss;
     int n_closest = 0;   // closest-hit queries of this lane's ray so far
@@ -2144,7 +2261,7 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
     for (;;) {
       if (stats) cyc_t0 = clock64();
       if (op.ess)
-        closest_pass(s, op, n_active, r, tn, tf, dS, ss, ls.error_flag,
+        closest_pass<S>(s, op, n_active, r, tn, tf, dS, ss, ls.error_flag,
                      stats ? &cnt[ST_CLOSEST] : nullptr, n_closest, px.ray);
       if (stats) cyc_closest += clock64() - cyc_t0;
       if (ss.alive) {
@@ -2167,20 +2284,20 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
       if (!ss.alive) { sp.t0 = 0.0f; sp.dt = 0.0f; }
       bool go;
       if (stats) cyc_t0 = clock64();
-      ensure_window<false>(s, op, M, r, lane, n_active, ss.alive, a, b, win, sm, ls.error_flag,
+      ensure_window<WIN_SEARCH>(s, op, M, r, lane, n_active, ss.alive, a, b, win, sm, ls.error_flag,
                     cnt[ST_NODES], cnt[ST_LEAVES], cnt[ST_WINDOWS], go, rec,
                     stats ? &cyc_boxstat : nullptr);
       if (stats) cyc_collect += clock64() - cyc_t0;
       if (stats && go && win.chunked) cnt[ST_CHUNKED]++;
       const float a_min = wave_min(go ? a : kInf), b_max = wave_max(go ? b : -kInf);
       const float lo = go ? a : kInf, hi = go ? b : -kInf;
-      float sg[NS], W0[NS], W1[NS], W2[NS];
+      float sg[NL], W0[NL], W1[NL], W2[NL];
 #pragma unroll
-      for (int k = 0; k < NS; k++) { sg[k] = 0.0f; W0[k] = W1[k] = W2[k] = 0.0f; }
+      for (int k = 0; k < NL; k++) { sg[k] = 0.0f; W0[k] = W1[k] = W2[k] = 0.0f; }
       int nhit = 0;
 
       do {
-        for_each_candidate<CAND_MARK, false>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
+        for_each_candidate<CAND_MARK, (S > 1)>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
                                              r, ops, go, lo, hi, [&] { if (stats) cnt[ST_CAND]++; },
                                             [&](int, int j, const Cand &g, bool hit) {
         const Chord &c = g.ch;
@@ -2195,42 +2312,58 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
             }
             n_dump++;
           }
-          // the colour record's loads go out before the sample weights,
-          // which do not need them
-          const ColRec rc = colour_load(s.col, j);
           const SampleExp se = sample_exp(g.k2, g.l2sig, c, sp);
-          float wk[NS];
-          uint32_t live = 0;   // (uniform) samples some lane sees inside the Gaussian
+          // samples no lane sees inside the Gaussian are skipped with a
+          // uniform branch (their terms are exact zeros)
+          if constexpr (S == 1) {
+            // the colour record's loads go out before the sample weights,
+            // which do not need them
+            const ColRec rc = colour_load(s.col, j);
+            float wk[NS];
+            uint32_t live = 0;   // (uniform) samples some lane sees inside the Gaussian
 #pragma unroll
-          for (int k = 0; k < NS; k++) {
-            const float x = se.at(k);
-            const bool in = x >= se.e_min;
-            // samples no lane sees inside the Gaussian are skipped with a
-            // uniform branch (their terms are exact zeros)
-            wk[k] = 0.0f;
-            if (ballot(in) != 0) {
-              wk[k] = in ? __builtin_amdgcn_exp2f(x) : 0.0f;
-              live |= 1u << k;
+            for (int k = 0; k < NS; k++) {
+              const float x = se.at(k);
+              const bool in = x >= se.e_min;
+              wk[k] = 0.0f;
+              if (ballot(in) != 0) {
+                wk[k] = in ? __builtin_amdgcn_exp2f(x) : 0.0f;
+                live |= 1u << k;
+              }
+            }
+            float cr, cg, cb;
+            colour_eval(rc, Y, cr, cg, cb);
+            if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
+#pragma unroll
+            for (int k = 0; k < NS; k++) {
+              if (!(live & (1u << k))) continue;
+              sg[k] += wk[k];
+              W0[k] = fmaf(wk[k], cr, W0[k]);
+              W1[k] = fmaf(wk[k], cg, W1[k]);
+              W2[k] = fmaf(wk[k], cb, W2[k]);
+            }
+          } else {
+            float cr = g.cr, cg = g.cg, cb = g.cb;
+            if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
+#pragma unroll
+            for (int k = 0; k < NL; k++) {
+              const float x = se.at((float)(k * S) + (float)sub);
+              const bool in = x >= se.e_min;
+              if (ballot(in) == 0) continue;
+              const float w = in ? __builtin_amdgcn_exp2f(x) : 0.0f;
+              sg[k] += w;
+              W0[k] = fmaf(w, cr, W0[k]);
+              W1[k] = fmaf(w, cg, W1[k]);
+              W2[k] = fmaf(w, cb, W2[k]);
             }
           }
-          float cr, cg, cb;
-          colour_eval(rc, Y, cr, cg, cb);
-          if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
-#pragma unroll
-          for (int k = 0; k < NS; k++) {
-            if (!(live & (1u << k))) continue;
-            sg[k] += wk[k];
-            W0[k] = fmaf(wk[k], cr, W0[k]);
-            W1[k] = fmaf(wk[k], cg, W1[k]);
-            W2[k] = fmaf(wk[k], cb, W2[k]);
-          }
         }
-      }, [](int, int) {});
+      }, [](int, int, uint32_t) {});
         // the entries this pass hit, for a replaying backward
         if (op.replay_mode == 1 && win.kind == SRC_LIST) rec_put_marks(rec, op, M, win.count, lane);
       } while ([&] {
         if (stats) cyc_t0 = clock64();
-        const bool more = next_chunk<false>(s, op, M, r, lane, n_active, go, a, b, win, sm,
+        const bool more = next_chunk<WIN_SEARCH>(s, op, M, r, lane, n_active, go, a, b, win, sm,
                                      ls.error_flag, cnt[ST_NODES], cnt[ST_LEAVES], cnt[ST_WINDOWS],
                                      rec, stats ? &cyc_boxstat : nullptr);
         if (stats) cyc_collect += clock64() - cyc_t0;
@@ -2247,28 +2380,40 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
                                             r, ops, empty, b, win.hi, [] {},
                                             [&](int, int, const Cand &g, bool hit) {
           if (hit) best = fminf(best, fmaxf(g.ch.tin, b));
-        }, [](int, int) {});
+        }, [](int, int, uint32_t) {});
       }
       // the step's per-sample sums and restarts, for a replaying backward
       if (op.replay_mode == 1 && op.sample_rec)
-        rec_put_samples<NS>(rec, op, go && nhit > 0, empty, best, sg, W0, W1, W2, lane);
-      if (go) {
-        if (nhit > 0) {
-          if (stats) { cnt[ST_SEGMENTS]++; cnt[ST_P] += nhit; }
+        rec_put_samples<NL>(rec, op, go && nhit > 0, empty, best, sg, W0, W1, W2, lane);
+      const bool shade = go && nhit > 0;
+      if (stats && shade) { cnt[ST_SEGMENTS]++; cnt[ST_P] += nhit; }
+      if (ballot(shade) != 0) {
 #pragma unroll
-          for (int k = 0; k < NS; k++) {
-            if (sp.t(k) < tf) {
+        for (int k0 = 0; k0 < NL; k0++) {
+          // samples k0 S .. k0 S + S - 1 of the ray, in order, in all its lanes
+          float v[S], w0[S], w1[S], w2[S];
+          ray_lanes<S>(sg[k0], v);
+          ray_lanes<S>(W0[k0], w0);
+          ray_lanes<S>(W1[k0], w1);
+          ray_lanes<S>(W2[k0], w2);
+#pragma unroll
+          for (int i = 0; i < S; i++) {
+            if (shade && sp.t(k0 * S + i) < tf) {
               if (stats) cnt[ST_SAMPLES]++;
-              if (sg[k] > 0.0f) {
-                const float x = sg[k] * dt;
-                const float f = T * (one_minus_exp_neg(x) * __builtin_amdgcn_rcpf(sg[k]));
-                C0 = fmaf(f, W0[k], C0);
-                C1 = fmaf(f, W1[k], C1);
-                C2 = fmaf(f, W2[k], C2);
+              if (v[i] > 0.0f) {
+                const float x = v[i] * dt;
+                const float f = T * (one_minus_exp_neg(x) * __builtin_amdgcn_rcpf(v[i]));
+                C0 = fmaf(f, w0[i], C0);
+                C1 = fmaf(f, w1[i], C1);
+                C2 = fmaf(f, w2[i], C2);
                 T *= exp_neg(x);
               }
             }
           }
+        }
+      }
+      if (go) {
+        if (nhit > 0) {
           prev_a = a;
           prev_b = b;
         }
@@ -2285,7 +2430,7 @@ __global__ __launch_bounds__(kWave, NS <= 8 ? 3 : 2) void k_forward(SceneDev s, 
     }
     if (DUMP) {
       if (px.valid) out.dump_count[dump_slot] = n_dump;
-    } else if (px.valid) {
+    } else if (px.valid && sub == 0) {
       out.rgb[3 * (size_t)px.ray + 0] = fmaf(T, op.bg[0], C0);
       out.rgb[3 * (size_t)px.ray + 1] = fmaf(T, op.bg[1], C1);
       out.rgb[3 * (size_t)px.ray + 2] = fmaf(T, op.bg[2], C2);
@@ -2341,23 +2486,32 @@ __device__ __forceinline__ void sg_slots(const float *sg, float *sgacc, int j, f
 // segment's per-sample sums from the forward's record (or sums them again
 // where there is none), recomputes the transmittance before every sample,
 // derives dL/dsigma_k and dL/dW_k, then revisits the Gaussians some lane hit
-// for their parameter adjoints.  The ten
+// for their parameter adjoints.  The 16
 // geometry and density slots are summed over the wave (DPP and half-wave
 // swaps) before one atomic per slot; the SH-coefficient slots, a per-ray
 // constant times one scalar per (ray, Gaussian), are staged 16 Gaussians at a
-// time and multiplied out on the matrix cores.  Two waves per SIMD: the
-// tile's matrix operand and the staging buffer need the registers and LDS.
+// time and multiplied out on the matrix cores.
 
-template <int NS, bool SG = false>
+// REPLAY: only the tiles whose record is complete, per-sample sums included;
+// nothing there walks the tree or sums Gaussians again, and without that code
+// the kernel fits two waves per SIMD without spills.  (Three, at 168 registers,
+// spill into the candidate loop: 37.8 ms against 31.5.)  Otherwise the tiles of every other
+// kind; launched after a REPLAY launch (op.rest) it takes what that left.
+template <int NS, int S, bool SG, bool REPLAY>
 __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt, MarchOpts op,
                                                     BwdIn in, LaunchShape ls) {
-  __shared__ WaveMem M;
-  __shared__ float sb[16 * kSbStride];   // staged S rows of the SH batch
+  constexpr int kMode = REPLAY ? WIN_REPLAY : WIN_BOTH;
+  __shared__ std::conditional_t<REPLAY, ListMem, WaveMem> M;
+  __shared__ ShMem<S> sb;
   ShBatch shb;
+  constexpr int kRays = 64 / S, NL = NS / S;   // rays of the tile; samples of a ray per lane
   const int lane = threadIdx.x;
-  const int slot = slot_of_lane(lane);
+  const int sub = lane / kRays;                // this lane's samples: sub, sub + S, ...
   const int n_active = uniform_int(s.counters[0]);
   const bool grid = !op.adaptive && op.ess != 2;
+  if (!marches_any(s, op, vt)) return;
+  // every record found room: nothing is left for this launch
+  if (!REPLAY && op.rest && *reinterpret_cast<const unsigned long long *>(op.wrec) <= op.wrec_cap) return;
   bool first = true;
   for (;;) {
     int w;
@@ -2371,8 +2525,12 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
     }
     first = false;
 
-    const Pixel px = tile_pixel(vt, op, w, lane);
+    const Pixel px = tile_pixel(vt, op, w, lane & (kRays - 1), kRays);
     const View &V = vt.v[px.view];
+    if (!marches_view(s, op, V)) continue;
+    WinRec rec;
+    rec_start(rec, op, vt, w);
+    if (REPLAY ? !rec.ok : (op.rest && rec.ok)) continue;
     const Ray r = make_ray(V, px.px, px.py);
     const float tn = V.t_near, tf = V.t_far;
     float Y[16];
@@ -2388,15 +2546,12 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
       // C_fin - (prefix through k), kept as the running scalar GP = G . prefix
       GCf = Gc0 * in.rgb[q] + Gc1 * in.rgb[q + 1] + Gc2 * in.rgb[q + 2] + gT * in.T[px.ray];
     }
-    // (the list arrays are free before the tile's first window)
-    sh_batch_start(shb, sb, M.l_tin, Y, Gc0, Gc1, Gc2, lane);
-    TileOps ops;
+    sh_batch_start(shb, sb, Y, Gc0, Gc1, Gc2, lane);
+    TileOps<S> ops;
     tile_ops<true>(ops, r, Y, lane);
     float GP = 0.0f;
     SegState ss;
     int n_closest = 0;   // closest-hit queries of this lane's ray so far
-    WinRec rec;
-    rec_start(rec, op, vt, w);
     ss.alive = px.valid;
     ss.pending = op.ess && px.valid;
     ss.seg_i = 0;
@@ -2419,7 +2574,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
     float T = 1.0f;
 
     for (;;) {
-      if (op.ess) closest_pass(s, op, n_active, r, tn, tf, dS, ss, ls.error_flag, nullptr, n_closest, px.ray);
+      if (op.ess) closest_pass<S>(s, op, n_active, r, tn, tf, dS, ss, ls.error_flag, nullptr, n_closest, px.ray);
       if (ss.alive) {
         const float a0 = grid ? fmaf((float)(ss.seg_i * NS), op.dt, tn) : ss.a;
         if (!(a0 < tf) || !(T > op.t_eps)) ss.alive = false;
@@ -2435,23 +2590,24 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
       }
       if (!ss.alive) { sp.t0 = 0.0f; sp.dt = 0.0f; }
       bool go;
-      ensure_window<true>(s, op, M, r, lane, n_active, ss.alive, a, b, win, nullptr, ls.error_flag,
+      ensure_window<kMode>(s, op, M, r, lane, n_active, ss.alive, a, b, win, nullptr, ls.error_flag,
                     dummy_nodes, dummy_leaves, dummy_windows, go, rec);
       const float a_min = wave_min(go ? a : kInf), b_max = wave_max(go ? b : -kInf);
       const float lo = go ? a : kInf, hi = go ? b : -kInf;
       // only G . W_k enters the adjoints, so pass A sums the Gaussians'
       // weights times G . c_l, one scalar per sample
-      float sg[NS], GW[NS];
+      float sg[NL], GW[NL];
 #pragma unroll
-      for (int k = 0; k < NS; k++) { sg[k] = 0.0f; GW[k] = 0.0f; }
+      for (int k = 0; k < NL; k++) { sg[k] = 0.0f; GW[k] = 0.0f; }
       int nhit = 0;
       // a replayed tile reads the forward's per-sample sums from its record;
       // pass A then only moves through the step's lists and marks
-      const bool from_rec = op.replay_mode == 2 && rec.ok && op.sample_rec;
+      const bool from_rec = REPLAY || (op.replay_mode == 2 && rec.ok && op.sample_rec);
 
       // pass A: the forward's per-sample sums, in the forward's order
       do {
         const bool use_marks = rec_next_marks(rec, op, M, win.count, win.kind, lane, ls.error_flag);
+        if constexpr (!REPLAY)
         if (!from_rec)
         for_each_candidate<CAND_MARK, true>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
                                             r, ops, go, lo, hi, [] {},
@@ -2464,56 +2620,64 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
           const float gc = fmaf(Gc0, cr, fmaf(Gc1, cg, Gc2 * cb));
           const SampleExp se = sample_exp(g.k2, g.l2sig, c, sp);
 #pragma unroll
-          for (int k = 0; k < NS; k++) {
-            const float x = se.at(k);
+          for (int k = 0; k < NL; k++) {
+            const float x = S == 1 ? se.at(k) : se.at((float)(k * S) + (float)sub);
             const float w = x >= se.e_min ? __builtin_amdgcn_exp2f(x) : 0.0f;
             sg[k] += w;
             GW[k] = fmaf(w, gc, GW[k]);
           }
         }
-      }, [](int, int) {}, use_marks);
-      } while (next_chunk<true>(s, op, M, r, lane, n_active, go, a, b, win, nullptr, ls.error_flag,
+      }, [](int, int, uint32_t) {}, use_marks);
+      } while (next_chunk<kMode>(s, op, M, r, lane, n_active, go, a, b, win, nullptr, ls.error_flag,
                             dummy_nodes, dummy_leaves, dummy_windows, rec));
       float best = kInf;
       if (from_rec)
-        nhit = rec_get_samples<NS>(rec, op, go, Gc0, Gc1, Gc2, sg, GW, &best, lane, ls.error_flag) ? 1 : 0;
+        nhit = rec_get_samples<NL>(rec, op, go, Gc0, Gc1, Gc2, sg, GW, &best, lane, ls.error_flag) ? 1 : 0;
 
       // per-sample adjoints: dL/dsigma_k (into sg) and T_k phi_k (into GW);
       // dL/dW_k is G T_k phi_k
       const bool any = go && nhit > 0;
-      if (any) {
+      if (ballot(any) != 0) {
 #pragma unroll
-        for (int k = 0; k < NS; k++) {
-          float dsig = 0.0f, dW = 0.0f;
-          if (sp.t(k) < tf && sg[k] > 0.0f) {
-            const float x = sg[k] * dt;
-            const float E = exp_neg(x);
-            const float rs = __builtin_amdgcn_rcpf(sg[k]);
-            const float alpha = one_minus_exp_neg(x);
-            const float phi = alpha * rs;
-            // d(alpha/sigma)/dsigma = dt^2 f'(x), f(x) = (1 - e^-x)/x
-            const float dphi = x < 1e-2f
-                ? dt * dt * (-0.5f + x * (1.0f / 3.0f - x * (0.125f - x * (1.0f / 30.0f))))
-                : (x * E - alpha) * rs * rs;
-            GP = fmaf(T * phi, GW[k], GP);
-            dsig = T * dphi * GW[k] - dt * (GCf - GP);
-            dW = T * phi;
-            T *= E;
+        for (int k0 = 0; k0 < NL; k0++) {
+          // samples k0 S .. k0 S + S - 1 of the ray, in order, in all its lanes
+          float v[S], gw[S], own_sig = 0.0f, own_w = 0.0f;
+          ray_lanes<S>(sg[k0], v);
+          ray_lanes<S>(GW[k0], gw);
+#pragma unroll
+          for (int i = 0; i < S; i++) {
+            float dsig = 0.0f, dW = 0.0f;
+            if (any && sp.t(k0 * S + i) < tf && v[i] > 0.0f) {
+              const float x = v[i] * dt;
+              const float E = exp_neg(x);
+              const float rs = __builtin_amdgcn_rcpf(v[i]);
+              const float alpha = one_minus_exp_neg(x);
+              const float phi = alpha * rs;
+              // d(alpha/sigma)/dsigma = dt^2 f'(x), f(x) = (1 - e^-x)/x
+              const float dphi = x < 1e-2f
+                  ? dt * dt * (-0.5f + x * (1.0f / 3.0f - x * (0.125f - x * (1.0f / 30.0f))))
+                  : (x * E - alpha) * rs * rs;
+              GP = fmaf(T * phi, gw[i], GP);
+              dsig = T * dphi * gw[i] - dt * (GCf - GP);
+              dW = T * phi;
+              T *= E;
+            }
+            if (S == 1 || sub == i) { own_sig = dsig; own_w = dW; }
           }
-          sg[k] = dsig;
-          GW[k] = dW;
+          sg[k0] = own_sig;
+          GW[k0] = own_w;
         }
       }
 
       // pass B: per-Gaussian adjoints
       if (ballot(any) != 0) {
-        float red[4];   // the group's reduced slots, one candidate each
+        float red[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // the group's reduced slots, one candidate each
         auto pass_b = [&](int ci, int j, const Cand &g, bool hit) {
           const Chord &c = g.ch;
-          float S = 0.0f;
-          float v[kGeomSlots];
+          float sw = 0.0f;   // sum over the lane's samples of w_k T_k phi_k
+          float v[16];
 #pragma unroll
-          for (int e2 = 0; e2 < kGeomSlots; e2++) v[e2] = 0.0f;
+          for (int e2 = 0; e2 < 16; e2++) v[e2] = 0.0f;
           if (hit) {
             float cr = g.cr, cg = g.cg, cb = g.cb;
             if constexpr (SG) sg_colour(s.sg, j, r.dx, r.dy, r.dz, cr, cg, cb);
@@ -2523,48 +2687,80 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
             // moments over u_k = u_0 + k dt from sums over the sample index
             float ds = 0.0f, F1 = 0.0f, F2 = 0.0f;
 #pragma unroll
-            for (int k = 0; k < NS; k++) {
-              const float x = se.at(k);
+            for (int k = 0; k < NL; k++) {
+              const float kf = S == 1 ? (float)k : (float)(k * S) + (float)sub;
+              const float x = S == 1 ? se.at(k) : se.at(kf);
               const float e = __builtin_amdgcn_exp2f(x);
               const float w = x >= se.e_min ? e : 0.0f;
               const float wdw = w * fmaf(GW[k], gc, sg[k]);
               ds += wdw;
-              F1 = fmaf((float)k, wdw, F1);
-              F2 = fmaf((float)(k * k), wdw, F2);
-              S = fmaf(w, GW[k], S);
+              F1 = fmaf(kf, wdw, F1);
+              F2 = fmaf(kf * kf, wdw, F2);
+              sw = fmaf(w, GW[k], sw);
             }
             const float u0 = sp.t0 - c.ts;
             const float E1 = fmaf(u0, ds, sp.dt * F1);                         // sum wdw u
             const float E2 = fmaf(u0, fmaf(u0, ds, 2.0f * sp.dt * F1), sp.dt * sp.dt * F2);
             const float D0 = -0.5f * ds, D1 = -0.5f * E1, D2 = -0.5f * E2;
             // z_k = p + u_k d' with p = o' + t* d' (closest approach, local
-            // frame): the first and second moments of dq over z
+            // frame), and the closest-approach point's world offset P from
+            // the mean
             const float px = fmaf(c.ts, g.dx, g.ox), py = fmaf(c.ts, g.dy, g.oy),
                         pz = fmaf(c.ts, g.dz, g.oz);
-            const float Zx = fmaf(D0, px, D1 * g.dx), Zy = fmaf(D0, py, D1 * g.dy),
-                        Zz = fmaf(D0, pz, D1 * g.dz);
-            const float Ux = fmaf(D1, px, D2 * g.dx), Uy = fmaf(D1, py, D2 * g.dy),
-                        Uz = fmaf(D1, pz, D2 * g.dz);
-            v[0] = Zx; v[1] = Zy; v[2] = Zz;
-            v[3] = fmaf(Zx, px, Ux * g.dx);
-            v[4] = fmaf(Zx, py, Ux * g.dy);
-            v[5] = fmaf(Zx, pz, Ux * g.dz);
-            v[6] = fmaf(Zy, py, Uy * g.dy);
-            v[7] = fmaf(Zy, pz, Uy * g.dz);
-            v[8] = fmaf(Zz, pz, Uz * g.dz);
-            v[9] = ds;
+            const float Ps[3] = {fmaf(c.ts, r.dx, g.ex), fmaf(c.ts, r.dy, g.ey),
+                                 fmaf(c.ts, r.dz, g.ez)};
+            const float Zs[3] = {fmaf(D0, px, D1 * g.dx), fmaf(D0, py, D1 * g.dy),
+                                 fmaf(D0, pz, D1 * g.dz)};
+            const float Us[3] = {fmaf(D1, px, D2 * g.dx), fmaf(D1, py, D2 * g.dy),
+                                 fmaf(D1, pz, D2 * g.dz)};
+            const float dd[3] = {r.dx, r.dy, r.dz};
+            v[0] = Zs[0]; v[1] = Zs[1]; v[2] = Zs[2];
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+#pragma unroll
+              for (int jj = 0; jj < 3; jj++) v[3 + 3 * i + jj] = fmaf(Zs[i], Ps[jj], Us[i] * dd[jj]);
+            v[12] = fmaf(D0, px * px, fmaf(2.0f * D1, px * g.dx, D2 * g.dx * g.dx));
+            v[13] = fmaf(D0, py * py, fmaf(2.0f * D1, py * g.dy, D2 * g.dy * g.dy));
+            v[14] = fmaf(D0, pz * pz, fmaf(2.0f * D1, pz * g.dz, D2 * g.dz * g.dz));
+            v[15] = ds;
           }
           // the geometry and density slots are summed over the wave; the SH
           // slots go through the matrix-core batch
-          sb[shb.n * kSbStride + lane] = S;
+          sb.s[shb.n * kSbStride + lane] = sw;
           shb.id = lane == shb.n ? j : shb.id;
           shb.n++;
-          red[ci] = wave_sum_slots10(v, lane);
-          if constexpr (SG) sg_slots(s.sg, in.sgacc, j, hit ? S : 0.0f, Gc0, Gc1, Gc2, r, lane);
+          // (through LDS the waves of a full chip gain 0.8 ms in 31.2, 1M
+          // Gaussians, 4 x 1024x768; a launch of few waves waits for it: 22.8 ms
+          // against 20.8, 100k, 8 x 160x121 one by one)
+          if constexpr (S == 1) {
+            red[ci] = sum_rows16(sb.r, v, lane);
+          } else {
+            float t[16];
+#pragma unroll
+            for (int e2 = 0; e2 < 16; e2++) t[e2] = v[4 * (e2 & 3) + (e2 >> 2)];
+            red[ci] = wave_sum_slots16(t, lane);
+          }
+          if constexpr (SG) sg_slots(s.sg, in.sgacc, j, hit ? sw : 0.0f, Gc0, Gc1, Gc2, r, lane);
         };
-        // a group's atomics go out together, behind the next group's loads
-        auto put_b = [&](int c, int j) {
-          if (slot >= 0) unsafeAtomicAdd(in.acc + (size_t)kAccFloats * j + slot, red[c]);
+        // a group's atomics go out as one instruction, behind the next group's
+        // loads: 16 consecutive floats (one 64-byte line) of each of the four
+        // Gaussians, slot lane & 15 of candidate lane >> 4
+        auto put_b = [&](int ids, int first, uint32_t hits) {
+          if (hits != 0) {
+            float mine;
+            if constexpr (S == 1) {
+              // red[c]: slot lane & 15 summed over one row of lanes
+              mine = swap16_sum(swap32_sum(red[0], red[2]), swap32_sum(red[1], red[3]));
+            } else {
+              // red[c]: sum lane >> 2, which is slot 4 (i & 3) + (i >> 2)
+              transpose_rows(red);
+              const float even = (lane & 2) ? red[2] : red[0], odd = (lane & 2) ? red[3] : red[1];
+              mine = (lane & 1) ? odd : even;
+            }
+            const uint32_t j = (uint32_t)__shfl(ids, first + (lane >> 4), 64);
+            if ((hits >> (lane >> 4)) & 1u)
+              unsafeAtomicAdd(in.acc + (size_t)kAccFloats * j + (lane & 15), mine);
+          }
           if (shb.n > 12) sh_batch_flush(shb, sb, in.acc, op.sh_k, lane);
         };
         // the list still holds the whole window, or the segment's last Z
@@ -2590,11 +2786,13 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
                 break;
               }
               off = after;
+            } else if constexpr (REPLAY) {
+              break;
             } else {
               if (marked)
                 first_chunk(s, M, r, lane, n_active, any, a, b, zlast, win, nullptr, ls.error_flag,
                             dummy_nodes, dummy_leaves, dummy_windows);
-              else if (!next_chunk<true>(s, op, M, r, lane, n_active, any, a, b, win, nullptr,
+              else if (!next_chunk<kMode>(s, op, M, r, lane, n_active, any, a, b, win, nullptr,
                                          ls.error_flag, dummy_nodes, dummy_leaves, dummy_windows, rec))
                 break;
               marked = false;
@@ -2610,13 +2808,14 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
       // restart after an empty segment: from the list inside the window, else
       // through the closest-hit traversal (same decisions as the forward)
       const bool empty = go && nhit == 0;
+      if constexpr (!REPLAY)
       if (!from_rec && op.ess && win.kind == SRC_LIST && !win.chunked && ballot(empty)) {
         const float bmin = wave_min(empty ? b : kInf);
         for_each_candidate<CAND_ALL, false>(SRC_LIST, s, M, win.count, lane, bmin, kInf, n_active,
                                             r, ops, empty, b, win.hi, [] {},
                                             [&](int, int, const Cand &g, bool hit) {
           if (hit) best = fminf(best, fmaxf(g.ch.tin, b));
-        }, [](int, int) {});
+        }, [](int, int, uint32_t) {});
       }
       if (go) step_after(op, grid, nhit > 0, best, tn, dS, b, ss);
     }
@@ -2661,23 +2860,13 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t n, const int32_t *__re
   for (int jj = 0; jj < 3; jj++)
     put(gm[3 * u + jj], -2.0f * (G[G_M + jj] * Z[0] + G[G_M + 3 + jj] * Z[1] + G[G_M + 6 + jj] * Z[2]));
   // dL/dl_i = -2 sum z_i^2 dq
-  put(gl[3 * u], -2.0f * A[3]);
-  put(gl[3 * u + 1], -2.0f * A[6]);
-  put(gl[3 * u + 2], -2.0f * A[8]);
-  // dL/dR_ji = 2 G'_ij / s_i with G' = sum dq z x^T, x = R S z the world
-  // offset from the mean: G'_ij = sum_l (sum dq z_i z_l) s_l R_jl
+  for (int k = 0; k < 3; k++) put(gl[3 * u + k], -2.0f * A[12 + k]);
+  // dL/dR_ji = 2 G'_ij / s_i
   const float *X = aux + (size_t)kAuxFloats * i;
-  const float w = X[3], x = X[4], y = X[5], z = X[6], qn = X[7];
-  const float R[9] = {1.0f - 2.0f * (y * y + z * z), 2.0f * (x * y - w * z), 2.0f * (x * z + w * y),
-                      2.0f * (x * y + w * z), 1.0f - 2.0f * (x * x + z * z), 2.0f * (y * z - w * x),
-                      2.0f * (x * z - w * y), 2.0f * (y * z + w * x), 1.0f - 2.0f * (x * x + y * y)};
-  const float m2[9] = {A[3], A[4], A[5], A[4], A[6], A[7], A[5], A[7], A[8]};
   float dR[9];
-  for (int ii = 0; ii < 3; ii++) {
-    const float e0 = m2[3 * ii] * X[0], e1 = m2[3 * ii + 1] * X[1], e2 = m2[3 * ii + 2] * X[2];
-    for (int jj = 0; jj < 3; jj++)
-      dR[3 * jj + ii] = 2.0f * fmaf(e0, R[3 * jj], fmaf(e1, R[3 * jj + 1], e2 * R[3 * jj + 2])) / X[ii];
-  }
+  for (int ii = 0; ii < 3; ii++)
+    for (int jj = 0; jj < 3; jj++) dR[3 * jj + ii] = 2.0f * A[3 + 3 * ii + jj] / X[ii];
+  const float w = X[3], x = X[4], y = X[5], z = X[6], qn = X[7];
   float dq[4];
   dq[0] = 2.0f * (-z * dR[1] + y * dR[2] + z * dR[3] - x * dR[5] - y * dR[6] + x * dR[7]);
   dq[1] = 2.0f * (y * dR[1] + z * dR[2] + y * dR[3] - 2.0f * x * dR[4] - w * dR[5] + z * dR[6] +
@@ -2689,7 +2878,7 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t n, const int32_t *__re
   const float pr = dq[0] * w + dq[1] * x + dq[2] * y + dq[3] * z;
   const float qh[4] = {w, x, y, z};
   for (int k = 0; k < 4; k++) put(gq[4 * u + k], (dq[k] - pr * qh[k]) / qn);
-  put(gd[u], A[9] / G[G_SIG]);
+  put(gd[u], A[15] / G[G_SIG]);
   for (int m = 0; m < sh_k; m++)
     for (int ch = 0; ch < 3; ch++) {
       put(gsh[(size_t)3 * sh_k * u + 3 * m + ch], A[16 + 16 * ch + m]);
@@ -2704,21 +2893,61 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
 
 // ---------------------------------------------------------------------------
 
-template <int NS>
-static void fwd_dispatch(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
-                         const FwdOut &out, const LaunchShape &ls, hipStream_t st) {
-  if (out.dump_pix) k_forward<NS, true, false><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
-  else if (out.stats) k_forward<NS, false, true><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
-  else k_forward<NS, false, false><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+// The kernels for tiles of 64 / split rays.  Statistics, hit dumps and the
+// shortest segments run at split 1 only (set by the host).
+template <int NS, bool SG>
+static hipError_t fwd_dispatch(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
+                               const FwdOut &out, const LaunchShape &ls, hipStream_t st) {
+  if (op.split == 1) {
+    // (the hit dump does not depend on colour and takes the plain kernel)
+    if (out.dump_pix) k_forward<NS, 1, true, false><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+    else if (out.stats) k_forward<NS, 1, false, true, SG><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+    else k_forward<NS, 1, false, false, SG><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+    return hipGetLastError();
+  }
+  if constexpr (NS >= 4) {
+    if (out.dump_pix || out.stats) return hipErrorInvalidValue;
+    if (op.split == 2) k_forward<NS, 2, false, false, SG><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+    else if (op.split == 4) k_forward<NS, 4, false, false, SG><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
-// Lobed colour (spherical Gaussians): N_s = 8 only (checked by the host).
-// The hit dump does not depend on colour and takes the plain kernel.
-static void fwd_dispatch_sg(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
-                            const FwdOut &out, const LaunchShape &ls, hipStream_t st) {
-  if (out.dump_pix) k_forward<8, true, false><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
-  else if (out.stats) k_forward<8, false, true, true><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
-  else k_forward<8, false, false, true><<<ls.grid, kWave, 0, st>>>(s, vt, op, out, ls);
+template <int NS, bool SG, bool REPLAY>
+static hipError_t bwd_dispatch(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
+                               const BwdIn &in, const LaunchShape &ls, hipStream_t st) {
+  if (op.split == 1) {
+    k_backward<NS, 1, SG, REPLAY><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls);
+    return hipGetLastError();
+  }
+  if constexpr (NS >= 4) {
+    if (op.split == 2) k_backward<NS, 2, SG, REPLAY><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls);
+    else if (op.split == 4) k_backward<NS, 4, SG, REPLAY><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
+template <bool REPLAY>
+static hipError_t bwd_launch(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
+                             const BwdIn &in, const LaunchShape &ls, hipStream_t st) {
+  if (op.persistent) {
+    hipError_t e = launch_fill(ls.queue, 8, 0u, st);
+    if (e != hipSuccess) return e;
+  }
+  if (s.n_sg > 0)
+    return op.n_s == 8 ? bwd_dispatch<8, true, REPLAY>(s, vt, op, in, ls, st) : hipErrorInvalidValue;
+  switch (op.n_s) {
+    case 1: return bwd_dispatch<1, false, REPLAY>(s, vt, op, in, ls, st);
+    case 2: return bwd_dispatch<2, false, REPLAY>(s, vt, op, in, ls, st);
+    case 4: return bwd_dispatch<4, false, REPLAY>(s, vt, op, in, ls, st);
+    case 8: return bwd_dispatch<8, false, REPLAY>(s, vt, op, in, ls, st);
+    case 16: return bwd_dispatch<16, false, REPLAY>(s, vt, op, in, ls, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_forward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
@@ -2727,42 +2956,27 @@ hipError_t launch_forward(const SceneDev &s, const ViewTable &vt, const MarchOpt
     hipError_t e = launch_fill(ls.queue, 8, 0u, st);
     if (e != hipSuccess) return e;
   }
-  if (s.n_sg > 0) {
-    if (op.n_s != 8) return hipErrorInvalidValue;
-    fwd_dispatch_sg(s, vt, op, out, ls, st);
-    return hipGetLastError();
-  }
+  if (s.n_sg > 0)   // lobed colour (spherical Gaussians): N_s = 8 only (checked by the host)
+    return op.n_s == 8 ? fwd_dispatch<8, true>(s, vt, op, out, ls, st) : hipErrorInvalidValue;
   switch (op.n_s) {
-    case 1: fwd_dispatch<1>(s, vt, op, out, ls, st); break;
-    case 2: fwd_dispatch<2>(s, vt, op, out, ls, st); break;
-    case 4: fwd_dispatch<4>(s, vt, op, out, ls, st); break;
-    case 8: fwd_dispatch<8>(s, vt, op, out, ls, st); break;
-    case 16: fwd_dispatch<16>(s, vt, op, out, ls, st); break;
-    default: return hipErrorInvalidValue;
+    case 1: return fwd_dispatch<1, false>(s, vt, op, out, ls, st);
+    case 2: return fwd_dispatch<2, false>(s, vt, op, out, ls, st);
+    case 4: return fwd_dispatch<4, false>(s, vt, op, out, ls, st);
+    case 8: return fwd_dispatch<8, false>(s, vt, op, out, ls, st);
+    case 16: return fwd_dispatch<16, false>(s, vt, op, out, ls, st);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_backward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
                            const BwdIn &in, const LaunchShape &ls, hipStream_t st) {
-  if (op.persistent) {
-    hipError_t e = launch_fill(ls.queue, 8, 0u, st);
+  MarchOpts o = op;
+  o.rest = op.replay_mode == 2 && op.sample_rec;
+  if (o.rest) {
+    const hipError_t e = bwd_launch<true>(s, vt, o, in, ls, st);
     if (e != hipSuccess) return e;
   }
-  if (s.n_sg > 0) {
-    if (op.n_s != 8) return hipErrorInvalidValue;
-    k_backward<8, true><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls);
-    return hipGetLastError();
-  }
-  switch (op.n_s) {
-    case 1: k_backward<1><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls); break;
-    case 2: k_backward<2><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls); break;
-    case 4: k_backward<4><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls); break;
-    case 8: k_backward<8><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls); break;
-    case 16: k_backward<16><<<ls.grid, kWave, 0, st>>>(s, vt, op, in, ls); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return bwd_launch<false>(s, vt, o, in, ls, st);
 }
 
 hipError_t launch_finalize_grads(const SceneDev &s, int sh_k, float *acc, float *g_means,

@@ -78,3 +78,49 @@ def test_collection_finds_every_hit(torch_cuda, kind, n, sd, eye, fov, tile):
     brute, Tb = r.forward([cam], RenderOptions(brute_force=True, **kw))
     assert torch.equal(rgb, brute) and torch.equal(T, Tb)
     r.check_errors()
+
+
+@pytest.mark.parametrize("kind,n,eye,size,views,n_s,n_sg", [
+    ("cluster", 3_000, (0.0, 0.2, 2.6), (67, 45), 1, 8, 0),       # 4 lanes a ray, ragged
+    ("cluster", 3_000, (0.0, 0.2, 2.6), (67, 45), 1, 4, 0),
+    ("cluster", 3_000, (0.0, 0.2, 2.6), (61, 37), 2, 16, 0),
+    ("cluster", 3_000, (0.0, 0.2, 2.6), (45, 39), 1, 8, 7),
+    ("cluster", 20_000, (0.0, 0.2, 2.6), (163, 129), 1, 8, 0),    # over one tile per CU
+    ("cluster", 20_000, (0.1, 0.2, 0.1), (163, 129), 1, 8, 0),    # camera inside: one lane a ray
+    ("cluster", 20_000, None, (163, 129), 2, 8, 0),               # one view inside, one outside
+    ("cluster", 30_000, (0.0, 0.2, 2.6), (253, 249), 1, 8, 0),    # 2 lanes a ray
+    ("cluster", 30_000, None, (179, 177), 2, 4, 0),
+    ("cluster", 30_000, (0.0, 0.2, 2.6), (253, 249), 1, 16, 0),
+])
+@pytest.mark.parametrize("fixed,persistent", [(False, False), (True, True)])
+def test_lanes_per_ray_give_the_same_rays(torch_cuda, kind, n, eye, size, views, n_s, n_sg, fixed,
+                                          persistent):
+    """A call that asks for statistics marches one lane per ray; without them
+    small calls share a ray between 2 or 4 lanes.  Same images bit for bit;
+    the gradients (replayed, and searched again) differ by the order of the
+    FP32 sums over rays alone."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions, Renderer
+    sc = inputs.make_scene(kind, n, 91, sh_degree=2 if n_sg else None, n_sg=n_sg)
+    keys = ("means", "log_scales", "quats", "density", "sh") + (("sg",) if n_sg else ())
+    p = {k: torch.from_numpy(sc[k]).cuda() for k in keys}
+    r = Renderer(0)
+    r.build(p, sc["sh_degree"])
+    eyes = [eye] * views if eye is not None else [(0.1, 0.2, 0.1), (0.0, 0.2, 2.6)]
+    cams = [inputs.look_at_camera(*size, e, target=(0.0, 0.1 * i, -0.1)) for i, e in enumerate(eyes)]
+    kw = dict(adaptive=not fixed, dt=0.01, n_s=n_s, ess=1, t_eps=1e-4, persistent=persistent)
+    o = RenderOptions(**kw)
+    one, many, own = r.new_state(), r.new_state(), r.new_state()
+    rgb, T, _ = r.forward(cams, o, stats=True, state=one)
+    rgb2, T2 = r.forward(cams, o, state=many)
+    assert torch.equal(rgb, rgb2) and torch.equal(T, T2)
+    g = torch.from_numpy(np.random.default_rng(3).standard_normal(tuple(rgb.shape)).astype(np.float32)).cuda()
+    ref = r.backward(one, rgb, T, g, None, p)
+    r.forward(cams, RenderOptions(no_record=True, **kw), state=own)
+    for st in (many, own):
+        grads = r.backward(st, rgb, T, g, None, p)
+        for k in keys:
+            a, b = grads[k].double(), ref[k].double()
+            assert float((a - b).norm()) <= 2e-5 * float(b.norm()), k
+    r.check_errors()
+    r.close()
