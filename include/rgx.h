@@ -142,7 +142,8 @@ typedef struct {             /* gradient outputs, user order, float32 */
      L_v the loss restricted to view v's pixels; densify_views[i] += 1 when
      that gradient is non-zero.  Both are added to (never cleared), so the
      caller keeps the running sums between densification steps.  When
-     densify is set the views are marched one at a time. */
+     densify is set the structure keeps a workspace of 12 n bytes for each
+     view of a launch, at most 256 MB (or one view's). */
   float *densify;            /* [n] */
   int32_t *densify_views;    /* [n], required with densify */
 } rgx_grads;

@@ -88,7 +88,7 @@ struct rgx_bvh {
   int sorted_sel = 0;
   uint64_t serial = 0;              // the context's build serial of the current contents
   DevBuf geom_user, aabb_user, aux_user, aux, active, bounds, counters, keys0, keys1, vals0, vals1, hist, geom,
-      aabb, col, nodes, nodes4, quads, sup, seg, acc, zsum, sg_user, sgrec, sgacc;
+      aabb, col, nodes, nodes4, quads, sup, seg, acc, zview, sg_user, sgrec, sgacc;
 };
 
 // Lanes per ray (choose_split).
@@ -213,7 +213,7 @@ void rgx_bvh_destroy(rgx_bvh *b) {
   if (!b) return;
   DevBuf *all[] = {&b->geom_user, &b->aabb_user, &b->aux_user, &b->aux, &b->active, &b->bounds, &b->counters, &b->keys0,
                    &b->keys1, &b->vals0, &b->vals1, &b->hist, &b->geom, &b->aabb, &b->col,
-                   &b->nodes, &b->nodes4, &b->quads, &b->sup, &b->seg, &b->acc, &b->zsum,
+                   &b->nodes, &b->nodes4, &b->quads, &b->sup, &b->seg, &b->acc, &b->zview,
                    &b->sg_user, &b->sgrec, &b->sgacc};
   for (DevBuf *d : all) release(*d);
   delete b;
@@ -519,17 +519,19 @@ static rgx_status view_tables(rgx_context *ctx, const rgx_camera *cams, int n_vi
   return RGX_OK;
 }
 
-// The table of one view of a call (its rays and tiles keep their numbers).
-static ViewTable one_view(const std::vector<ViewTable> &tabs, int v) {
-  const ViewTable &t = tabs[v / kMaxViewsPerLaunch];
-  const int i = v % kMaxViewsPerLaunch;
+// The views [first, first + count) of a table (their rays and tiles keep
+// their numbers).
+static ViewTable sub_table(const ViewTable &t, int first, int count) {
   ViewTable o;
   memset(&o, 0, sizeof o);
-  o.n_views = 1;
-  o.v[0] = t.v[i];
-  o.v[0].tile_begin = 0;
-  o.n_tiles = t.v[i].tiles_x * t.v[i].tiles_y;
-  o.tile0 = t.tile0 + t.v[i].tile_begin;
+  o.n_views = count;
+  const int begin = t.v[first].tile_begin;
+  for (int i = 0; i < count; i++) {
+    o.v[i] = t.v[first + i];
+    o.v[i].tile_begin -= begin;
+    o.n_tiles += o.v[i].tiles_x * o.v[i].tiles_y;
+  }
+  o.tile0 = t.tile0 + begin;
   return o;
 }
 
@@ -781,6 +783,7 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
   in.grad_T = grad_T;
   in.acc = (float *)bvh->acc.p;
   in.sgacc = bvh->n_sg > 0 ? (float *)bvh->sgacc.p : nullptr;
+  in.zview = nullptr;
   if (!grads->densify) {
     for (size_t k = 0; k < plan.parts[0].tabs.size(); k++) {
       if (plan.parts[0].tabs[k].n_tiles == 0) continue;
@@ -795,27 +798,31 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
       }));
     }
   } else {
-    // one view at a time: each view's mean gradient is the change of the
-    // accumulated mean slots, turned into the densification statistic
+    // each view's mean sums apart, as many views at a time as 256 MB hold
+    // (never fewer than one)
     if (!grads->densify_views) return fail(ctx, RGX_ERR_INVALID_ARG, "densify needs densify_views");
     rgx_bvh *mb = const_cast<rgx_bvh *>(bvh);
-    HIP_TRY(ctx, ensure(mb->zsum, (size_t)bvh->n * 3 * sizeof(float)));
-    HIP_TRY(ctx, launch_fill(mb->zsum.p, bvh->n * 3, 0u, stream));
-    for (int v = 0; v < n_views; v++) {
-      HIP_TRY(ctx, timed(ctx, RGX_KERN_BACKWARD, stream, [&] {
-        hipError_t e = hipSuccess;
-        for (const MarchPlan::Part &part : plan.parts) {
-          const ViewTable t = one_view(part.tabs, v);
-          if (e == hipSuccess)
-            e = launch_backward(sd, t, part.m, in, shape_for(ctx, part.m, t.n_tiles, bwd_waves_per_cu()), stream);
-        }
-        return e;
-      }));
-      const float *c2w = cams[v].cam_to_world;
-      HIP_TRY(ctx, launch_densify(sd, (float *)bvh->acc.p, (float *)mb->zsum.p, c2w[3], c2w[7],
-                                  c2w[11], cams[v].fx, grads->densify, grads->densify_views, stream));
-    }
-    HIP_TRY(ctx, launch_densify_restore(sd, (float *)bvh->acc.p, (const float *)mb->zsum.p, stream));
+    const int64_t per_view = bvh->n * 3;
+    const int batch = (int)std::min<int64_t>(std::min(n_views, kMaxViewsPerLaunch),
+                                             std::max<int64_t>(1, ((int64_t)1 << 26) / per_view));
+    HIP_TRY(ctx, ensure(mb->zview, (size_t)batch * per_view * sizeof(float)));
+    in.zview = (float *)mb->zview.p;
+    for (size_t k = 0; k < plan.parts[0].tabs.size(); k++)
+      for (int v0 = 0; v0 < plan.parts[0].tabs[k].n_views; v0 += batch) {
+        const int nv = std::min(batch, plan.parts[0].tabs[k].n_views - v0);
+        HIP_TRY(ctx, launch_fill(mb->zview.p, nv * per_view, 0u, stream));
+        HIP_TRY(ctx, timed(ctx, RGX_KERN_BACKWARD, stream, [&] {
+          hipError_t e = hipSuccess;
+          for (const MarchPlan::Part &part : plan.parts) {
+            const ViewTable t = sub_table(part.tabs[k], v0, nv);
+            if (e == hipSuccess)
+              e = launch_backward(sd, t, part.m, in, shape_for(ctx, part.m, t.n_tiles, bwd_waves_per_cu()), stream);
+          }
+          return e;
+        }));
+        HIP_TRY(ctx, launch_densify(sd, (float *)bvh->acc.p, in.zview, sub_table(plan.parts[0].tabs[k], v0, nv),
+                                    grads->densify, grads->densify_views, stream));
+      }
   }
   HIP_TRY(ctx, timed(ctx, RGX_KERN_FINALIZE, stream, [&] {
     return launch_finalize_grads(sd, bvh->sh_k, (float *)bvh->acc.p, grads->means, grads->log_scales,

@@ -73,6 +73,7 @@ struct BwdIn {
   const float *rgb, *T, *grad_rgb, *grad_T;
   float *acc;                // [n, 64] packed-order gradient accumulators
   float *sgacc;              // [n, kSgAccFloats] lobe accumulators (with lobes)
+  float *zview;              // nullable [views of the launch][n][3]: takes the mean slots instead
 };
 
 struct LaunchShape {
@@ -94,9 +95,8 @@ hipError_t launch_finalize_grads(const SceneDev &s, int sh_k, float *acc, float 
                                  float *g_sh, int accumulate, hipStream_t st);
 hipError_t launch_finalize_sg(const SceneDev &s, float *sgacc, float *g_sg, int accumulate,
                               hipStream_t st);
-hipError_t launch_densify(const SceneDev &s, float *acc, float *zsum, float ox, float oy,
-                          float oz, float focal, float *densify, int32_t *views, hipStream_t st);
-hipError_t launch_densify_restore(const SceneDev &s, float *acc, const float *zsum, hipStream_t st);
+hipError_t launch_densify(const SceneDev &s, float *acc, const float *zview, const ViewTable &vt,
+                          float *densify, int32_t *views, hipStream_t st);
 // Totals of a forward's per-ray statistics [rays, kNStat] into int64
 // totals[RGX_NTOT]; wrec_tile (nullable) gives the record's per-tile status.
 hipError_t launch_stat_totals(const int32_t *stats, int64_t rays, const SceneDev &s,

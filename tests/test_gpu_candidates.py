@@ -124,3 +124,34 @@ def test_lanes_per_ray_give_the_same_rays(torch_cuda, kind, n, eye, size, views,
             assert float((a - b).norm()) <= 2e-5 * float(b.norm()), k
     r.check_errors()
     r.close()
+
+
+def test_densify_views_of_two_launches(torch_cuda):
+    """26 views fill one launch (24) and start a second; every view's statistic
+    equals that of a call of its own (FP32 sums over rays in another order)."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    n, views = 700, 26
+    sc = inputs.make_scene("cluster", n, 5)
+    r, p = renderer_for(sc)
+    cams = [inputs.look_at_camera(19, 13, (2.5 * np.sin(v), 0.1 * v - 1.0, 2.5 * np.cos(v)))
+            for v in range(views)]
+    o = RenderOptions(adaptive=True, ess=1, t_eps=1e-4)
+    rng = np.random.default_rng(6)
+
+    def statistic(group, g):
+        st = r.new_state()
+        rgb, T = r.forward(group, o, state=st)
+        stat = torch.zeros(n, device="cuda")
+        seen = torch.zeros(n, device="cuda", dtype=torch.int32)
+        grads = r.backward(st, rgb, T, g, None, p, stat, seen)
+        return stat.double(), seen, grads["means"].double()
+
+    g = torch.from_numpy(rng.standard_normal((views * 247, 3)).astype(np.float32)).cuda()
+    stat, seen, gm = statistic(cams, g)
+    one = [statistic([c], g[247 * v:247 * (v + 1)].contiguous()) for v, c in enumerate(cams)]
+    ref, ref_gm = sum(x[0] for x in one), sum(x[2] for x in one)
+    assert float((stat - ref).norm()) <= 2e-5 * float(ref.norm())
+    assert float((gm - ref_gm).norm()) <= 2e-5 * float(ref_gm.norm())
+    assert torch.equal(seen, sum(x[1] for x in one))
+    r.check_errors()
