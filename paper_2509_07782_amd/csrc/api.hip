@@ -87,8 +87,8 @@ struct rgx_bvh {
   int morton_bits = 21;
   int sorted_sel = 0;
   uint64_t serial = 0;              // the context's build serial of the current contents
-  DevBuf geom_user, aabb_user, aux_user, aux, active, bounds, counters, keys0, keys1, vals0, vals1, hist, geom,
-      aabb, col, nodes, nodes4, quads, sup, seg, acc, zview, sg_user, sgrec, sgacc;
+  DevBuf aux, active, bounds, counters, keys0, keys1, vals0, vals1, hist, geom,
+      aabb, col, nodes, quads, sup, seg, acc, zview, sg_user, sgrec, sgacc;
 };
 
 // Lanes per ray (choose_split).
@@ -211,9 +211,9 @@ void rgx_destroy(rgx_context *ctx) {
 
 void rgx_bvh_destroy(rgx_bvh *b) {
   if (!b) return;
-  DevBuf *all[] = {&b->geom_user, &b->aabb_user, &b->aux_user, &b->aux, &b->active, &b->bounds, &b->counters, &b->keys0,
+  DevBuf *all[] = {&b->aux, &b->active, &b->bounds, &b->counters, &b->keys0,
                    &b->keys1, &b->vals0, &b->vals1, &b->hist, &b->geom, &b->aabb, &b->col,
-                   &b->nodes, &b->nodes4, &b->quads, &b->sup, &b->seg, &b->acc, &b->zview,
+                   &b->nodes, &b->quads, &b->sup, &b->seg, &b->acc, &b->zview,
                    &b->sg_user, &b->sgrec, &b->sgacc};
   for (DevBuf *d : all) release(*d);
   delete b;
@@ -253,9 +253,6 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   hipError_t e = hipSuccess;
 #define ENS(buf, bytes) \
   if (e == hipSuccess) e = ensure(b->buf, (bytes))
-  ENS(geom_user, (size_t)n * kGeomFloats * 4);
-  ENS(aabb_user, (size_t)n * 6 * 4);
-  ENS(aux_user, (size_t)n * kAuxFloats * 4);
   ENS(aux, (size_t)n * kAuxFloats * 4);
   ENS(active, (size_t)n);
   ENS(bounds, 64);
@@ -264,12 +261,11 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   ENS(keys1, (size_t)n * 8);
   ENS(vals0, (size_t)n * 4);
   ENS(vals1, (size_t)n * 4);
-  ENS(hist, (size_t)nb * 256 * 4);
+  ENS(hist, (size_t)(nb + 1) * 256 * 4);
   ENS(geom, (size_t)n * kGeomFloats * 4);
   ENS(aabb, (size_t)n * 6 * 4);
   ENS(col, (size_t)n * col_stride * 4);
   ENS(nodes, nodes_n * 16 * 4);
-  ENS(nodes4, nodes_n * kNode4Floats * 4);
   ENS(quads, nodes_n * kQuadFloats * 4);
   ENS(sup, (size_t)n * kSupFloats * 4);
   int64_t P = 1;
@@ -303,9 +299,8 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   a.n_sg = g->n_sg;
   a.sg_user = (float *)b->sg_user.p;
   a.sgrec = (float *)b->sgrec.p;
-  a.sh_k = sh_k; a.col_stride = col_stride; a.morton_bits = bits; a.sigma_eps = sigma_eps;
-  a.geom_user = (float *)b->geom_user.p; a.aabb_user = (float *)b->aabb_user.p;
-  a.aux_user = (float *)b->aux_user.p; a.aux = (float *)b->aux.p;
+  a.sh_k = sh_k; a.morton_bits = bits; a.sigma_eps = sigma_eps;
+  a.aux = (float *)b->aux.p;
   a.active = (uint8_t *)b->active.p; a.bounds = (uint32_t *)b->bounds.p;
   a.counters = (int32_t *)b->counters.p;
   a.keys[0] = (uint64_t *)b->keys0.p; a.keys[1] = (uint64_t *)b->keys1.p;
@@ -314,14 +309,10 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   a.sorted_sel = &b->sorted_sel;
   a.geom = (float *)b->geom.p; a.aabb = (float *)b->aabb.p; a.col = (float *)b->col.p;
   a.nodes = (float *)b->nodes.p; a.seg = (float *)b->seg.p;
-  a.nodes4 = (float *)b->nodes4.p;
   a.quads = (float *)b->quads.p;
   a.sup = (float *)b->sup.p;
   e = timed(ctx, RGX_KERN_BUILD, stream, [&] {
-    hipError_t r = launch_build(a, stream);
-    if (r == hipSuccess) r = launch_fill(b->acc.p, n * kAccFloats, 0u, stream);
-    if (r == hipSuccess && g->n_sg > 0) r = launch_fill(b->sgacc.p, n * kSgAccFloats, 0u, stream);
-    return r;
+    return launch_build(a, stream);
   });
   if (e != hipSuccess) {
     if (fresh) rgx_bvh_destroy(b);
@@ -341,7 +332,6 @@ static SceneDev scene_of(const rgx_bvh *b) {
   s.geom = (const float *)b->geom.p;
   s.col = (const float *)b->col.p;
   s.nodes = (const float *)b->nodes.p;
-  s.nodes4 = (const float *)b->nodes4.p;
   s.quads = (const float *)b->quads.p;
   s.sup = (const float *)b->sup.p;
   s.aabb = (const float *)b->aabb.p;
@@ -764,7 +754,6 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
   HIP_TRY(ctx, enter(ctx->device));
   MarchPlan plan;
   const SceneDev sd = scene_of(bvh);
-  // the accumulators are zero: cleared by the build and by every finalisation
   ctx->replayed = 0;
   if (f->recorded) {
     m.replay_mode = 2;
@@ -784,6 +773,10 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
   in.acc = (float *)bvh->acc.p;
   in.sgacc = bvh->n_sg > 0 ? (float *)bvh->sgacc.p : nullptr;
   in.zview = nullptr;
+  // the accumulators are cleared here, so that neither a rebuild nor the
+  // finalisation has to write them
+  HIP_TRY(ctx, launch_fill(in.acc, bvh->n * kAccFloats, 0u, stream));
+  if (in.sgacc) HIP_TRY(ctx, launch_fill(in.sgacc, bvh->n * kSgAccFloats, 0u, stream));
   if (!grads->densify) {
     for (size_t k = 0; k < plan.parts[0].tabs.size(); k++) {
       if (plan.parts[0].tabs[k].n_tiles == 0) continue;
@@ -920,9 +913,18 @@ rgx_status rgx_bvh_debug(rgx_context *ctx, const rgx_bvh *b, uint64_t *keys, int
   if (aabb) HIP_TRY(ctx, hipMemcpy(aabb, b->aabb.p, n * 24, hipMemcpyDeviceToHost));
   if (nodes)
     HIP_TRY(ctx, hipMemcpy(nodes, b->nodes.p, std::max<size_t>(n - 1, 1) * 64, hipMemcpyDeviceToHost));
-  if (nodes4)
-    HIP_TRY(ctx, hipMemcpy(nodes4, b->nodes4.p, std::max<size_t>(n - 1, 1) * kNode4Floats * 4,
-                           hipMemcpyDeviceToHost));
+  if (nodes4) {
+    // the marching kernels keep the nodes in another form: made here, on demand
+    const size_t bytes = std::max<size_t>(n - 1, 1) * kNode4Floats * 4;
+    void *tmp = nullptr;
+    HIP_TRY(ctx, hipMalloc(&tmp, bytes));
+    hipError_t e = launch_fill(tmp, (int64_t)(bytes / 4), 0u, stream);
+    if (e == hipSuccess) e = launch_nodes4(b->n, (const int32_t *)b->counters.p, (const float *)b->nodes.p, (float *)tmp, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e == hipSuccess) e = hipMemcpy(nodes4, tmp, bytes, hipMemcpyDeviceToHost);
+    (void)hipFree(tmp);
+    if (e != hipSuccess) return hip_fail(ctx, e, "nodes4");
+  }
   if (n_active) {
     int32_t c = 0;
     HIP_TRY(ctx, hipMemcpy(&c, b->counters.p, 4, hipMemcpyDeviceToHost));

@@ -16,10 +16,11 @@ constexpr int kGeomFloats = 16;           // packed geometry record (64 B)
 constexpr int kAccFloats = 64;
 constexpr int kColFloats = 48;            // colour record: 3 channels x 16 SH coefficients, zero past the degree,
                                           // [channel][k][q] for coefficient 4q + k
-// 4-wide node record: 4 child boxes (lo xyz, hi xyz), 4 child links (>= 0
-// 4-wide node, < 0 leaf ~j, kNoChild none), 4 leaf ranges (first, last).
+// 4-wide node as the debug call returns it: 4 child boxes (lo xyz, hi xyz), 4
+// child links (>= 0 4-wide node, < 0 leaf ~j, kNoChild none), 4 leaf ranges
+// (first, last).
 constexpr int kNode4Floats = 36;
-// The same node for the window collection, one child per lane of a quad: 4
+// The same node for the marching kernels, one child per lane of a quad: 4
 // children x (box centre xyz, half-extents xyz, link, first leaf), 128 bytes;
 // absent children have link kNoChild and a first leaf past every range.
 constexpr int kQuadFloats = 32;

@@ -13,11 +13,10 @@ struct BuildArgs {
   const float *sg;           // [n, n_sg, 7] user lobes (n_sg > 0)
   int n_sg;
   float *sg_user, *sgrec;    // packed lobes, user order / Z order [n, kSgFloats]
-  int sh_k, col_stride, morton_bits;
+  int sh_k, morton_bits;
   float sigma_eps;
-  // scratch (user order)
-  float *geom_user, *aabb_user, *aux_user;
-  uint8_t *active;
+  // scratch
+  uint8_t *active;           // user order
   uint32_t *bounds;          // 6 ordered floats
   int32_t *counters;         // [0] active count
   uint64_t *keys[2];
@@ -26,12 +25,14 @@ struct BuildArgs {
   int *sorted_sel;           // (host) which ping-pong buffer holds the result
   // outputs (Z order)
   float *geom, *aabb, *col, *aux, *nodes;
-  float *nodes4;             // 4-wide nodes, one per binary internal node, same index
-  float *quads;              // the 4-wide nodes in the collection's layout, same index
+  float *quads;              // 4-wide nodes, one per binary internal node, same index
   float *sup;                // [n, kSupFloats] leaf-test records
   float *seg;                // segment tree of leaf boxes, 2P boxes
 };
 hipError_t launch_build(const BuildArgs &a, hipStream_t st);
+// The 4-wide nodes as rgx_bvh_debug returns them ([max(n-1,1), kNode4Floats]).
+hipError_t launch_nodes4(int64_t n, const int32_t *counters, const float *nodes, float *nodes4,
+                         hipStream_t st);
 int64_t iso_blocks(int64_t n);
 // Largest n (must equal RGX_MAX_GAUSSIANS of the public header).
 constexpr int64_t RGX_MAX_GAUSSIANS_INTERNAL = int64_t(1) << 23;
@@ -46,8 +47,7 @@ struct SceneDev {
   const float *geom;          // [n,16]
   const float *col;           // [n,col_stride]
   const float *nodes;         // [max(n-1,1),16]
-  const float *nodes4;        // [max(n-1,1),36] 4-wide nodes, one per binary internal node
-  const float *quads;         // [max(n-1,1),32] the same nodes, one child per lane of a quad
+  const float *quads;         // [max(n-1,1),32] 4-wide nodes, one per binary internal node
   const float *sup;           // [n,16] leaf-test records
   const float *aabb;          // [n,6]
   const int32_t *counters;    // [0] = active count

@@ -57,23 +57,9 @@ __device__ __forceinline__ bool box_hit(float lx, float ly, float lz, float hx, 
   return fmaxf(bmin, lo) <= fminf(bmax, hi);
 }
 
-// Entry parameter of the box over [lo, hi] (same slab arithmetic as box_hit),
-// or +inf when the box misses the interval.
-__device__ __forceinline__ float box_entry(float lx, float ly, float lz, float hx, float hy,
-                                           float hz, const Ray &r, float lo, float hi) {
-  const float tx0 = (lx - r.ox) * r.ix, tx1 = (hx - r.ox) * r.ix;
-  const float ty0 = (ly - r.oy) * r.iy, ty1 = (hy - r.oy) * r.iy;
-  const float tz0 = (lz - r.oz) * r.iz, tz1 = (hz - r.oz) * r.iz;
-  float bmin = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fminf(tz0, tz1));
-  float bmax = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fmaxf(tz0, tz1));
-  bmin = fmaf(-fabsf(bmin), 1e-6f, bmin);
-  bmax = fmaf(fabsf(bmax), 1e-6f, bmax);
-  const float e = fmaxf(bmin, lo);
-  return e <= fminf(bmax, hi) ? e : kInf;
-}
-
-// The same for a box of the collection's node layout (centre, half-extents),
-// widened by 1e-6 of the distances involved.
+// Entry parameter over [lo, hi] of a box of the 4-wide nodes (centre,
+// half-extents), widened by 1e-6 of the distances involved, or +inf when the
+// box misses the interval.
 __device__ __forceinline__ float ray_box_entry(const vf4 &q0, const vf4 &q1, const Ray &r, float lo,
                                                float hi) {
   const float tx = (q0.x - r.ox) * r.ix, ty = (q0.y - r.oy) * r.iy, tz = (q0.z - r.oz) * r.iz;
@@ -761,24 +747,20 @@ __device__ __forceinline__ void closest_pass(const SceneDev &s, const MarchOpts 
           }
         }
       } else {
-        cfloat4p np = as_const4(s.nodes4) + (kNode4Floats / 4) * node;
-        float f[kNode4Floats];
+        cfloat4p np = as_const4(s.quads) + (kQuadFloats / 4) * (size_t)node;
+        vf4 q[kQuadFloats / 4];
 #pragma unroll
-        for (int q = 0; q < kNode4Floats / 4; q++) {
-          const vf4 x = np[q];
-          f[4 * q] = x.x; f[4 * q + 1] = x.y; f[4 * q + 2] = x.z; f[4 * q + 3] = x.w;
-        }
+        for (int k = 0; k < kQuadFloats / 4; k++) q[k] = np[k];
         // the boxes and links go out as one batch of loads: the box tests and
         // the link checks below would otherwise each wait for a load of their
         // own
 #pragma unroll
-        for (int q = 0; q < 24 + 4; q++) pin_uniform(f[q]);
+        for (int k = 0; k < kQuadFloats / 4; k++) { pin_uniform(q[k].x); pin_uniform(q[k].z); }
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-          link[k] = __float_as_int(f[24 + k]);
+          link[k] = __float_as_int(q[2 * k + 1].z);
           e[k] = link[k] != kNoChild
-                     ? wave_min_nonneg_dpp(box_entry(f[6 * k], f[6 * k + 1], f[6 * k + 2], f[6 * k + 3],
-                                                     f[6 * k + 4], f[6 * k + 5], r, lo, hi))
+                     ? wave_min_nonneg_dpp(ray_box_entry(q[2 * k], q[2 * k + 1], r, lo, hi))
                      : kInf;
         }
       }
@@ -1088,7 +1070,8 @@ __device__ __forceinline__ Cone packet_cone(const WaveMem &M, const Ray &self, i
 // against the packet: false only if no point of the box lies on a ray of the
 // packet at a depth inside the shell.  The box's exact distance from the apex
 // bounds the depth from below (near the apex, inside dense clusters, an axial
-// bound is much weaker: config 4's tiles tested 19.1k leaves against 11.2k).
+// bound is weaker: 1.2M Gaussians of an outdoor scene, 1600x1063, 19.1k leaf
+// tests a tile against 17.8k and 29.7 ms against 28.3 ms).
 // From above, along the axis the box reaches v.u + h.|u|, and a ray point at
 // depth t lies in [t cos, t].
 // Across it, with p = v - (v.u) u, every box point has a distance of at least
@@ -1485,8 +1468,10 @@ enum CandMode { CAND_ALL = 0, CAND_MARK = 1, CAND_FILTER = 2 };
 // candidate: 9 readlanes and 9 FMAs on them 32.6 ns, one product and three
 // swaps 25.5 ns.  Its colour: 48 scalar-operand FMAs 85 ns and a scalar load's
 // latency, against 71 ns with the operands loaded a group ahead -- but for
-// every candidate.  In the forward, where half the candidates are hit by no
-// lane, the colour therefore stays with the vector units; the backward's
+// every candidate.  In the forward with one lane a ray, where half the
+// candidates are hit by no lane, the colour therefore stays with the vector
+// units (a split forward's operands serve 2 or 4 times as few groups, and it
+// takes the matrix units); the backward's
 // candidates are the hit ones.  1M Gaussians, 4 x 1024x768: forward 41.5 ->
 // 39.7 ms (43.2 with the colour here too), backward 32.4 -> 30.3 ms (with sum_rows16).
 template <int S>
@@ -2829,33 +2814,48 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
 // ---------------------------------------------------------------------------
 // Gradient finalisation: chain rule from the per-Gaussian accumulators to the
 // user parameters (means, log-scales, quaternions through normalisation,
-// density, SH), scattered to user order.
+// density, SH), scattered to user order.  Bound by memory: 300 bytes read and
+// 236 written a Gaussian.  A block takes its 256 Gaussians' SH rows element by
+// element -- consecutive threads write consecutive floats of a user row -- and
+// then one Gaussian a thread for the rest (a thread a whole Gaussian, whose
+// stores go to 64 rows at once, and clearing what it read: 0.78 ms at 1M
+// against 0.30 ms and 0.04 ms for the backward's clear).
+template <int SHK>
 __global__ __launch_bounds__(256) void k_finalize(int64_t n, const int32_t *__restrict__ counters,
                                                   const uint32_t *__restrict__ perm,
                                                   const float *__restrict__ geom,
-                                                  float *__restrict__ acc, int sh_k,
+                                                  const float *__restrict__ acc,
                                                   const float *__restrict__ aux,
                                                   float *__restrict__ gm, float *__restrict__ gl,
                                                   float *__restrict__ gq, float *__restrict__ gd,
                                                   float *__restrict__ gsh, int accumulate) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t u = perm[i];
+  constexpr int kRow = 3 * SHK;
+  __shared__ uint32_t user[256];
+  const int64_t i0 = (int64_t)blockIdx.x * 256;
+  const int64_t i = i0 + threadIdx.x;
+  const int n_here = (int)(n - i0 < 256 ? n - i0 : 256), n_act = counters[0];
   // overwrite mode never reads the output buffers (they may hold anything)
   auto put = [accumulate](float &dst, float v) { dst = accumulate ? dst + v : v; };
-  if (i >= counters[0]) {   // inactive Gaussian: zero gradient
+  if ((int)threadIdx.x < n_here) user[threadIdx.x] = perm[i];
+  __syncthreads();
+  for (int e = threadIdx.x; e < n_here * kRow; e += 256) {
+    const int j = e / kRow, f = e - j * kRow, m = f / 3, ch = f - 3 * m;
+    const float v = i0 + j < n_act ? acc[(size_t)kAccFloats * (i0 + j) + 16 + 16 * ch + m] : 0.0f;
+    put(gsh[(size_t)kRow * user[j] + f], v);
+  }
+  if (i >= n) return;
+  const int64_t u = user[threadIdx.x];
+  if (i >= n_act) {   // inactive Gaussian: zero gradient
     for (int k = 0; k < 3; k++) { put(gm[3 * u + k], 0.0f); put(gl[3 * u + k], 0.0f); }
     for (int k = 0; k < 4; k++) put(gq[4 * u + k], 0.0f);
     put(gd[u], 0.0f);
-    for (int k = 0; k < 3 * sh_k; k++) put(gsh[(size_t)3 * sh_k * u + k], 0.0f);
     return;
   }
-  float A[kAccFloats];
-  float4 *accp = reinterpret_cast<float4 *>(acc + (size_t)kAccFloats * i);
-  for (int k = 0; k < kAccFloats / 4; k++) {
+  float A[16];
+  const float4 *accp = reinterpret_cast<const float4 *>(acc + (size_t)kAccFloats * i);
+  for (int k = 0; k < 4; k++) {
     const float4 v = accp[k];
     A[4 * k] = v.x; A[4 * k + 1] = v.y; A[4 * k + 2] = v.z; A[4 * k + 3] = v.w;
-    accp[k] = make_float4(0.f, 0.f, 0.f, 0.f);   // ready for the next backward
   }
   const float *G = geom + (size_t)kGeomFloats * i;
   float Z[3] = {A[0], A[1], A[2]};
@@ -2882,10 +2882,6 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t n, const int32_t *__re
   const float qh[4] = {w, x, y, z};
   for (int k = 0; k < 4; k++) put(gq[4 * u + k], (dq[k] - pr * qh[k]) / qn);
   put(gd[u], A[15] / G[G_SIG]);
-  for (int m = 0; m < sh_k; m++)
-    for (int ch = 0; ch < 3; ch++) {
-      put(gsh[(size_t)3 * sh_k * u + 3 * m + ch], A[16 + 16 * ch + m]);
-    }
 }
 
 __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
@@ -2986,18 +2982,19 @@ hipError_t launch_finalize_grads(const SceneDev &s, int sh_k, float *acc, float 
                                  float *g_log_scales, float *g_quats, float *g_density,
                                  float *g_sh, int accumulate, hipStream_t st) {
   const unsigned nb = (unsigned)((s.n + 255) / 256);
-  k_finalize<<<nb, 256, 0, st>>>(s.n, s.counters, s.perm, s.geom, acc, sh_k, s.aux, g_means,
-                                 g_log_scales, g_quats, g_density, g_sh, accumulate);
+  auto k = sh_k == 1 ? k_finalize<1> : sh_k == 4 ? k_finalize<4> : sh_k == 9 ? k_finalize<9> : k_finalize<16>;
+  k<<<nb, 256, 0, st>>>(s.n, s.counters, s.perm, s.geom, acc, s.aux, g_means, g_log_scales, g_quats,
+                        g_density, g_sh, accumulate);
   return hipGetLastError();
 }
 
 // Lobe gradients to user order: per lobe, dL/da and dL/dlambda as summed;
 // the axis through u = xi / |xi|: dL/dxi = lambda (h - (h.u) u) / |xi|.
-// Absent lobes and inactive Gaussians get zeros.  Clears the accumulators.
+// Absent lobes and inactive Gaussians get zeros.
 __global__ __launch_bounds__(256) void k_finalize_sg(int64_t n, const int32_t *__restrict__ counters,
                                                      const uint32_t *__restrict__ perm,
                                                      const float *__restrict__ sg,
-                                                     float *__restrict__ sgacc, int n_sg,
+                                                     const float *__restrict__ sgacc, int n_sg,
                                                      float *__restrict__ g_sg, int accumulate) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -3019,10 +3016,6 @@ __global__ __launch_bounds__(256) void k_finalize_sg(int64_t n, const int32_t *_
     }
     float *dst = g_sg + ((size_t)u * n_sg + k) * kSgUserFloats;
     for (int e = 0; e < kSgUserFloats; e++) dst[e] = accumulate ? dst[e] + out[e] : out[e];
-  }
-  if (active) {
-    float4 *z = reinterpret_cast<float4 *>(sgacc + (size_t)kSgAccFloats * i);
-    for (int e = 0; e < kSgAccFloats / 4; e++) z[e] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
 }
 
