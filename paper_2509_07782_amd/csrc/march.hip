@@ -2671,17 +2671,33 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
             // dL/dw_k = dsigma_k + G.c_l T_k phi_k; dq_k = -w_k dL/dw_k / 2
             // moments over u_k = u_0 + k dt from sums over the sample index
             float ds = 0.0f, F1 = 0.0f, F2 = 0.0f;
+            // four samples at a time, skipped when no lane sees one of them
+            // inside the Gaussian: their terms are zeros (1M Gaussians, 2.5 of 8
+            // samples are seen: 30.5 -> 29.95 ms; a test for each sample costs
+            // what it saves, 30.6 ms).  Lanes sharing a ray hold few samples
+            // and take them all.
+            constexpr int kSkip = NL < 4 ? NL : 4;
 #pragma unroll
-            for (int k = 0; k < NL; k++) {
-              const float kf = S == 1 ? (float)k : (float)(k * S) + (float)sub;
-              const float x = S == 1 ? se.at(k) : se.at(kf);
-              const float e = __builtin_amdgcn_exp2f(x);
-              const float w = x >= se.e_min ? e : 0.0f;
-              const float wdw = w * fmaf(GW[k], gc, sg[k]);
-              ds += wdw;
-              F1 = fmaf(kf, wdw, F1);
-              F2 = fmaf(kf * kf, wdw, F2);
-              sw = fmaf(w, GW[k], sw);
+            for (int k0 = 0; k0 < NL; k0 += kSkip) {
+              float x[kSkip], top = -kInf;
+#pragma unroll
+              for (int q = 0; q < kSkip; q++) {
+                x[q] = S == 1 ? se.at(k0 + q) : se.at((float)((k0 + q) * S) + (float)sub);
+                top = fmaxf(top, x[q]);
+              }
+              if (S == 1 && ballot(top >= se.e_min) == 0) continue;
+#pragma unroll
+              for (int q = 0; q < kSkip; q++) {
+                const int k = k0 + q;
+                const float kf = S == 1 ? (float)k : (float)(k * S) + (float)sub;
+                const float e = __builtin_amdgcn_exp2f(x[q]);
+                const float w = x[q] >= se.e_min ? e : 0.0f;
+                const float wdw = w * fmaf(GW[k], gc, sg[k]);
+                ds += wdw;
+                F1 = fmaf(kf, wdw, F1);
+                F2 = fmaf(kf * kf, wdw, F2);
+                sw = fmaf(w, GW[k], sw);
+              }
             }
             const float u0 = sp.t0 - c.ts;
             const float E1 = fmaf(u0, ds, sp.dt * F1);                         // sum wdw u
