@@ -792,13 +792,25 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
     }
   } else {
     // each view's mean sums apart, as many views at a time as 256 MB hold
-    // (never fewer than one)
+    // (never fewer than one); as many as the buffer holds already where it
+    // cannot grow, in a capture or out of memory
     if (!grads->densify_views) return fail(ctx, RGX_ERR_INVALID_ARG, "densify needs densify_views");
     rgx_bvh *mb = const_cast<rgx_bvh *>(bvh);
     const int64_t per_view = bvh->n * 3;
-    const int batch = (int)std::min<int64_t>(std::min(n_views, kMaxViewsPerLaunch),
-                                             std::max<int64_t>(1, ((int64_t)1 << 26) / per_view));
-    HIP_TRY(ctx, ensure(mb->zview, (size_t)batch * per_view * sizeof(float)));
+    const size_t view_bytes = (size_t)per_view * sizeof(float);
+    int batch = (int)std::min<int64_t>(std::min(n_views, kMaxViewsPerLaunch),
+                                       std::max<int64_t>(1, ((int64_t)1 << 26) / per_view));
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIP_TRY(ctx, hipStreamIsCapturing(stream, &capture));
+    const int held = (int)std::min<size_t>(mb->zview.bytes / view_bytes, (size_t)batch);
+    if (capture != hipStreamCaptureStatusNone && held > 0) batch = held;
+    hipError_t grown = ensure(mb->zview, (size_t)batch * view_bytes);
+    while (grown == hipErrorOutOfMemory && batch > 1) {
+      (void)hipGetLastError();
+      batch /= 2;
+      grown = ensure(mb->zview, (size_t)batch * view_bytes);
+    }
+    HIP_TRY(ctx, grown);
     in.zview = (float *)mb->zview.p;
     for (size_t k = 0; k < plan.parts[0].tabs.size(); k++)
       for (int v0 = 0; v0 < plan.parts[0].tabs[k].n_views; v0 += batch) {

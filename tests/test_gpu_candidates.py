@@ -155,3 +155,49 @@ def test_densify_views_of_two_launches(torch_cuda):
     assert float((gm - ref_gm).norm()) <= 2e-5 * float(ref_gm.norm())
     assert torch.equal(seen, sum(x[1] for x in one))
     r.check_errors()
+
+
+def test_densify_captured_after_fewer_views(torch_cuda):
+    """A capture of three views after an eager call of one: the views' buffer
+    cannot grow there and holds one view at a time; every replay gives what
+    the eager call gives."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    n = 700
+    sc = inputs.make_scene("cluster", n, 23)
+    cams = [inputs.look_at_camera(21, 17, (x, 0.4, 2.2), fov_deg=45.0) for x in (-0.6, 0.1, 0.7)]
+    r, p = renderer_for(sc)
+    o = RenderOptions(dt=0.02, ess=1)
+    stat = torch.zeros(n, device="cuda")
+    seen = torch.zeros(n, dtype=torch.int32, device="cuda")
+    gt = torch.from_numpy(np.random.default_rng(3).standard_normal((3 * 21 * 17, 3))
+                          .astype(np.float32)).cuda()
+    s1 = r.new_state()
+    rgb, T = r.forward(cams[:1], o, state=s1)
+    r.backward(s1, rgb, T, gt[:21 * 17].contiguous(), None, p, densify=stat, densify_views=seen)
+    s3 = r.new_state()
+    rgb, T = r.forward(cams, o, state=s3)
+    r.backward(s3, rgb, T, gt, None, p)   # (the launches, without the statistic)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = r.backward(s3, rgb, T, gt, None, p, densify=stat, densify_views=seen)
+    got = []
+    for _ in range(3):
+        stat.zero_()
+        seen.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        got.append((stat.clone(), seen.clone(), {k: v.clone() for k, v in captured.items()}))
+    stat.zero_()
+    seen.zero_()
+    eager = r.backward(s3, rgb, T, gt, None, p, densify=stat, densify_views=seen)
+    torch.cuda.synchronize()
+    assert int(seen.sum()) > 0
+    for st, se, gr in got:
+        assert torch.equal(se, seen)
+        # the order of the atomic sums differs, a few rounding errors of each
+        assert float((st - stat).norm()) <= 1e-4 * float(stat.norm())
+        for k, v in eager.items():
+            assert float((gr[k] - v).norm()) <= 1e-4 * float(v.norm()), k
+    r.check_errors()
