@@ -143,7 +143,11 @@ typedef struct {             /* gradient outputs, user order, float32 */
      that gradient is non-zero.  Both are added to (never cleared), so the
      caller keeps the running sums between densification steps.  When
      densify is set the structure keeps a workspace of 12 n bytes for each
-     view of a launch, at most 256 MB (or one view's). */
+     view of a launch, at most 256 MB (or one view's).  The first such call,
+     and one of more views than any before, allocates it; a call being
+     captured works with what is there, fewer views at a time (it needs one
+     call before it).  Outgrown workspaces are kept until rgx_bvh_destroy, so
+     an earlier capture stays valid. */
   float *densify;            /* [n] */
   int32_t *densify_views;    /* [n], required with densify */
 } rgx_grads;

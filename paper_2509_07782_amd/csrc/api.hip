@@ -3,6 +3,7 @@
 // descriptors.  All device work is enqueued on the caller's stream.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -11,6 +12,7 @@
 #include <vector>
 
 #include "../../include/rgx.h"
+#include "buffers.hpp"
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -25,15 +27,6 @@ static_assert(RGX_STAT_Q == ST_Q && RGX_STAT_P == ST_P && RGX_STAT_SAMPLES == ST
                   RGX_NSTAT == kNStat,
               "stat slots");
 static_assert(RGX_MAX_GAUSSIANS == RGX_MAX_GAUSSIANS_INTERNAL, "size limit");
-
-namespace {
-
-struct DevBuf {
-  void *p = nullptr;
-  size_t bytes = 0;
-};
-
-}  // namespace
 
 struct rgx_context {
   int device = 0;
@@ -89,6 +82,7 @@ struct rgx_bvh {
   uint64_t serial = 0;              // the context's build serial of the current contents
   DevBuf aux, active, bounds, counters, keys0, keys1, vals0, vals1, hist, geom,
       aabb, col, nodes, quads, sup, seg, acc, zview, sg_user, sgrec, sgacc;
+  std::vector<void *> retired;      // outgrown zview buffers: a captured graph may still use them
 };
 
 // Lanes per ray (choose_split).
@@ -146,6 +140,14 @@ static hipError_t ensure(DevBuf &b, size_t bytes) {
   hipError_t e = hipMalloc(&b.p, std::max<size_t>(bytes, 256));
   if (e == hipSuccess) b.bytes = std::max<size_t>(bytes, 256);
   return e;
+}
+
+// A new device block, or nullptr (the error is not left pending).
+static void *device_block(size_t bytes) {
+  void *p = nullptr;
+  if (hipMalloc(&p, std::max<size_t>(bytes, 256)) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
 }
 
 static void release(DevBuf &b) {
@@ -216,6 +218,7 @@ void rgx_bvh_destroy(rgx_bvh *b) {
                    &b->nodes, &b->quads, &b->sup, &b->seg, &b->acc, &b->zview,
                    &b->sg_user, &b->sgrec, &b->sgacc};
   for (DevBuf *d : all) release(*d);
+  for (void *p : b->retired) (void)hipFree(p);
   delete b;
 }
 
@@ -525,20 +528,10 @@ static ViewTable sub_table(const ViewTable &t, int first, int count) {
   return o;
 }
 
-// Grows a state's record buffer to at least `need` bytes; an outgrown buffer
-// is kept until rgx_fwd_destroy (a captured graph may hold its address).
+// Grows a state's record buffer to at least `need` bytes (a failure only
+// disables the record); outgrown buffers are kept until rgx_fwd_destroy.
 static bool grow_record(rgx_fwd *f, DevBuf &b, size_t need) {
-  if (b.bytes >= need) return true;
-  void *p = nullptr;
-  const size_t bytes = std::max(need, 2 * b.bytes);
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    (void)hipGetLastError();   // an allocation failure only disables the record
-    return false;
-  }
-  if (b.p) f->retired.push_back(b.p);
-  b.p = p;
-  b.bytes = bytes;
-  return true;
+  return grow_kept(b, need, SIZE_MAX, f->retired, device_block);
 }
 
 static int64_t total_rays(const rgx_camera *cams, int32_t n_views) {
@@ -797,20 +790,15 @@ rgx_status rgx_render_backward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_f
     if (!grads->densify_views) return fail(ctx, RGX_ERR_INVALID_ARG, "densify needs densify_views");
     rgx_bvh *mb = const_cast<rgx_bvh *>(bvh);
     const int64_t per_view = bvh->n * 3;
+    constexpr size_t kViewsBytes = (size_t)1 << 28;
     const size_t view_bytes = (size_t)per_view * sizeof(float);
-    int batch = (int)std::min<int64_t>(std::min(n_views, kMaxViewsPerLaunch),
-                                       std::max<int64_t>(1, ((int64_t)1 << 26) / per_view));
+    const int want = (int)std::min<size_t>(std::min(n_views, kMaxViewsPerLaunch),
+                                           std::max<size_t>(1, kViewsBytes / view_bytes));
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     HIP_TRY(ctx, hipStreamIsCapturing(stream, &capture));
-    const int held = (int)std::min<size_t>(mb->zview.bytes / view_bytes, (size_t)batch);
-    if (capture != hipStreamCaptureStatusNone && held > 0) batch = held;
-    hipError_t grown = ensure(mb->zview, (size_t)batch * view_bytes);
-    while (grown == hipErrorOutOfMemory && batch > 1) {
-      (void)hipGetLastError();
-      batch /= 2;
-      grown = ensure(mb->zview, (size_t)batch * view_bytes);
-    }
-    HIP_TRY(ctx, grown);
+    const int batch = grow_items(mb->zview, view_bytes, want, capture == hipStreamCaptureStatusNone,
+                                 kViewsBytes, mb->retired, device_block);
+    if (batch == 0) return fail(ctx, RGX_ERR_HIP, "densification workspace: allocation failed");
     in.zview = (float *)mb->zview.p;
     for (size_t k = 0; k < plan.parts[0].tabs.size(); k++)
       for (int v0 = 0; v0 < plan.parts[0].tabs[k].n_views; v0 += batch) {

@@ -201,3 +201,47 @@ def test_densify_captured_after_fewer_views(torch_cuda):
         for k, v in eager.items():
             assert float((gr[k] - v).norm()) <= 1e-4 * float(v.norm()), k
     r.check_errors()
+
+
+def test_densify_capture_outlives_larger_calls(torch_cuda):
+    """A captured one-view densification backward, an eager call of three
+    views (the views' buffer grows), new allocations, then replays: the graph
+    still owns the memory it addresses and gives what its eager call gave."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    n, px = 700, 21 * 17
+    sc = inputs.make_scene("cluster", n, 23)
+    cams = [inputs.look_at_camera(21, 17, (x, 0.4, 2.2), fov_deg=45.0) for x in (-0.6, 0.1, 0.7)]
+    r, p = renderer_for(sc)
+    o = RenderOptions(dt=0.02, ess=1)
+    gt = torch.from_numpy(np.random.default_rng(3).standard_normal((3 * px, 3)).astype(np.float32)).cuda()
+    g1 = gt[:px].contiguous()
+
+    def buffers():
+        return torch.zeros(n, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+
+    stat, seen = buffers()
+    s1, s3 = r.new_state(), r.new_state()
+    rgb, T = r.forward(cams[:1], o, state=s1)
+    eager = r.backward(s1, rgb, T, g1, None, p, densify=stat, densify_views=seen)
+    ref_stat, ref_seen = stat.clone(), seen.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = r.backward(s1, rgb, T, g1, None, p, densify=stat, densify_views=seen)
+    rgb3, T3 = r.forward(cams, o, state=s3)
+    stat3, seen3 = buffers()
+    r.backward(s3, rgb3, T3, gt, None, p, densify=stat3, densify_views=seen3)
+    others = [torch.full((n * k,), float("nan"), device="cuda") for k in (3, 6, 9)]
+    for _ in range(2):
+        stat.zero_()
+        seen.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(seen.sum()) > 0 and torch.equal(seen, ref_seen)
+        # the order of the atomic sums differs, a few rounding errors of each
+        assert float((stat - ref_stat).norm()) <= 1e-4 * float(ref_stat.norm())
+        for k, v in eager.items():
+            assert float((captured[k] - v).norm()) <= 1e-4 * float(v.norm()), k
+        assert all(bool(t.isnan().all()) for t in others)
+    r.check_errors()
