@@ -15,6 +15,7 @@
 #include "buffers.hpp"
 #include "common.hpp"
 #include "internal.hpp"
+#include "tiles.hpp"
 
 using namespace rgx;
 
@@ -33,7 +34,7 @@ struct rgx_context {
   int n_cu = 256;
   std::string last_error;
   int32_t *queue = nullptr;        // 8 persistent-launch queues + error flag
-  std::map<std::tuple<int, int, int, int>, int32_t *> tile_orders;
+  std::map<std::tuple<int, int, int, int>, uint32_t *> tile_orders;
   // optional per-launch timing: event pairs recorded on the caller's stream
   bool timing = false;
   std::vector<hipEvent_t> ev;       // 2 per recorded launch, reused after a reset
@@ -400,14 +401,9 @@ static rgx_status make_opts(rgx_context *ctx, const rgx_bvh *b, const rgx_render
   return RGX_OK;
 }
 
-// Tiles of 64 / split rays: the tile shape loses its longer side's half per
-// factor of two.
 static void set_split(MarchOpts &m, int split) {
   m.split = split;
-  for (int k = split; k > 1; k >>= 1) {
-    if (m.tile_h >= m.tile_w) m.tile_h >>= 1;
-    else m.tile_w >>= 1;
-  }
+  split_tile(split, m.tile_w, m.tile_h);
   m.tile_w_log2 = ilog2(m.tile_w);
 }
 
@@ -430,22 +426,25 @@ static uint32_t interleave2(uint32_t x, uint32_t y) {
   return r;
 }
 
-// Tile coordinates of a view in Morton order of (tx, ty), cached per shape.
-static rgx_status tile_order(rgx_context *ctx, int W, int H, int tw, int th, const int32_t **out) {
+// Tile coordinates of a view in Morton order of (tx, ty), cached per shape;
+// nullptr where they do not fit their words (tile_codes_hold).
+static rgx_status tile_order(rgx_context *ctx, int W, int H, int tw, int th, const uint32_t **out) {
+  *out = nullptr;
+  if (!tile_codes_hold(((int64_t)W + tw - 1) / tw, ((int64_t)H + th - 1) / th)) return RGX_OK;
   auto key = std::make_tuple(W, H, tw, th);
   auto it = ctx->tile_orders.find(key);
   if (it != ctx->tile_orders.end()) { *out = it->second; return RGX_OK; }
   const int tx = (W + tw - 1) / tw, ty = (H + th - 1) / th;
-  std::vector<std::pair<uint32_t, int32_t>> v;
+  std::vector<std::pair<uint32_t, uint32_t>> v;
   v.reserve((size_t)tx * ty);
   for (int y = 0; y < ty; y++)
-    for (int x = 0; x < tx; x++) v.push_back({interleave2(x, y), x | (y << 16)});
+    for (int x = 0; x < tx; x++) v.push_back({interleave2(x, y), tile_code(x, y)});
   std::sort(v.begin(), v.end());
-  std::vector<int32_t> codes(v.size());
+  std::vector<uint32_t> codes(v.size());
   for (size_t i = 0; i < v.size(); i++) codes[i] = v[i].second;
-  int32_t *d = nullptr;
-  HIP_TRY(ctx, hipMalloc(&d, codes.size() * sizeof(int32_t)));
-  HIP_TRY(ctx, hipMemcpy(d, codes.data(), codes.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+  uint32_t *d = nullptr;
+  HIP_TRY(ctx, hipMalloc(&d, codes.size() * sizeof(uint32_t)));
+  HIP_TRY(ctx, hipMemcpy(d, codes.data(), codes.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
   ctx->tile_orders[key] = d;
   *out = d;
   return RGX_OK;

@@ -52,7 +52,7 @@ constexpr int kNStatUsed = 16;
 constexpr int kNStat = 16;
 
 struct View {
-  const int32_t *tile_order;  // tile coordinates (tx | ty << 16) in launch order
+  const uint32_t *tile_order; // tile coordinates (tile_code) in launch order; nullptr: row by row
   int32_t width, height, tiles_x, tiles_y;
   int32_t tile_begin;     // first global tile index of the view
   int32_t ray_begin;      // first output ray of the view

@@ -25,6 +25,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "tiles.hpp"
 
 
 namespace rgx {
@@ -255,8 +256,15 @@ __device__ __forceinline__ Pixel tile_pixel(const ViewTable &vt, const MarchOpts
     p.px = r % V.width;
     p.py = r / V.width;
   } else {
-    const int code = V.tile_order[t];
-    const int tx = code & 0xffff, ty = code >> 16;
+    int tx, ty;
+    if (V.tile_order) {
+      const uint32_t code = V.tile_order[t];
+      tx = tile_column(code);
+      ty = tile_row(code);
+    } else {
+      ty = t / V.tiles_x;
+      tx = t - ty * V.tiles_x;
+    }
     p.px = tx * op.tile_w + (lane & (op.tile_w - 1));
     p.py = ty * op.tile_h + (lane >> op.tile_w_log2);
     p.valid = p.px < V.width && p.py < V.height;

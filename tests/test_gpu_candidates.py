@@ -245,3 +245,36 @@ def test_densify_capture_outlives_larger_calls(torch_cuda):
             assert float((captured[k] - v).norm()) <= 1e-4 * float(v.norm()), k
         assert all(bool(t.isnan().all()) for t in others)
     r.check_errors()
+
+
+@pytest.mark.parametrize("size,tile,n", [
+    ((1, 140_000), (8, 8), 120_000),    # 35000 rows of tiles, 4 lanes a ray
+    ((1, 270_000), (8, 8), 120_000),    # 67500, 2 lanes: no tile table
+    ((2, 262_200), (8, 8), 3_000),      # 32775, one lane
+    ((70_003, 2), (1, 64), 3_000),      # 70003 columns, 2 lanes: no tile table
+])
+def test_long_thin_images(torch_cuda, size, tile, n):
+    """Images with more tiles on a side than a signed or unsigned 16-bit
+    number counts: every pixel, and the gradients, as with rays in row order
+    (which has no tiles)."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene("cluster", n, 19)
+    w, h = size
+    pose = inputs.look_at_camera(8, 8, (0.2, 0.1, 2.6)).cam_to_world
+    f = 0.9 * max(w, h)
+    cam = inputs.Camera(w, h, f, f, w / 2.0, h / 2.0, pose, 0.0, 6.0)
+    r, p = renderer_for(sc)
+    kw = dict(adaptive=True, ess=1, t_eps=1e-4)
+    o = RenderOptions(tile_w=tile[0], tile_h=tile[1], **kw)
+    st, own = r.new_state(), r.new_state()
+    rgb, T = r.forward([cam], o, state=st)
+    ref, ref_T = r.forward([cam], RenderOptions(ray_order=0, **kw), state=own)
+    assert torch.equal(rgb, ref) and torch.equal(T, ref_T)
+    assert float((1 - T).max()) > 0.1
+    g = torch.from_numpy(np.random.default_rng(2).standard_normal(tuple(rgb.shape)).astype(np.float32)).cuda()
+    a, b = r.backward(st, rgb, T, g, None, p), r.backward(own, ref, ref_T, g, None, p)
+    for k, v in b.items():
+        # the same terms in another order of the atomic sums
+        assert float((a[k] - v).norm()) <= 2e-5 * float(v.norm()), k
+    r.check_errors()
