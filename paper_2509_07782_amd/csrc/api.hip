@@ -450,6 +450,17 @@ static rgx_status tile_order(rgx_context *ctx, int W, int H, int tw, int th, con
   return RGX_OK;
 }
 
+// Tiles of a view, across and down.
+static void tile_grid(const MarchOpts &m, const rgx_camera &c, int &tx, int &ty) {
+  if (m.ray_order == 0) {
+    tx = (c.width * c.height + 64 / m.split - 1) / (64 / m.split);
+    ty = 1;
+  } else {
+    tx = (c.width + m.tile_w - 1) / m.tile_w;
+    ty = (c.height + m.tile_h - 1) / m.tile_h;
+  }
+}
+
 // Split the views into launches of at most kMaxViewsPerLaunch.
 static rgx_status view_tables(rgx_context *ctx, const rgx_camera *cams, int n_views,
                               const MarchOpts &m, std::vector<ViewTable> &tabs,
@@ -467,16 +478,11 @@ static rgx_status view_tables(rgx_context *ctx, const rgx_camera *cams, int n_vi
       View &V = t.v[t.n_views++];
       V.width = c.width;
       V.height = c.height;
-      if (m.ray_order == 0) {
-        V.tiles_x = (c.width * c.height + 64 / m.split - 1) / (64 / m.split);
-        V.tiles_y = 1;
-        V.tile_order = nullptr;
-      } else {
-        V.tiles_x = (c.width + m.tile_w - 1) / m.tile_w;
-        V.tiles_y = (c.height + m.tile_h - 1) / m.tile_h;
-        s = tile_order(ctx, c.width, c.height, m.tile_w, m.tile_h, &V.tile_order);
-        if (s != RGX_OK) return s;
-      }
+      tile_grid(m, c, V.tiles_x, V.tiles_y);
+      V.tile_order = nullptr;
+      if (m.ray_order == 1 &&
+          (s = tile_order(ctx, c.width, c.height, m.tile_w, m.tile_h, &V.tile_order)) != RGX_OK)
+        return s;
       {
         // every segment must advance in FP32 up to t_far: its length N_s dt
         // (at least N_s dt_min in adaptive mode) above twice the spacing of
@@ -582,23 +588,78 @@ static int64_t count_tiles64(const rgx_camera *cams, int32_t n_views) {
   return t;
 }
 
-// Fills the parts.  Which views lie inside the scene is known on the device
-// only: where the two differ both kinds of launch go out, and a wave leaves
-// the tiles of the other's views alone.
-static rgx_status make_plan(rgx_context *ctx, const MarchOpts &m, Split split, const rgx_camera *cams,
-                            int32_t n_views, MarchPlan &p) {
+// The launches a split takes: options, views and tile shape of each.  Which
+// views lie inside the scene is known on the device only: where the two differ
+// both kinds of launch go out, and a wave leaves the tiles of the other's views
+// alone.
+static int split_parts(const MarchOpts &m, Split split, MarchOpts (&part)[2]) {
   const bool both = split.outside != split.inside;
   for (int k = 0; k < (both ? 2 : 1); k++) {
+    part[k] = m;
+    part[k].views = !both ? VIEWS_ALL : k == 0 ? VIEWS_OUTSIDE : VIEWS_INSIDE;
+    set_split(part[k], k == 0 ? split.outside : split.inside);
+  }
+  return both ? 2 : 1;
+}
+
+// Fills the parts.  The tables of 64-ray tiles are made too: a later call of
+// these image sizes that takes one lane a ray may be a captured one.
+static rgx_status make_plan(rgx_context *ctx, const MarchOpts &m, Split split, const rgx_camera *cams,
+                            int32_t n_views, MarchPlan &p) {
+  MarchOpts opts[2];
+  const int parts = split_parts(m, split, opts);
+  if (m.ray_order == 1)
+    for (int v = 0; v < n_views; v++) {
+      const uint32_t *order;
+      const rgx_status s = tile_order(ctx, cams[v].width, cams[v].height, m.tile_w, m.tile_h, &order);
+      if (s != RGX_OK) return s;
+    }
+  for (int k = 0; k < parts; k++) {
     MarchPlan::Part part;
-    part.m = m;
-    part.m.views = !both ? VIEWS_ALL : k == 0 ? VIEWS_OUTSIDE : VIEWS_INSIDE;
-    set_split(part.m, k == 0 ? split.outside : split.inside);
+    part.m = opts[k];
     const rgx_status s = view_tables(ctx, cams, n_views, part.m, part.tabs, p.tiles);
     if (s != RGX_OK) return s;
     for (const ViewTable &t : part.tabs) p.tiles += t.n_tiles;
     p.parts.push_back(std::move(part));
   }
   return RGX_OK;
+}
+
+// Dwords of a forward's record pool: 48 KB per 64 rays on average for the
+// window lists, as much again for the per-sample sums at N_s <= 8 (twice that
+// at 16), all twice for tiles of fewer rays, which share less; at least 64 MB
+// so that a call of few tiles with long window lists still records them all;
+// and within the caller's cap (the two counter dwords always fit).
+static size_t record_pool(const rgx_context *ctx, const rgx_render_opts *o, Split split, int64_t tiles64) {
+  const size_t per_tile = (size_t)kWrecDwordsPerTile +
+                          (o->no_sample_record ? 0 : (size_t)kSrecDwordsPerTile * (o->n_s > 8 ? 2 : 1));
+  const int shared = split.outside > 1 || split.inside > 1 ? 2 : 1;
+  size_t pool = std::min<size_t>(std::max<size_t>(2 + (size_t)tiles64 * per_tile * shared, (size_t)1 << 24),
+                                 0xfffffff0u);
+  if (ctx->record_limit > 0)
+    pool = std::max<size_t>(std::min<size_t>(pool, (size_t)ctx->record_limit / sizeof(uint32_t)), 2);
+  return pool;
+}
+
+// Whether a forward with this split finds its tile tables and (recording into
+// `f`) its record buffers made already: a call being captured cannot allocate.
+static bool split_is_sized(const rgx_context *ctx, const MarchOpts &m, Split split, const rgx_camera *cams,
+                           int32_t n_views, const rgx_fwd *f, size_t pool) {
+  MarchOpts part[2];
+  const int parts = split_parts(m, split, part);
+  int64_t tiles = 0;
+  for (int k = 0; k < parts; k++)
+    for (int v = 0; v < n_views; v++) {
+      const rgx_camera &c = cams[v];
+      int tx, ty;
+      tile_grid(part[k], c, tx, ty);
+      tiles += (int64_t)tx * ty;
+      if (m.ray_order == 1 && tile_codes_hold(tx, ty) &&
+          !ctx->tile_orders.count(std::make_tuple(c.width, c.height, part[k].tile_w, part[k].tile_h)))
+        return false;
+    }
+  return !f || (f->wrec.bytes >= pool * sizeof(uint32_t) &&
+                f->wrec_tile.bytes >= (size_t)tiles * 2 * sizeof(uint32_t));
 }
 
 // waves_per_cu: how many of the kernel's one-wave workgroups fit on a CU
@@ -628,9 +689,20 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
   if (!cams || n_views <= 0) return fail(ctx, RGX_ERR_INVALID_ARG, "no views");
   for (int v = 0; v < n_views; v++)
     if ((s = check_camera(ctx, cams[v])) != RGX_OK) return s;
+  const bool record = state && m.ess && !m.brute_force && !opts->no_record;
   // (the statistics are those of 64-ray waves)
   const int64_t tiles64 = count_tiles64(cams, n_views);
-  const Split split = stats ? Split() : choose_split(ctx, bvh, m, tiles64);
+  Split split = stats ? Split() : choose_split(ctx, bvh, m, tiles64);
+  if (split.outside > 1 || split.inside > 1) {
+    // captured after calls that took one lane a ray (more views, statistics,
+    // another n): so does this one, with the tables and buffers they made
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone &&
+        !split_is_sized(ctx, m, split, cams, n_views, record ? *state : nullptr,
+                        record_pool(ctx, opts, split, tiles64)))
+      split = Split();
+  }
   MarchPlan plan;
   if ((s = make_plan(ctx, m, split, cams, n_views, plan)) != RGX_OK) return s;
   const SceneDev sd = scene_of(bvh);
@@ -660,29 +732,15 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
     // results, every window list of every tile and each segment step's
     // per-sample sums
     const size_t need = (size_t)rays * kReplayK * sizeof(float);
-    // a shared pool: 48 KB per tile on average for the window lists, as much
-    // again for the per-sample sums at N_s <= 8 (twice that at 16), at least
-    // 64 MB so that a call of few tiles with long window lists still records
-    // them all
-    const bool samples = !opts->no_sample_record;
-    const size_t per_tile = (size_t)kWrecDwordsPerTile +
-                            (samples ? (size_t)kSrecDwordsPerTile * (m.n_s > 8 ? 2 : 1) : 0);
-    // (tiles of fewer rays share less: twice as much for both kinds of them)
-    size_t pool = std::min<size_t>(
-        std::max<size_t>(2 + (size_t)tiles64 * per_tile * (split.outside > 1 || split.inside > 1 ? 2 : 1), (size_t)1 << 24),
-        0xfffffff0u);
-    // a caller's cap (the two counter dwords always fit)
-    if (ctx->record_limit > 0)
-      pool = std::max<size_t>(std::min<size_t>(pool, (size_t)ctx->record_limit / sizeof(uint32_t)), 2);
-    if (m.ess && !m.brute_force && !opts->no_record && grow_record(f, f->replay, need) &&
-        grow_record(f, f->wrec, pool * sizeof(uint32_t)) &&
+    const size_t pool = record_pool(ctx, opts, split, tiles64);
+    if (record && grow_record(f, f->replay, need) && grow_record(f, f->wrec, pool * sizeof(uint32_t)) &&
         grow_record(f, f->wrec_tile, (size_t)tiles * 2 * sizeof(uint32_t))) {
       m.replay_mode = 1;
       m.replay = (float *)f->replay.p;
       m.wrec = (uint32_t *)f->wrec.p;
       m.wrec_tile = (uint32_t *)f->wrec_tile.p;
       m.wrec_cap = f->wrec_cap = (uint32_t)pool;
-      m.sample_rec = samples ? 1 : 0;
+      m.sample_rec = opts->no_sample_record ? 0 : 1;
       // the pool's 64-bit allocation counter (dwords 0-1) starts past itself
       // (fill kernels, not memset nodes, so the call can be captured)
       hipError_t e = launch_fill(f->wrec.p, 1, 2u, stream);

@@ -278,3 +278,65 @@ def test_long_thin_images(torch_cuda, size, tile, n):
         # the same terms in another order of the atomic sums
         assert float((a[k] - v).norm()) <= 2e-5 * float(v.norm()), k
     r.check_errors()
+
+
+@pytest.mark.parametrize("warm", ["more views", "statistics"])
+def test_capture_after_calls_with_one_lane_a_ray(torch_cuda, warm):
+    """A small forward and its backward captured after eager calls whose rays
+    had one lane each: nothing is left to allocate, and every replay gives the
+    eager result."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene("cluster", 3_000, 29)
+    cams = [inputs.look_at_camera(163, 129, (2.5 * np.sin(v), 0.3, 2.5 * np.cos(v))) for v in range(8)]
+    r, p = renderer_for(sc)
+    o = RenderOptions(adaptive=True, ess=1, t_eps=1e-4)
+    st, ref = r.new_state(), r.new_state()
+    g = torch.from_numpy(np.random.default_rng(4).standard_normal((163 * 129, 3)).astype(np.float32)).cuda()
+    if warm == "more views":
+        rgb, T = r.forward(cams, o, state=st)
+        r.backward(st, rgb, T, g.repeat(8, 1), None, p)
+    else:
+        rgb, T, _ = r.forward(cams[:1], o, stats=True, state=st)
+        r.backward(st, rgb, T, g, None, p)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rgb, T = r.forward(cams[:1], o, state=st)
+        got = r.backward(st, rgb, T, g, None, p)
+    eager, eager_T = r.forward(cams[:1], o, state=ref)
+    want = r.backward(ref, eager, eager_T, g, None, p)
+    for _ in range(3):
+        rgb.zero_()
+        T.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(rgb, eager) and torch.equal(T, eager_T)
+        for k, v in want.items():
+            # the order of the sums over rays differs
+            assert float((got[k] - v).norm()) <= 2e-5 * float(v.norm()), k
+    r.check_errors()
+
+
+def test_capture_after_calls_with_shared_rays(torch_cuda):
+    """Eight views captured after an eager call of one, whose rays were shared
+    between lanes: the tables of their 64-ray tiles are there."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene("cluster", 3_000, 29)
+    cams = [inputs.look_at_camera(163, 129, (2.5 * np.sin(v), 0.3, 2.5 * np.cos(v))) for v in range(8)]
+    r, _ = renderer_for(sc)
+    o = RenderOptions(adaptive=True, ess=1, t_eps=1e-4)
+    r.forward(cams[:1], o)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rgb, T = r.forward(cams, o)
+    eager, eager_T = r.forward(cams, o)
+    for _ in range(3):
+        rgb.zero_()
+        T.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(rgb, eager) and torch.equal(T, eager_T)
+    r.check_errors()
