@@ -1086,7 +1086,9 @@ __device__ __forceinline__ Cone packet_cone(const WaveMem &M, const Ray &self, i
 // |p| - h.|p| / |p| from the axis, and a cone point at most tan times its
 // axial coordinate; the inequality is taken times |p| to need no division.
 // Margins: 2e-5 of the distance (rounding of v, v.u and p), 1e-3 of the
-// box's extent across.
+// box's extent across.  Every comparison rejects, so that the NaN of a box with
+// infinite sides (a Gaussian whose squared scale overflows, and every node
+// above it) keeps it.
 __device__ __forceinline__ bool cone_box(const Cone &k, float vx, float vy, float vz, float hx,
                                          float hy, float hz) {
   const float al = fmaf(vx, k.ux, fmaf(vy, k.uy, vz * k.uz));
@@ -1100,8 +1102,8 @@ __device__ __forceinline__ bool cone_box(const Cone &k, float vx, float vy, floa
   const float qx = fmaxf(fabsf(vx) - hx, 0.0f), qy = fmaxf(fabsf(vy) - hy, 0.0f),
               qz = fmaxf(fabsf(vz) - hz, 0.0f);
   const float near2 = fmaf(qx, qx, fmaf(qy, qy, qz * qz)), reach = k.t_hi + pad;
-  return (near2 <= reach * reach) & (far >= k.t_lo * k.cs) & (far >= 0.0f) &
-         (fmaf(-1.001f, rp, p2) * k.cs <= fmaf(far, k.sn, pad) * pw);
+  return !(near2 > reach * reach) & !(far < k.t_lo * k.cs) & !(far < 0.0f) &
+         !(fmaf(-1.001f, rp, p2) * k.cs > fmaf(far, k.sn, pad) * pw);
 }
 
 // Depth bounds of the packet's rays inside a sphere (centre v relative to the
@@ -1115,7 +1117,7 @@ __device__ __forceinline__ bool cone_sphere(const Cone &k, float vx, float vy, f
   *dlo = d - pad;
   *dhi = d + pad;
   const float al = fmaf(vx, k.ux, fmaf(vy, k.uy, vz * k.uz));
-  return (*dlo <= k.t_hi) & (*dhi >= k.t_lo) & (al + pad >= 0.0f);
+  return !(*dlo > k.t_hi) & !(*dhi < k.t_lo) & !(al + pad < 0.0f);
 }
 
 // Depth bounds [lo, hi] of every ray of a narrow packet inside one ellipsoid,
@@ -1154,8 +1156,9 @@ __device__ __forceinline__ bool cone_ellipsoid(const Cone &k, float vx, float vy
   const float y1 = fmaf(n1.x, px, fmaf(n1.y, py, n1.z * pz));
   const float y2 = fmaf(n2.x, px, fmaf(n2.y, py, n2.z * pz));
   const float rwp = __builtin_amdgcn_sqrtf(fmaf(y0, y0, fmaf(y1, y1, y2 * y2)));
-  return (*lo <= k.t_hi) & (*hi >= k.t_lo) &
-         (fmaf(-1.001f, rwp, p2) * k.cs <= fmaf(al + ru, k.sn, pad) * perp);
+  // (rejecting comparisons, as in cone_box)
+  return !(*lo > k.t_hi) & !(*hi < k.t_lo) &
+         !(fmaf(-1.001f, rwp, p2) * k.cs > fmaf(al + ru, k.sn, pad) * perp);
 }
 
 // Wave-uniform state of a window collection.  The list holds the entries

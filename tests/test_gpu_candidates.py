@@ -340,3 +340,28 @@ def test_capture_after_calls_with_shared_rays(torch_cuda):
         torch.cuda.synchronize()
         assert torch.equal(rgb, eager) and torch.equal(T, eager_T)
     r.check_errors()
+
+
+@pytest.mark.parametrize("size,fov,tile", [((53, 37), 60.0, (8, 8)), ((53, 37), 160.0, (64, 1)),
+                                           ((320, 213), 60.0, (8, 8)), ((320, 213), 160.0, (64, 1))])
+@pytest.mark.parametrize("scales", [(45.0, 45.0, 45.0), (45.0, -3.0, -3.0), (43.0, 43.0, -2.0)])
+def test_boxes_with_infinite_sides(torch_cuda, size, fov, tile, scales):
+    """A Gaussian whose box overflows to infinite sides makes every node above
+    it infinite: nothing below them is lost (brute force, bit for bit).  Narrow
+    packets and ones too wide for the cone test, one and four lanes a ray."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene("cluster", 2_000, 31)
+    for i in (5, 900):
+        sc["log_scales"][i] = np.float32(scales)
+        sc["density"][i] = 0.5
+    cam = inputs.look_at_camera(*size, (0.0, 0.1, 2.4), fov_deg=fov)
+    r, _ = renderer_for(sc)
+    kw = dict(adaptive=True, ess=1, t_eps=1e-4, tile_w=tile[0], tile_h=tile[1])
+    rgb, T = r.forward([cam], RenderOptions(**kw))
+    one, one_T, _ = r.forward([cam], RenderOptions(**kw), stats=True)
+    brute, brute_T = r.forward([cam], RenderOptions(brute_force=True, **kw))
+    assert float((1 - brute_T).max()) > 0.5
+    assert torch.equal(rgb, brute) and torch.equal(T, brute_T)
+    assert torch.equal(one, brute) and torch.equal(one_T, brute_T)
+    r.check_errors()
