@@ -84,8 +84,9 @@ struct LaunchShape {
 
 // Resident one-wave workgroups per CU of the march kernels (their launch
 // bounds and LDS use), used to size persistent grids.
+constexpr int kLdsBytes = 160 * 1024, kBwdWavesPerCu = 8;
 inline int fwd_waves_per_cu(const MarchOpts &m) { return m.n_s <= 8 ? 12 : 8; }
-inline int bwd_waves_per_cu() { return 8; }
+inline int bwd_waves_per_cu() { return kBwdWavesPerCu; }
 hipError_t launch_forward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
                           const FwdOut &out, const LaunchShape &ls, hipStream_t st);
 hipError_t launch_backward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,

@@ -589,16 +589,16 @@ struct ShBatch {
 // A_c is formed from Y and G at every product (one multiplication beside
 // three matrix instructions): held whole it took 32 more registers, and the
 // kernel spilled.
-template <int S>
+template <bool ROWS>
 struct ShMem {
   float s[16 * kSbStride];
   float g[3][64];
-  float r[S == 1 ? 64 * kRowStride : 1];   // a Gaussian's slots, lane by lane (sum_rows16)
+  float r[ROWS ? 64 * kRowStride : 1];   // a Gaussian's slots, lane by lane (sum_rows16)
 };
 
 // Y and G of a new tile.
-template <int S>
-__device__ __forceinline__ void sh_batch_start(ShBatch &B, ShMem<S> &sm, const float *Y, float g0,
+template <bool ROWS>
+__device__ __forceinline__ void sh_batch_start(ShBatch &B, ShMem<ROWS> &sm, const float *Y, float g0,
                                                float g1, float g2, int lane) {
 #pragma unroll
   for (int m = 0; m < 16; m++) sm.s[m * kSbStride + lane] = Y[m];
@@ -613,8 +613,8 @@ __device__ __forceinline__ void sh_batch_start(ShBatch &B, ShMem<S> &sm, const f
 }
 
 // Multiplies out the staged batch and adds it to the accumulators.
-template <int S>
-__device__ __forceinline__ void sh_batch_flush(ShBatch &B, const ShMem<S> &sm, float *acc, int sh_k,
+template <bool ROWS>
+__device__ __forceinline__ void sh_batch_flush(ShBatch &B, const ShMem<ROWS> &sm, float *acc, int sh_k,
                                                int lane) {
   if (B.n == 0) return;
   __builtin_amdgcn_wave_barrier();
@@ -1570,7 +1570,9 @@ __device__ __forceinline__ void cand_pin(const CandOps &G) {
 // the same pass) and visits only the marked entries, and a CAND_FILTER pass
 // visits only the marked entries (list source only; the brute-force source
 // visits everything).
-template <int MODE, bool COL, int S, class Visit, class Fn, class After>
+// LATE: the colour's matrix instructions follow the hit tests, in groups some
+// lane hit, instead of going in between the chords.
+template <int MODE, bool COL, bool LATE = false, int S, class Visit, class Fn, class After>
 __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, ListMem &M,
                                                    int count, int lane, float a_min, float b_max,
                                                    int n_active, const Ray &r, const TileOps<S> &ops,
@@ -1659,7 +1661,7 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
         for (int p = 0; p < kG; p++) acc[p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
       }
       auto mm_step = [&](int i) {   // (16 steps; every S-th carries an instruction)
-        if constexpr (COL) {
+        if constexpr (COL && !LATE) {
           if (i % S == 0) {
             const int q = i / 4, p = (i / S) % kG;
             __builtin_amdgcn_sched_barrier(0);
@@ -1707,8 +1709,15 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
                  ballot(g[c].ch.tout >= lo) & (first + c < n ? wanted : 0ull);
         mm_step(12 + c);
       }
-      float col[3][4];
-      if constexpr (COL) {
+      float col[3][4] = {};
+      if (COL && (!LATE || (any[0] | any[1] | any[2] | any[3]) != 0)) {
+        if constexpr (LATE) {
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int p = 0; p < kG; p++)
+              acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.f[q], ops.y[p][q], acc[p], 0, 0, 0);
+        }
 #pragma unroll
         for (int i = 0; i < 3; i++) {
 #pragma unroll
@@ -2497,8 +2506,18 @@ template <int NS, int S, bool SG, bool REPLAY>
 __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt, MarchOpts op,
                                                     BwdIn in, LaunchShape ls) {
   constexpr int kMode = REPLAY ? WIN_REPLAY : WIN_BOTH;
+  // Where a tile may have to search, with one lane a ray: colours only for the
+  // groups some lane hits, and the slots summed in registers.  Half of a
+  // list's candidates and nearly all of a brute-force pass are hit by no lane,
+  // and sum_rows16's buffer beside the search's memory left seven waves to a
+  // CU.  Backward ms before and after: 1M Gaussians, 4 x 1024x768, searching
+  // everything 85.0 and 76.5, searches recorded 48.0 and 44.4; 1k, 640x480,
+  // brute force 48.6 and 30.5; 100k, 800x800, fixed step, searches recorded 9.5
+  // and 8.7.  (Vector colours of the hits alone: 84.8, 54.1, 30.0 and 10.3.)
+  constexpr bool kLate = !REPLAY && S == 1, kRows = REPLAY && S == 1;
   __shared__ std::conditional_t<REPLAY, ListMem, WaveMem> M;
-  __shared__ ShMem<S> sb;
+  __shared__ ShMem<kRows> sb;
+  static_assert((sizeof(M) + sizeof(sb)) * kBwdWavesPerCu <= kLdsBytes, "resident waves");
   ShBatch shb;
   constexpr int kRays = 64 / S, NL = NS / S;   // rays of the tile; samples of a ray per lane
   const int lane = threadIdx.x;
@@ -2605,7 +2624,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
         const bool use_marks = rec_next_marks(rec, op, M, win.count, win.kind, lane, ls.error_flag);
         if constexpr (!REPLAY)
         if (!from_rec)
-        for_each_candidate<CAND_MARK, true>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
+        for_each_candidate<CAND_MARK, true, kLate>(win.kind, s, M, win.count, lane, a_min, b_max, n_active,
                                             r, ops, go, lo, hi, [] {},
                                             [&](int, int j, const Cand &g, bool hit) {
         const Chord &c = g.ch;
@@ -2744,7 +2763,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
           // (through LDS the waves of a full chip gain 0.8 ms in 31.2, 1M
           // Gaussians, 4 x 1024x768; a launch of few waves waits for it: 22.8 ms
           // against 20.8, 100k, 8 x 160x121 one by one)
-          if constexpr (S == 1) {
+          if constexpr (kRows) {
             red[ci] = sum_rows16(sb.r, v, lane);
           } else {
             float t[16];
@@ -2760,7 +2779,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
         auto put_b = [&](int ids, int first, uint32_t hits) {
           if (hits != 0) {
             float mine;
-            if constexpr (S == 1) {
+            if constexpr (kRows) {
               // red[c]: slot lane & 15 summed over one row of lanes
               mine = swap16_sum(swap32_sum(red[0], red[2]), swap32_sum(red[1], red[3]));
             } else {
@@ -2815,7 +2834,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
             }
             kind_cur = SRC_LIST;
           }
-          for_each_candidate<CAND_FILTER, true>(kind_cur, s, M, n_cur, lane, a_min, b_max, n_active,
+          for_each_candidate<CAND_FILTER, true, kLate>(kind_cur, s, M, n_cur, lane, a_min, b_max, n_active,
                                                 r, ops, any, lo, hi, [] {}, pass_b, put_b, marked);
         }
       }
