@@ -92,7 +92,7 @@ struct MarchOpts {
   uint32_t *wrec_tile;    // per tile of the call: (complete, first chunk offset)
   uint32_t wrec_cap;      // pool size in dwords
   int32_t sample_rec;     // the record also holds each segment step's per-sample sums
-  int32_t rest;           // backward: this launch takes the tiles a replaying one left
+  int32_t either;         // backward: the record says which of two launches works
 };
 // all views, or those whose camera lies inside / outside the bounds of the means
 enum { VIEWS_ALL = 0, VIEWS_INSIDE, VIEWS_OUTSIDE };

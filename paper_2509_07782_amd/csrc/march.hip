@@ -2497,11 +2497,17 @@ __device__ __forceinline__ void sg_slots(const float *sg, float *sgacc, int j, f
 // constant times one scalar per (ray, Gaussian), are staged 16 Gaussians at a
 // time and multiplied out on the matrix cores.
 
-// REPLAY: only the tiles whose record is complete, per-sample sums included;
-// nothing there walks the tree or sums Gaussians again, and without that code
-// the kernel fits two waves per SIMD without spills.  (Three, at 168 registers,
-// spill into the candidate loop: 37.8 ms against 31.5.)  Otherwise the tiles of every other
-// kind; launched after a REPLAY launch (op.rest) it takes what that left.
+// REPLAY: every tile's record is complete, per-sample sums included; nothing
+// there walks the tree or sums Gaussians again, and without that code the
+// kernel fits two waves per SIMD without spills.  (Three, at 168 registers,
+// spill into the candidate loop: 37.8 ms against 31.5.)  Otherwise the tiles
+// are recorded or not, each for itself.  Whether every record found room is
+// known on the device only, so both are launched and the waves of one leave
+// at once (op.either).  With a replaying launch for the recorded tiles and one
+// of this kind for the rest, each waited for its own slowest tiles: 100k
+// Gaussians, 800x800, fixed step, 1490 tiles of 10000 unrecorded, 11.8 ms
+// against 9.7; 1M, 4 x 1024x768, 22150 of 49152, 68.4 against 64.0; outdoor
+// 3M, 1297x840, 2440 of 17115, 36.6 against 37.3.
 template <int NS, int S, bool SG, bool REPLAY>
 __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt, MarchOpts op,
                                                     BwdIn in, LaunchShape ls) {
@@ -2525,8 +2531,10 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
   const int n_active = uniform_int(s.counters[0]);
   const bool grid = !op.adaptive && op.ess != 2;
   if (!marches_any(s, op, vt)) return;
-  // every record found room: nothing is left for this launch
-  if (!REPLAY && op.rest && *reinterpret_cast<const unsigned long long *>(op.wrec) <= op.wrec_cap) return;
+  if (op.either) {
+    const bool all = *reinterpret_cast<const unsigned long long *>(op.wrec) <= op.wrec_cap;
+    if (REPLAY != all) return;
+  }
   bool first = true;
   for (;;) {
     int w;
@@ -2545,7 +2553,10 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
     if (!marches_view(s, op, V)) continue;
     WinRec rec;
     rec_start(rec, op, vt, w);
-    if (REPLAY ? !rec.ok : (op.rest && rec.ok)) continue;
+    if (REPLAY && !rec.ok) {   // (cannot happen)
+      if (ls.error_flag) *ls.error_flag = 5;
+      continue;
+    }
     const Ray r = make_ray(V, px.px, px.py);
     const float tn = V.t_near, tf = V.t_far;
     float Y[16];
@@ -3016,8 +3027,8 @@ hipError_t launch_forward(const SceneDev &s, const ViewTable &vt, const MarchOpt
 hipError_t launch_backward(const SceneDev &s, const ViewTable &vt, const MarchOpts &op,
                            const BwdIn &in, const LaunchShape &ls, hipStream_t st) {
   MarchOpts o = op;
-  o.rest = op.replay_mode == 2 && op.sample_rec;
-  if (o.rest) {
+  o.either = op.replay_mode == 2 && op.sample_rec;
+  if (o.either) {
     const hipError_t e = bwd_launch<true>(s, vt, o, in, ls, st);
     if (e != hipSuccess) return e;
   }

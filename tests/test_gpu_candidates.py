@@ -365,3 +365,69 @@ def test_boxes_with_infinite_sides(torch_cuda, size, fov, tile, scales):
     assert torch.equal(rgb, brute) and torch.equal(T, brute_T)
     assert torch.equal(one, brute) and torch.equal(one_T, brute_T)
     r.check_errors()
+
+
+@pytest.mark.parametrize("n,eye,size,views,n_s,n_sg", [
+    (3_000, (0.0, 0.2, 2.6), (67, 45), 1, 8, 0),          # 4 lanes a ray
+    (3_000, (0.0, 0.2, 2.6), (61, 37), 2, 16, 0),
+    (3_000, (0.0, 0.2, 2.6), (45, 39), 1, 8, 7),
+    (30_000, (0.0, 0.2, 2.6), (253, 249), 1, 8, 0),       # 2 lanes
+    (20_000, None, (163, 129), 2, 8, 0),                  # one view inside, one outside
+    (3_000, (0.0, 0.2, 2.6), (403, 301), 1, 8, 0),        # one lane
+])
+@pytest.mark.parametrize("persistent", [False, True])
+def test_partly_recorded_forwards(torch_cuda, n, eye, size, views, n_s, n_sg, persistent):
+    """Record pools from 4 MB to 16 KB: from a few tiles without a record to a
+    few with one.  Images are unchanged, and the gradients are those of a
+    backward that searches every tile itself."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions, Renderer
+    sc = inputs.make_scene("cluster", n, 91, sh_degree=2 if n_sg else None, n_sg=n_sg)
+    keys = ("means", "log_scales", "quats", "density", "sh") + (("sg",) if n_sg else ())
+    p = {k: torch.from_numpy(sc[k]).cuda() for k in keys}
+    r = Renderer(0)
+    r.build(p, sc["sh_degree"])
+    eyes = [eye] * views if eye is not None else [(0.1, 0.2, 0.1), (0.0, 0.2, 2.6)]
+    cams = [inputs.look_at_camera(*size, e, target=(0.0, 0.1 * i, -0.1)) for i, e in enumerate(eyes)]
+    kw = dict(adaptive=True, n_s=n_s, ess=1, t_eps=1e-4, persistent=persistent)
+    own, st = r.new_state(), r.new_state()
+    rgb, T = r.forward(cams, RenderOptions(no_record=True, **kw), state=own)
+    g = torch.from_numpy(np.random.default_rng(3).standard_normal(tuple(rgb.shape)).astype(np.float32)).cuda()
+    ref = r.backward(own, rgb, T, g, None, p)
+    for limit in (1 << 22, 1 << 20, 1 << 18, 1 << 16, 1 << 14):
+        r.ctx.set_record_limit(limit)
+        for lean in (False, True):
+            rgb2, T2 = r.forward(cams, RenderOptions(no_sample_record=lean, **kw), state=st)
+            assert torch.equal(rgb, rgb2) and torch.equal(T, T2)
+            grads = r.backward(st, rgb, T, g, None, p)
+            assert r.ctx.backward_replayed()
+            for k in keys:
+                # the same terms in another order of the FP32 sums
+                assert float((grads[k] - ref[k]).norm()) <= 2e-5 * float(ref[k].norm()), (k, limit, lean)
+    r.check_errors()
+    r.close()
+
+
+@pytest.mark.parametrize("limit", [0, 1 << 20])
+def test_chunked_windows_of_shared_rays(torch_cuda, limit):
+    """Dense lists that come in several chunks, with 4 and 2 lanes a ray: the
+    replay reads the chunks again as it does with one lane."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene("cluster", 40_000, 33)
+    sc["log_scales"] += np.float32(0.7)
+    r, p = renderer_for(sc)
+    r.ctx.set_record_limit(limit)
+    for size in ((96, 72), (253, 249)):
+        cam = inputs.look_at_camera(*size, (0.9, 0.3, 2.2), fov_deg=50.0)
+        kw = dict(adaptive=True, ess=1, t_eps=1e-4, window_segments=4)
+        st, own = r.new_state(), r.new_state()
+        ref, ref_T, stats = r.forward([cam], RenderOptions(no_record=True, **kw), stats=True, state=own)
+        assert own.totals()["chunked"] > 0
+        rgb, T = r.forward([cam], RenderOptions(**kw), state=st)
+        assert torch.equal(rgb, ref) and torch.equal(T, ref_T)
+        g = torch.from_numpy(np.random.default_rng(5).standard_normal(tuple(rgb.shape)).astype(np.float32)).cuda()
+        a, b = r.backward(st, rgb, T, g, None, p), r.backward(own, ref, ref_T, g, None, p)
+        for k, v in b.items():
+            assert float((a[k] - v).norm()) <= 2e-5 * float(v.norm()), (k, size)
+    r.check_errors()
