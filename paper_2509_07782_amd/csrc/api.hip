@@ -86,11 +86,6 @@ struct rgx_bvh {
   std::vector<void *> retired;      // outgrown zview buffers: a captured graph may still use them
 };
 
-// Lanes per ray (choose_split).
-struct Split {
-  int outside = 1, inside = 1;   // views whose camera is outside / inside the means' bounds
-};
-
 // Forward state: what one forward rendered and what its searches found.
 struct rgx_fwd {
   rgx_context *ctx = nullptr;       // compared only: the state may outlive its context
@@ -556,32 +551,6 @@ struct MarchPlan {
   int64_t tiles = 0;       // record slots: the parts' tiles one after another
 };
 
-// How many lanes share a ray.  A 64-ray tile is one wave's serial march, and a
-// few tiles at a scene's silhouette take many times the mean, so a launch too
-// small to keep the chip busy beside them lasts as long as they do; tiles of
-// 16 or 32 rays shorten every march, at 2.5 or 1.5 times the total work.  The
-// lines lie where both sides were measured (ms forward, 1 / 2 / 4 lanes a
-// ray): 100k Gaussians, cluster, 512 tiles 5.4 / 3.4 / 1.7, 1536 tiles 3.9 /
-// 2.6 / 2.0, 2048 tiles 3.0 / 2.4 / 2.6, 4096 tiles 2.8 / 2.7 / 3.9, 6144 tiles
-// 2.8 / 3.5 / 5.3; 1M, 4096 tiles 12.8 / 9.9 / 9.2, 8192 tiles 11.8 / 10.7 /
-// 12.3, 12288 tiles 11.7 / 11.9 / 14.9; 5k large ones, 512 tiles 2.3 / 1.4 /
-// 1.3, 1024 tiles 1.9 / 1.8 / 2.3, 1536 tiles 1.8 / 2.2 / 3.0.  Where the
-// camera stands inside a dense scene every ray starts in the medium and the
-// tiles are alike (outdoor layout, forward + backward, 256 tiles: 300k 1.5 /
-// 1.3 / 1.3, 3M 5.1 / 4.4 / 5.2; 512 tiles: 2.5k 4.9 / 3.8 / 4.2, 100k 1.65 /
-// 1.59 / 1.79, 300k 1.45 / 1.52 / 1.69, 3M 5.2 / 5.9 / 6.8; 1024 tiles: 2.5k 4.6
-// / 4.8 / 6.2, 300k 1.7 / 1.9 / 2.6), so those views have lines of their own.
-static Split choose_split(const rgx_context *ctx, const rgx_bvh *b, const MarchOpts &m, int64_t tiles) {
-  Split s;
-  if (m.n_s < 4 || m.brute_force) return s;
-  const int64_t cu = ctx->n_cu;
-  if (tiles <= 2 * cu || (tiles <= 16 * cu && b->n >= 50 * tiles)) s.outside = 4;
-  else if (tiles <= 4 * cu || (tiles <= 32 * cu && b->n >= 24 * tiles)) s.outside = 2;
-  if (tiles <= cu) s.inside = 4;
-  else if (tiles <= 2 * cu && b->n <= 400 * tiles) s.inside = 2;
-  return s;
-}
-
 static int64_t count_tiles64(const rgx_camera *cams, int32_t n_views) {
   int64_t t = 0;
   for (int v = 0; v < n_views; v++) t += ((int64_t)cams[v].width * cams[v].height + 63) / 64;
@@ -692,7 +661,7 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
   const bool record = state && m.ess && !m.brute_force && !opts->no_record;
   // (the statistics are those of 64-ray waves)
   const int64_t tiles64 = count_tiles64(cams, n_views);
-  Split split = stats ? Split() : choose_split(ctx, bvh, m, tiles64);
+  Split split = stats || m.n_s < 4 || m.brute_force ? Split() : choose_split(ctx->n_cu, bvh->n, tiles64, state != nullptr);
   if (split.outside > 1 || split.inside > 1) {
     // captured after calls that took one lane a ray (more views, statistics,
     // another n): so does this one, with the tables and buffers they made

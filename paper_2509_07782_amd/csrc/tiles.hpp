@@ -1,10 +1,45 @@
-// Tiles of a view: the shape a split leaves of a 64-ray tile, and how a
-// tile's place in the view's grid is held (shared by host and device, without
-// either's headers).
+// Tiles of a view: how many lanes share a ray, the shape that leaves of a
+// 64-ray tile, and how a tile's place in the view's grid is held (shared by
+// host and device, without either's headers).
 #pragma once
 #include <cstdint>
 
 namespace rgx {
+
+// Lanes per ray of the views whose camera is outside / inside the means' bounds.
+struct Split {
+  int outside = 1, inside = 1;
+};
+
+// How many lanes share a ray in a call of `tiles` 64-ray tiles over n
+// Gaussians on a chip of `cu` CUs.  A 64-ray tile is one wave's serial march,
+// and a few tiles at a scene's silhouette take many times the mean, so a launch
+// too small to keep the chip busy beside them lasts as long as they do; tiles
+// of 16 or 32 rays shorten every march, at 2.5 or 1.5 times the total work.  The
+// lines lie where both sides were measured (ms forward, 1 / 2 / 4 lanes a
+// ray): 100k Gaussians, cluster, 512 tiles 5.4 / 3.4 / 1.7, 1536 tiles 3.9 /
+// 2.6 / 2.0, 2048 tiles 3.0 / 2.4 / 2.6, 4096 tiles 2.8 / 2.7 / 3.9, 6144 tiles
+// 2.8 / 3.5 / 5.3; 1M, 4096 tiles 12.8 / 9.9 / 9.2, 8192 tiles 11.8 / 10.7 /
+// 12.3, 12288 tiles 11.7 / 11.9 / 14.9; 5k large ones, 512 tiles 2.3 / 1.4 /
+// 1.3, 1024 tiles 1.9 / 1.8 / 2.3, 1536 tiles 1.8 / 2.2 / 3.0.  Where the
+// camera stands inside a dense scene every ray starts in the medium and the
+// tiles are alike, so those views have lines of their own (outdoor layout,
+// forward + backward): 192 tiles, 30k 10.7 / 7.3 / 5.1, 300k 1.65 / 1.39 /
+// 1.29, 3M 6.54 / 5.64 / 5.27; 256 tiles, 30k 11.2 / 8.0 / 6.0, 100k 1.78 / 1.58
+// / 1.42, 200k 1.45 / 1.32 / 1.34, 300k 1.63 / 1.45 / 1.50, 1M 2.04 / 1.77 /
+// 2.00, 3M 6.60 / 5.64 / 6.64; 512 tiles, 2.5k 4.9 / 3.8 / 4.2, 100k 1.65 / 1.59 /
+// 1.79, 300k 1.45 / 1.52 / 1.69, 3M 5.2 / 5.9 / 6.8; 1024 tiles, 2.5k 4.6 / 4.8 /
+// 6.2, 300k 1.7 / 1.9 / 2.6.  It is the backward that four lanes slow down there
+// (3M, 208 tiles: 3.5 / 3.0 / 3.8, forward 3.04 / 2.66 / 2.39): a forward
+// without a state, which none follows, takes them up to a tile a CU.
+inline Split choose_split(int64_t cu, int64_t n, int64_t tiles, bool backward) {
+  Split s;
+  if (tiles <= 2 * cu || (tiles <= 16 * cu && n >= 50 * tiles)) s.outside = 4;
+  else if (tiles <= 4 * cu || (tiles <= 32 * cu && n >= 24 * tiles)) s.outside = 2;
+  if (tiles <= cu) s.inside = !backward || 4 * tiles <= 3 * cu || n <= 400 * tiles ? 4 : 2;
+  else if (tiles <= 2 * cu && n <= 400 * tiles) s.inside = 2;
+  return s;
+}
 
 // Tiles of 64 / split rays: the tile shape loses its longer side's half per
 // factor of two.

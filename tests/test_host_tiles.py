@@ -1,5 +1,6 @@
-"""Tile shapes and tile-order words at the limits of accepted image sizes: the
-host-and-device header the library uses, compiled here for the host."""
+"""Tile shapes and tile-order words at the limits of accepted image sizes, and
+the rule for lanes sharing a ray: the host-and-device header the library uses,
+compiled here for the host."""
 import os
 import shutil
 import subprocess
@@ -49,12 +50,40 @@ int main() {
 }
 """
 
+LANES = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "tiles.hpp"
+using namespace rgx;
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+int main() {
+  // (CUs, Gaussians, 64-ray tiles): the fastest of 1, 2 and 4 lanes at the
+  // measured sizes on both sides of every line
+  for (bool back : {false, true}) {
+    CHECK(choose_split(256, 1000, 512, back).outside == 4 && choose_split(256, 1000, 1024, back).outside == 2);
+    CHECK(choose_split(256, 1000, 2048, back).outside == 1);
+    CHECK(choose_split(256, 1000000, 4096, back).outside == 4);
+    CHECK(choose_split(256, 1000000, 8192, back).outside == 2);
+    CHECK(choose_split(256, 1000000, 12288, back).outside == 1);
+    for (int64_t n : {30000, 300000, 3000000}) CHECK(choose_split(256, n, 192, back).inside == 4);
+    for (int64_t n : {30000, 100000}) CHECK(choose_split(256, n, 256, back).inside == 4);
+    for (int64_t n : {200000, 300000, 1000000, 3000000})
+      for (int64_t tiles : {208, 240, 256})
+        CHECK(choose_split(256, n, tiles, back).inside == (back ? 2 : 4));
+    CHECK(choose_split(256, 2500, 512, back).inside == 2 && choose_split(256, 300000, 512, back).inside == 1);
+    CHECK(choose_split(256, 2500, 1024, back).inside == 1);
+  }
+  return 0;
+}
+"""
 
-def test_tile_words_hold_every_accepted_image(tmp_path):
+
+@pytest.mark.parametrize("program", [PROGRAM, LANES], ids=["tiles", "lanes"])
+def test_tile_words_and_lane_rule(tmp_path, program):
     if shutil.which("g++") is None:
         pytest.skip("no host C++ compiler")
     src, exe = tmp_path / "tiles.cpp", tmp_path / "tiles"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)],
                    check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
