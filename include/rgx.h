@@ -162,7 +162,7 @@ enum {
   RGX_STAT_BOX_ONLY,     /* per ray, summed over its window collections: visited leaves whose
                             AABB meets the ray's window interval while the ellipsoid chord
                             does not (the AABB false positives) */
-  RGX_STAT_NODES,        /* BVH nodes loaded by the wave for the segment collections */
+  RGX_STAT_NODES,        /* 4-wide BVH nodes loaded by the wave for the segment collections */
   RGX_STAT_LEAVES,       /* leaves the wave visited for the segment collections */
   RGX_STAT_WINDOWS,      /* window collections the wave made (attempts included) */
   RGX_STAT_CHUNKED,      /* segments whose candidates were collected in several Z chunks */
@@ -185,7 +185,7 @@ enum {
   RGX_TOT_SAMPLES,       /* sum of RGX_STAT_SAMPLES */
   RGX_TOT_SEGMENTS,      /* sum of RGX_STAT_SEGMENTS */
   RGX_TOT_CLOSEST,       /* sum of RGX_STAT_CLOSEST */
-  RGX_TOT_NODES,         /* BVH nodes loaded for window collections, summed over waves */
+  RGX_TOT_NODES,         /* sum of RGX_STAT_NODES (a ray has its wave's count) */
   RGX_TOT_BOX_ONLY,      /* sum of RGX_STAT_BOX_ONLY (AABB-only leaves per window collection) */
   RGX_TOT_CHUNKED,       /* segments whose window list overflowed and was taken in Z chunks */
   RGX_TOT_INACTIVE,      /* Gaussians of the structure that are inactive */
@@ -367,14 +367,18 @@ rgx_status rgx_adam_step(rgx_context *ctx, const rgx_adam_group *groups, int32_t
                          int32_t *step, float beta1, float beta2, float eps, hipStream_t stream);
 
 /* Optional kernel timing, for measurement.  While enabled, every launch made
-   by rgx_build_bvh, rgx_render_forward and rgx_render_backward is bracketed
-   by two HIP events recorded on the caller's stream (so the interval is that
-   launch's duration on its own stream).  Do not enable it while a stream is
+   by rgx_build_bvh and rgx_render_forward, and the marches and the
+   finalisation of rgx_render_backward, are bracketed by two HIP events recorded
+   on the caller's stream (so the interval is their duration on that stream;
+   the fill that clears the gradient accumulators and the densification
+   statistic's launches are in none).  Do not enable it while a stream is
    being captured into a graph.  Enabling or disabling clears the record. */
 enum {
   RGX_KERN_BUILD = 0,    /* the whole build sequence of one rgx_build_bvh */
-  RGX_KERN_FORWARD,      /* one forward march launch (one per chunk of views) */
-  RGX_KERN_BACKWARD,     /* one backward march launch */
+  RGX_KERN_FORWARD,      /* the forward march of one chunk of views (up to 24): a launch, or two
+                            that share its views between them */
+  RGX_KERN_BACKWARD,     /* the backward march of one chunk of views: each of those launches, or
+                            two of which one does the work */
   RGX_KERN_FINALIZE,     /* gradient chain rule + scatter to user order */
   RGX_NKERN = 4
 };

@@ -75,7 +75,7 @@ static hipError_t timed(rgx_context *ctx, int kind, hipStream_t stream, F &&laun
 struct rgx_bvh {
   rgx_context *ctx = nullptr;
   int64_t n = 0, cap = 0;
-  int32_t sh_degree = 0, sh_k = 1, col_stride = 4, col_cap = 0;
+  int32_t sh_degree = 0, sh_k = 1;
   int32_t n_sg = 0;                 // spherical-Gaussian lobes per Gaussian
   float sigma_eps = 0.01f;
   int morton_bits = 21;
@@ -246,7 +246,6 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   }
   const int64_t n = g->n;
   const int sh_k = (g->sh_degree + 1) * (g->sh_degree + 1);
-  const int col_stride = kColFloats;   // fixed record length: the march reads it unconditionally
   const int64_t nb = (n + 4095) / 4096;
   const size_t nodes_n = (size_t)std::max<int64_t>(n - 1, 1);
   hipError_t e = hipSuccess;
@@ -263,7 +262,7 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   ENS(hist, (size_t)(nb + 1) * 256 * 4);
   ENS(geom, (size_t)n * kGeomFloats * 4);
   ENS(aabb, (size_t)n * 6 * 4);
-  ENS(col, (size_t)n * col_stride * 4);
+  ENS(col, (size_t)n * kColFloats * 4);   // (whatever the degree: the march reads all of it)
   ENS(nodes, nodes_n * 16 * 4);
   ENS(quads, nodes_n * kQuadFloats * 4);
   ENS(sup, (size_t)n * kSupFloats * 4);
@@ -286,7 +285,6 @@ rgx_status rgx_build_bvh(rgx_context *ctx, const rgx_gaussians *g, const rgx_bui
   b->serial = ++ctx->build_serial;
   b->sh_degree = g->sh_degree;
   b->sh_k = sh_k;
-  b->col_stride = col_stride;
   b->sigma_eps = sigma_eps;
   b->morton_bits = bits;
   b->n_sg = g->n_sg;
@@ -390,7 +388,6 @@ static rgx_status make_opts(rgx_context *ctx, const rgx_bvh *b, const rgx_render
   m.window_segments = o->window_segments ? o->window_segments : 1;
   for (int i = 0; i < 3; i++) m.bg[i] = o->bg[i];
   m.sh_k = b->sh_k;
-  m.col_stride = b->col_stride;
   if (b->n_sg > 0 && m.n_s != 8)
     return fail(ctx, RGX_ERR_UNSUPPORTED, "spherical-Gaussian colour lobes need n_s = 8");
   return RGX_OK;
@@ -636,7 +633,7 @@ static LaunchShape shape_for(rgx_context *ctx, const MarchOpts &m, int n_tiles, 
   LaunchShape ls;
   ls.queue = ctx->queue;
   ls.error_flag = ctx->queue + 8;
-  // one wave (one 64-ray tile) per workgroup
+  // one wave, one tile, per workgroup
   ls.grid = m.persistent ? std::min(n_tiles, ctx->n_cu * waves_per_cu) : n_tiles;
   if (ls.grid < 1) ls.grid = 1;
   return ls;

@@ -4,9 +4,10 @@
 // tree of the leaf boxes.  Every size follows from N on the host; the number
 // of active Gaussians stays on the device, so the whole build is asynchronous.
 // Bound by memory: 3.1 ms at 5M Gaussians (0.8 of them the sort), 0.71 ms at
-// 1M, and by 16 launches below 4096 (0.09 ms); with records made in user
-// order and gathered, one scanning workgroup, a launch for each tree level and
-// both forms of the 4-wide nodes it was 7.2, 1.54 and 0.22 ms.
+// 1M, and by nine launches (two more with lobes) up to 4096 (0.09 ms); with
+// records made in user order and gathered, one scanning workgroup, a launch for
+// each tree level and both forms of the 4-wide nodes it was 7.2, 1.54 and 0.22
+// ms.
 #include <algorithm>
 
 #include "common.hpp"
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(256) void k_records(int64_t P, const int32_t *__res
   geom[4 * i] = make_float4(mu[0], mu[1], mu[2], k2);
   geom[4 * i + 1] = make_float4(M[0], M[1], M[2], M[3]);
   geom[4 * i + 2] = make_float4(M[4], M[5], M[6], M[7]);
-  geom[4 * i + 3] = make_float4(M[8], p.sig, log2f(p.sig), rad);
+  geom[4 * i + 3] = make_float4(M[8], p.sig, log2f(p.sig), 0.0f);
   aux[2 * i] = make_float4(s[0], s[1], s[2], q[0] / qn);
   aux[2 * i + 1] = make_float4(q[1] / qn, q[2] / qn, q[3] / qn, qn);
   // N = k S R^T

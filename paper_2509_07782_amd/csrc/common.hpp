@@ -6,7 +6,7 @@
 namespace rgx {
 
 constexpr int kWave = 64;
-constexpr int kBlock = 256;               // 4 waves, each owning its own 64-ray tile
+constexpr int kBlock = 256;               // of the build's kernels (a march's workgroup is one wave)
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxViewsPerLaunch = 24;    // view table travels as a kernel argument
 constexpr int kGeomFloats = 16;           // packed geometry record (64 B)
@@ -39,10 +39,9 @@ constexpr int kSgUserFloats = 7;          // user lobe: amplitude rgb, axis xyz,
 constexpr int kSgAccFloats = 64;          // per Gaussian: 8 slots per lobe (da rgb, dlambda, h xyz, pad)
 constexpr int32_t kNoChild = INT32_MIN;
 
-// Packed geometry record, Z order: [mu.xyz, k^2, M (3x3 row-major), sigma~, log2 sigma~, pad]
+// Packed geometry record, Z order: [mu.xyz, k^2, M (3x3 row-major), sigma~, log2 sigma~, 0]
 // with M = S^-1 R^T so that q = |M (x - mu)|^2.
-// G_RAD: radius of a sphere around the mean holding the whole ellipsoid
-enum GeomSlot { G_MU = 0, G_K2 = 3, G_M = 4, G_SIG = 13, G_L2SIG = 14, G_RAD = 15 };
+enum GeomSlot { G_MU = 0, G_K2 = 3, G_M = 4, G_SIG = 13, G_L2SIG = 14 };
 
 // per-ray statistics slots (same order as the public RGX_STAT_* enum)
 enum { ST_Q = 0, ST_P, ST_SAMPLES, ST_SEGMENTS, ST_CLOSEST, ST_BOX_ONLY, ST_NODES, ST_LEAVES,
@@ -83,7 +82,6 @@ struct MarchOpts {
   int32_t window_segments;
   float bg[3];
   int32_t sh_k;           // SH coefficients per channel
-  int32_t col_stride;     // floats per packed colour record
   // closest-hit replay: the forward records each ray's first kReplayK
   // closest-hit results, a backward of the same rays replays them
   int32_t replay_mode;    // 0 off, 1 record, 2 replay

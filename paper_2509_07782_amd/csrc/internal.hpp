@@ -45,7 +45,7 @@ hipError_t launch_isotropic_loss(int64_t n, const float *log_scales, float r0, f
 
 struct SceneDev {
   const float *geom;          // [n,16]
-  const float *col;           // [n,col_stride]
+  const float *col;           // [n,kColFloats]
   const float *nodes;         // [max(n-1,1),16]
   const float *quads;         // [max(n-1,1),32] 4-wide nodes, one per binary internal node
   const float *sup;           // [n,16] leaf-test records
@@ -83,7 +83,8 @@ struct LaunchShape {
 };
 
 // Resident one-wave workgroups per CU of the march kernels (their launch
-// bounds and LDS use), used to size persistent grids.
+// bounds and LDS use), used to size persistent grids; at 16 samples a segment
+// those of the forward with one lane a ray.
 constexpr int kLdsBytes = 160 * 1024, kBwdWavesPerCu = 8;
 inline int fwd_waves_per_cu(const MarchOpts &m) { return m.n_s <= 8 ? 12 : 8; }
 inline int bwd_waves_per_cu() { return kBwdWavesPerCu; }

@@ -75,7 +75,7 @@ __device__ __forceinline__ float ray_box_entry(const vf4 &q0, const vf4 &q1, con
 struct Gauss {
   float mx, my, mz, k2;
   float m[9];
-  float sig, l2sig, rad;   // rad: bounding-sphere radius of the ellipsoid
+  float sig, l2sig;
   float ox, oy, oz;        // the camera centre in the local frame, M (o - mu) (with_origin)
 };
 
@@ -95,7 +95,7 @@ __device__ __forceinline__ Gauss load_gauss(const float *geom, int j) {
   g.mx = a.x; g.my = a.y; g.mz = a.z; g.k2 = a.w;
   g.m[0] = b.x; g.m[1] = b.y; g.m[2] = b.z; g.m[3] = b.w;
   g.m[4] = c.x; g.m[5] = c.y; g.m[6] = c.z; g.m[7] = c.w;
-  g.m[8] = d.x; g.sig = d.y; g.l2sig = d.z; g.rad = d.w;
+  g.m[8] = d.x; g.sig = d.y; g.l2sig = d.z;
   return g;
 }
 
@@ -897,7 +897,7 @@ __device__ __forceinline__ Gauss load_gauss_lane(const float *geom, int j) {
   g.mx = a.x; g.my = a.y; g.mz = a.z; g.k2 = a.w;
   g.m[0] = b.x; g.m[1] = b.y; g.m[2] = b.z; g.m[3] = b.w;
   g.m[4] = c.x; g.m[5] = c.y; g.m[6] = c.z; g.m[7] = c.w;
-  g.m[8] = d.x; g.sig = d.y; g.l2sig = d.z; g.rad = d.w;
+  g.m[8] = d.x; g.sig = d.y; g.l2sig = d.z;
   return g;
 }
 
