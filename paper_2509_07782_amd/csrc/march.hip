@@ -1,8 +1,9 @@
 // Forward and backward ray marching through the Gaussian field (Sec. 3.1
 // Eq. 1-3; Sec. 3.2 Algorithm 1, Eq. 4-5).
 //
-// Execution model: one wave64 (one workgroup) owns one tile of 64 rays.  Each
-// lane marches its ray segment by segment (Alg. 1).  Candidate Gaussians come
+// Execution model: one wave64 (one workgroup) owns one tile of 64 rays, or in
+// small calls of 32 or 16, each shared by 2 or 4 lanes that take its samples
+// between them.  Each lane marches its ray segment by segment (Alg. 1).  Candidate Gaussians come
 // from a per-wave window list: for a depth window covering one or more
 // segments of every live lane, a node-parallel walk of the LBVH gathers the
 // Gaussians that may meet the packet of rays in its windows, each with
@@ -1346,8 +1347,9 @@ __device__ __forceinline__ int trav_run(const SceneDev &s, WaveMem &M, const Ray
       staged += totL;
     }
     const bool done = sp == 0;
-    // tests of staged leaves, 64 at a time, in staging order: the bounding
-    // sphere of the ellipsoid against the packet gives the entry's depth bounds
+    // tests of staged leaves, 64 at a time, in staging order: the ellipsoid
+    // (for a packet too wide, its bounding sphere) against the packet gives the
+    // entry's depth bounds
     int head = 0;
     while (staged - head >= 64 || (done && staged > head)) {
       __builtin_amdgcn_wave_barrier();
@@ -2487,13 +2489,14 @@ __device__ __forceinline__ void sg_slots(const float *sg, float *sgacc, int j, f
 
 // ---------------------------------------------------------------------------
 // Backward kernel: replays the forward's segments from the same window lists
-// (or brute force / depth-first sources) in the same order, takes each
+// (or brute force) in the same order, takes each
 // segment's per-sample sums from the forward's record (or sums them again
 // where there is none), recomputes the transmittance before every sample,
 // derives dL/dsigma_k and dL/dW_k, then revisits the Gaussians some lane hit
 // for their parameter adjoints.  The 16
-// geometry and density slots are summed over the wave (DPP and half-wave
-// swaps) before one atomic per slot; the SH-coefficient slots, a per-ray
+// geometry and density slots are summed over the wave (through LDS, or by DPP
+// and half-wave swaps), four Gaussians' to one atomic instruction; the
+// SH-coefficient slots, a per-ray
 // constant times one scalar per (ray, Gaussian), are staged 16 Gaussians at a
 // time and multiplied out on the matrix cores.
 
