@@ -100,7 +100,7 @@ struct rgx_fwd {
   bool recorded = false;            // closest hits and window lists recorded
   bool has_totals = false;          // statistics totals reduced into `totals`
   DevBuf replay;                    // [rays][kReplayK] closest-hit results
-  DevBuf wrec;                      // window-list pool (64-bit counter first)
+  DevBuf wrec;                      // record pool (counters first, kWrecLine)
   uint32_t wrec_cap = 0;            // dwords of it that forward could use
   DevBuf wrec_tile;                 // per tile: (complete, first record)
   DevBuf totals;                    // int64 [RGX_NTOT]
@@ -595,7 +595,7 @@ static rgx_status make_plan(rgx_context *ctx, const MarchOpts &m, Split split, c
 // window lists, as much again for the per-sample sums at N_s <= 8 (twice that
 // at 16), all twice for tiles of fewer rays, which share less; at least 64 MB
 // so that a call of few tiles with long window lists still records them all;
-// and within the caller's cap (the two counter dwords always fit).
+// and within the caller's cap (one counter's line always fits).
 static size_t record_pool(const rgx_context *ctx, const rgx_render_opts *o, Split split, int64_t tiles64) {
   const size_t per_tile = (size_t)kWrecDwordsPerTile +
                           (o->no_sample_record ? 0 : (size_t)kSrecDwordsPerTile * (o->n_s > 8 ? 2 : 1));
@@ -603,8 +603,13 @@ static size_t record_pool(const rgx_context *ctx, const rgx_render_opts *o, Spli
   size_t pool = std::min<size_t>(std::max<size_t>(2 + (size_t)tiles64 * per_tile * shared, (size_t)1 << 24),
                                  0xfffffff0u);
   if (ctx->record_limit > 0)
-    pool = std::max<size_t>(std::min<size_t>(pool, (size_t)ctx->record_limit / sizeof(uint32_t)), 2);
+    pool = std::max<size_t>(std::min<size_t>(pool, (size_t)ctx->record_limit / sizeof(uint32_t)), kWrecLine);
   return pool;
+}
+
+// Shares of a pool: at least 64K dwords each, many times the largest record.
+static uint32_t record_shares(uint32_t pool) {
+  return std::min<uint32_t>(std::max<uint32_t>(pool >> 16, 1), kWrecMaxShares);
 }
 
 // Whether a forward with this split finds its tile tables and (recording into
@@ -707,10 +712,9 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
       m.wrec_tile = (uint32_t *)f->wrec_tile.p;
       m.wrec_cap = f->wrec_cap = (uint32_t)pool;
       m.sample_rec = opts->no_sample_record ? 0 : 1;
-      // the pool's 64-bit allocation counter (dwords 0-1) starts past itself
-      // (fill kernels, not memset nodes, so the call can be captured)
-      hipError_t e = launch_fill(f->wrec.p, 1, 2u, stream);
-      if (e == hipSuccess) e = launch_fill((uint32_t *)f->wrec.p + 1, 1, 0u, stream);
+      m.wrec_shares = record_shares(m.wrec_cap);
+      // (a fill kernel, not a memset node, so the call can be captured)
+      const hipError_t e = launch_fill(f->wrec.p, kWrecLine * m.wrec_shares, 0u, stream);
       if (e != hipSuccess) {
         if (!*state) rgx_fwd_destroy(f);
         return hip_fail(ctx, e, "record reset");
@@ -734,6 +738,7 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
         pm.wrec = m.wrec;
         pm.wrec_tile = m.wrec_tile;
         pm.wrec_cap = m.wrec_cap;
+        pm.wrec_shares = m.wrec_shares;
         pm.sample_rec = m.sample_rec;
         const ViewTable &t = part.tabs[k];
         if (e == hipSuccess)

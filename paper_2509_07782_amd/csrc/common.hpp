@@ -86,9 +86,10 @@ struct MarchOpts {
   // closest-hit results, a backward of the same rays replays them
   int32_t replay_mode;    // 0 off, 1 record, 2 replay
   float *replay;          // [rays of the call][kReplayK]
-  uint32_t *wrec;         // window-list record pool: [0,2) 64-bit allocation counter, records after
+  uint32_t *wrec;         // window-list record pool (kWrecLine)
   uint32_t *wrec_tile;    // per tile of the call: (complete, first chunk offset)
   uint32_t wrec_cap;      // pool size in dwords
+  uint32_t wrec_shares;   // shares of the pool, each with an allocation counter
   int32_t sample_rec;     // the record also holds each segment step's per-sample sums
   int32_t either;         // backward: the record says which of two launches works
 };
@@ -102,6 +103,17 @@ constexpr int kReplayK = 4;
 // incomplete and is not replayed.
 constexpr int kWrecHeader = 7;
 constexpr uint32_t kWrecNone = 0xffffffffu;
+// The pool: a line of kWrecLine dwords for each share, its 64-bit allocation
+// counter first (and in share 0's line kWrecFull: set once a record found no
+// room), then the shares' dwords, equal parts.  A tile starts in the share of
+// its number and goes on to the next one when that is full.  With one counter
+// for all, a recording forward of many short steps waited in its queue, twice
+// or four times as long where rays are shared between lanes: 1k large
+// Gaussians, 1020 64-ray tiles, two lanes a ray, forward 0.69 ms without a
+// record, 1.75 with one (1.16 with one lane a ray) and 0.79 with 64 counters;
+// 100k, 400x300, four lanes, 1.63, 2.38 and 1.73.  16 counters and 512 give the
+// same; blocks of several records to a tile left part of the pool unused.
+constexpr int kWrecLine = 64, kWrecFull = 2, kWrecMaxShares = 64;
 // Sample record: after every segment step of a tile the forward appends
 // [next, hit-lane mask (2 dwords), empty-lane mask (2 dwords)], then for the
 // lanes whose segment hit some Gaussian the per-sample sums sigma_k and the

@@ -1756,7 +1756,7 @@ __device__ __forceinline__ void for_each_candidate(int kind, const SceneDev &s, 
 struct WinRec {
   uint32_t *slot = nullptr;   // the tile's (complete, first record) pair
   uint32_t cur = kWrecNone;   // replay: next record to read; record: last record written
-  uint32_t first = kWrecNone; // record: first record
+  uint32_t share = 0;         // record: share of the pool its records come from
   bool ok = false;            // record: nothing dropped so far; replay: tile complete
 };
 
@@ -1764,10 +1764,11 @@ __device__ __forceinline__ void rec_start(WinRec &R, const MarchOpts &op, const 
                                           int w) {
   R.slot = op.replay_mode ? op.wrec_tile + 2 * (size_t)(vt.tile0 + w) : nullptr;
   R.cur = kWrecNone;
-  R.first = kWrecNone;
   R.ok = false;
   if (op.replay_mode == 1) {
     R.ok = true;
+    R.share = (uint32_t)(vt.tile0 + w) % op.wrec_shares;
+    if (__lane_id() == 0) R.slot[1] = kWrecNone;
   } else if (op.replay_mode == 2) {
     R.ok = uniform_int((int)R.slot[0]) == 1;
     R.cur = (uint32_t)uniform_int((int)R.slot[1]);
@@ -1777,29 +1778,38 @@ __device__ __forceinline__ void rec_start(WinRec &R, const MarchOpts &op, const 
 // forward: the tile's status once all its records are in
 __device__ __forceinline__ void rec_finish(WinRec &R, const MarchOpts &op, int lane) {
   if (op.replay_mode != 1) return;
-  if (lane == 0) {
-    R.slot[0] = R.ok ? 1u : 0u;
-    R.slot[1] = R.first;
-  }
+  if (lane == 0) R.slot[0] = R.ok ? 1u : 0u;
 }
 
 // Appends a record of `size` dwords to the tile's chain; kWrecNone (and the
 // tile marked incomplete) when the pool is full.
 __device__ __forceinline__ uint32_t rec_alloc(WinRec &R, const MarchOpts &op, uint32_t size,
                                               int lane) {
-  // a 64-bit allocation counter (pool dwords 0-1): failed allocations keep
-  // adding to it, and it must not wrap back into the pool
-  unsigned long long got = 0;
-  if (lane == 0) got = atomicAdd(reinterpret_cast<unsigned long long *>(op.wrec), (unsigned long long)size);
-  const uint64_t at = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(got >> 32)) << 32) |
-                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
-  if (at + size > op.wrec_cap) { R.ok = false; return kWrecNone; }
-  const uint32_t off = (uint32_t)at;
+  const uint32_t head = (uint32_t)kWrecLine * op.wrec_shares, len = (op.wrec_cap - head) / op.wrec_shares;
+  uint64_t at = 0;
+  for (uint32_t tries = 0;; tries++) {
+    if (tries == op.wrec_shares) {
+      if (lane == 0) op.wrec[kWrecFull] = 1u;
+      R.ok = false;
+      return kWrecNone;
+    }
+    // a 64-bit counter: failed allocations keep adding to it, and it must not
+    // wrap back into the share
+    unsigned long long got = 0;
+    if (lane == 0)
+      got = atomicAdd(reinterpret_cast<unsigned long long *>(op.wrec + kWrecLine * R.share), (unsigned long long)size);
+    at = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(got >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
+    if (at + size <= len) break;
+    R.share = R.share + 1 == op.wrec_shares ? 0 : R.share + 1;
+  }
+  const uint32_t off = head + len * R.share + (uint32_t)at;
   if (lane == 0) {
     op.wrec[off] = kWrecNone;
-    if (R.cur != kWrecNone) op.wrec[R.cur] = off;   // link from the previous record
+    // link from the previous record, or the tile's slot
+    uint32_t *from = R.cur != kWrecNone ? op.wrec + R.cur : R.slot + 1;
+    *from = off;
   }
-  if (R.first == kWrecNone) R.first = off;
   R.cur = off;
   return off;
 }
@@ -2535,8 +2545,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
   const bool grid = !op.adaptive && op.ess != 2;
   if (!marches_any(s, op, vt)) return;
   if (op.either) {
-    const bool all = *reinterpret_cast<const unsigned long long *>(op.wrec) <= op.wrec_cap;
-    if (REPLAY != all) return;
+    if (REPLAY != (op.wrec[kWrecFull] == 0u)) return;
   }
   bool first = true;
   for (;;) {

@@ -431,3 +431,27 @@ def test_chunked_windows_of_shared_rays(torch_cuda, limit):
         for k, v in b.items():
             assert float((a[k] - v).norm()) <= 2e-5 * float(v.norm()), (k, size)
     r.check_errors()
+
+
+@pytest.mark.parametrize("limit,whole", [(0, True), (1 << 22, False)])
+def test_records_of_one_tile_in_many_shares(torch_cuda, limit, whole):
+    """One tile whose records (several MB) fill one share of the pool after
+    another: recorded whole in the default pool, not in a smaller one, and the
+    gradients are those of a backward that searches."""
+    torch = torch_cuda
+    from paper_2509_07782_amd.render import RenderOptions
+    sc = inputs.make_scene("cluster", 20_000, 37)
+    cam = inputs.look_at_camera(8, 8, (0.2, 0.1, 2.4), fov_deg=30.0)
+    r, p = renderer_for(sc)
+    r.ctx.set_record_limit(limit)
+    kw = dict(dt=0.0005, ess=1, t_eps=0.0)
+    st, own = r.new_state(), r.new_state()
+    ref, ref_T = r.forward([cam], RenderOptions(no_record=True, **kw), state=own)
+    rgb, T, _ = r.forward([cam], RenderOptions(**kw), stats=True, state=st)
+    assert st.totals()["unrecorded"] == (0 if whole else 1)
+    assert torch.equal(rgb, ref) and torch.equal(T, ref_T)
+    g = torch.from_numpy(np.random.default_rng(6).standard_normal((64, 3)).astype(np.float32)).cuda()
+    a, b = r.backward(st, rgb, T, g, None, p), r.backward(own, ref, ref_T, g, None, p)
+    for k, v in b.items():
+        assert float((a[k] - v).norm()) <= 2e-5 * float(v.norm()), k
+    r.check_errors()
