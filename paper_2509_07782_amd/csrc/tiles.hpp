@@ -19,8 +19,13 @@ struct Split {
 // lines lie where both sides were measured (ms forward, 1 / 2 / 4 lanes a
 // ray): 100k Gaussians, cluster, 512 tiles 5.4 / 3.4 / 1.7, 1536 tiles 3.9 /
 // 2.6 / 2.0, 2048 tiles 3.0 / 2.4 / 2.6, 4096 tiles 2.8 / 2.7 / 3.9, 6144 tiles
-// 2.8 / 3.5 / 5.3; 1M, 4096 tiles 12.8 / 9.9 / 9.2, 8192 tiles 11.8 / 10.7 /
-// 12.3, 12288 tiles 11.7 / 11.9 / 14.9; 5k large ones, 512 tiles 2.3 / 1.4 /
+// 2.8 / 3.5 / 5.3; 1M, 8192 tiles 11.8 / 10.7 / 12.3, 12288 tiles 11.7 / 11.9 /
+// 14.9; with the record and a backward, 2600 tiles, 210k 8.7 / 6.3 / 6.2, 1M 23.8
+// / 17.2 / 14.8; 3000 tiles, 2 and 4 lanes, 210k 6.2 / 6.4, 400k 9.4 / 8.8, 700k
+// 13.0 / 11.8; 3300 tiles, 210k 8.5 / 6.8 / 7.1, 400k 11.6 / 9.1 / 9.3 (a fixed step
+// 11.1 / 8.8 / 10.0), 1M 24.1 / 18.0 / 17.1; 4090 tiles, 210k 7.8 / 6.4 / 7.6, 400k
+// 11.9 / 9.2 / 11.0 (10.5 / 9.6 / 10.8), 700k 16.3 / 13.0 / 13.6 (17.2 / 14.4 /
+// 14.0), 1M 25.0 / 17.4 / 16.9; 5k large ones, 512 tiles 2.3 / 1.4 /
 // 1.3, 1024 tiles 1.9 / 1.8 / 2.3, 1536 tiles 1.8 / 2.2 / 3.0.  Where the
 // camera stands inside a dense scene every ray starts in the medium and the
 // tiles are alike, so those views have lines of their own (outdoor layout,
@@ -34,7 +39,8 @@ struct Split {
 // without a state, which none follows, takes them up to a tile a CU.
 inline Split choose_split(int64_t cu, int64_t n, int64_t tiles, bool backward) {
   Split s;
-  if (tiles <= 2 * cu || (tiles <= 16 * cu && n >= 50 * tiles)) s.outside = 4;
+  if (tiles <= 2 * cu || (tiles <= 12 * cu && n >= 50 * tiles) || (tiles <= 16 * cu && n >= 160 * tiles))
+    s.outside = 4;
   else if (tiles <= 4 * cu || (tiles <= 32 * cu && n >= 24 * tiles)) s.outside = 2;
   if (tiles <= cu) s.inside = !backward || 4 * tiles <= 3 * cu || n <= 400 * tiles ? 4 : 2;
   else if (tiles <= 2 * cu && n <= 400 * tiles) s.inside = 2;

@@ -62,7 +62,11 @@ int main() {
   for (bool back : {false, true}) {
     CHECK(choose_split(256, 1000, 512, back).outside == 4 && choose_split(256, 1000, 1024, back).outside == 2);
     CHECK(choose_split(256, 1000, 2048, back).outside == 1);
-    CHECK(choose_split(256, 1000000, 4096, back).outside == 4);
+    for (int64_t n : {210000, 400000, 700000}) CHECK(choose_split(256, n, 3000, back).outside == 4);
+    CHECK(choose_split(256, 700000, 4090, back).outside == 4);
+    for (int64_t n : {210000, 400000})
+      for (int64_t tiles : {3300, 4090}) CHECK(choose_split(256, n, tiles, back).outside == 2);
+    CHECK(choose_split(256, 1000000, 3300, back).outside == 4 && choose_split(256, 1000000, 4096, back).outside == 4);
     CHECK(choose_split(256, 1000000, 8192, back).outside == 2);
     CHECK(choose_split(256, 1000000, 12288, back).outside == 1);
     for (int64_t n : {30000, 300000, 3000000}) CHECK(choose_split(256, n, 192, back).inside == 4);
