@@ -607,9 +607,12 @@ static size_t record_pool(const rgx_context *ctx, const rgx_render_opts *o, Spli
   return pool;
 }
 
-// Shares of a pool: at least 64K dwords each, many times the largest record.
-static uint32_t record_shares(uint32_t pool) {
-  return std::min<uint32_t>(std::max<uint32_t>(pool >> 16, 1), kWrecMaxShares);
+// Divides the pool into shares: at least 64K dwords each, many times the
+// largest record, where there are two or more.
+static void share_pool(MarchOpts &m) {
+  m.wrec_shares = 1;
+  while (m.wrec_shares < (uint32_t)kWrecMaxShares && m.wrec_cap >> 17 >= m.wrec_shares) m.wrec_shares *= 2;
+  m.wrec_len = (m.wrec_cap - kWrecLine * m.wrec_shares) / m.wrec_shares;
 }
 
 // Whether a forward with this split finds its tile tables and (recording into
@@ -712,7 +715,7 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
       m.wrec_tile = (uint32_t *)f->wrec_tile.p;
       m.wrec_cap = f->wrec_cap = (uint32_t)pool;
       m.sample_rec = opts->no_sample_record ? 0 : 1;
-      m.wrec_shares = record_shares(m.wrec_cap);
+      share_pool(m);
       // (a fill kernel, not a memset node, so the call can be captured)
       const hipError_t e = launch_fill(f->wrec.p, kWrecLine * m.wrec_shares, 0u, stream);
       if (e != hipSuccess) {
@@ -739,6 +742,7 @@ rgx_status rgx_render_forward(rgx_context *ctx, const rgx_bvh *bvh, const rgx_ca
         pm.wrec_tile = m.wrec_tile;
         pm.wrec_cap = m.wrec_cap;
         pm.wrec_shares = m.wrec_shares;
+        pm.wrec_len = m.wrec_len;
         pm.sample_rec = m.sample_rec;
         const ViewTable &t = part.tabs[k];
         if (e == hipSuccess)

@@ -1767,7 +1767,7 @@ __device__ __forceinline__ void rec_start(WinRec &R, const MarchOpts &op, const 
   R.ok = false;
   if (op.replay_mode == 1) {
     R.ok = true;
-    R.share = (uint32_t)(vt.tile0 + w) % op.wrec_shares;
+    R.share = (uint32_t)(vt.tile0 + w) & (op.wrec_shares - 1);
     if (__lane_id() == 0) R.slot[1] = kWrecNone;
   } else if (op.replay_mode == 2) {
     R.ok = uniform_int((int)R.slot[0]) == 1;
@@ -1785,7 +1785,6 @@ __device__ __forceinline__ void rec_finish(WinRec &R, const MarchOpts &op, int l
 // tile marked incomplete) when the pool is full.
 __device__ __forceinline__ uint32_t rec_alloc(WinRec &R, const MarchOpts &op, uint32_t size,
                                               int lane) {
-  const uint32_t head = (uint32_t)kWrecLine * op.wrec_shares, len = (op.wrec_cap - head) / op.wrec_shares;
   uint64_t at = 0;
   for (uint32_t tries = 0;; tries++) {
     if (tries == op.wrec_shares) {
@@ -1800,10 +1799,10 @@ __device__ __forceinline__ uint32_t rec_alloc(WinRec &R, const MarchOpts &op, ui
       got = atomicAdd(reinterpret_cast<unsigned long long *>(op.wrec + kWrecLine * R.share), (unsigned long long)size);
     at = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(got >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
-    if (at + size <= len) break;
-    R.share = R.share + 1 == op.wrec_shares ? 0 : R.share + 1;
+    if (at + size <= op.wrec_len) break;
+    R.share = (R.share + 1) & (op.wrec_shares - 1);
   }
-  const uint32_t off = head + len * R.share + (uint32_t)at;
+  const uint32_t off = (uint32_t)kWrecLine * op.wrec_shares + op.wrec_len * R.share + (uint32_t)at;
   if (lane == 0) {
     op.wrec[off] = kWrecNone;
     // link from the previous record, or the tile's slot
