@@ -1760,16 +1760,18 @@ struct WinRec {
   bool ok = false;            // record: nothing dropped so far; replay: tile complete
 };
 
+// FORWARD: to be recorded if the options say so; else to be replayed.
+template <bool FORWARD>
 __device__ __forceinline__ void rec_start(WinRec &R, const MarchOpts &op, const ViewTable &vt,
                                           int w) {
   R.slot = op.replay_mode ? op.wrec_tile + 2 * (size_t)(vt.tile0 + w) : nullptr;
   R.cur = kWrecNone;
   R.ok = false;
-  if (op.replay_mode == 1) {
+  if (FORWARD && op.replay_mode == 1) {
     R.ok = true;
     R.share = (uint32_t)(vt.tile0 + w) & (op.wrec_shares - 1);
     if (__lane_id() == 0) R.slot[1] = kWrecNone;
-  } else if (op.replay_mode == 2) {
+  } else if (!FORWARD && op.replay_mode == 2) {
     R.ok = uniform_int((int)R.slot[0]) == 1;
     R.cur = (uint32_t)uniform_int((int)R.slot[1]);
   }
@@ -2244,7 +2246,7 @@ __global__ __launch_bounds__(kWave, NS / S <= 8 ? 3 : 2) void k_forward(SceneDev
     SegState ss;
     int n_closest = 0;   // closest-hit queries of this lane's ray so far
     WinRec rec;
-    rec_start(rec, op, vt, w);
+    rec_start<true>(rec, op, vt, w);
     ss.alive = px.valid;
     ss.pending = op.ess && px.valid;
     ss.seg_i = 0;
@@ -2563,7 +2565,7 @@ __global__ __launch_bounds__(kWave, 2) void k_backward(SceneDev s, ViewTable vt,
     const View &V = vt.v[px.view];
     if (!marches_view(s, op, V)) continue;
     WinRec rec;
-    rec_start(rec, op, vt, w);
+    rec_start<false>(rec, op, vt, w);
     if (REPLAY && !rec.ok) {   // (cannot happen)
       if (ls.error_flag) *ls.error_flag = 5;
       continue;
