@@ -89,10 +89,10 @@ struct MarchOpts {
   uint32_t *wrec;         // window-list record pool (kWrecLine)
   uint32_t *wrec_tile;    // per tile of the call: (complete, first chunk offset)
   uint32_t wrec_cap;      // pool size in dwords
-  int32_t sample_rec;     // the record also holds each segment step's per-sample sums
-  int32_t either;         // backward: the record says which of two launches works
   uint32_t wrec_shares;   // shares of the pool, each with an allocation counter (a power of two)
   uint32_t wrec_len;      // dwords of a share
+  int32_t sample_rec;     // the record also holds each segment step's per-sample sums
+  int32_t either;         // backward: the record says which of two launches works
 };
 // all views, or those whose camera lies inside / outside the bounds of the means
 enum { VIEWS_ALL = 0, VIEWS_INSIDE, VIEWS_OUTSIDE };
