@@ -395,7 +395,7 @@ int32_t rgx_backward_replayed(const rgx_context *ctx);
 /* (host) Caps the record pool of every later forward given a state on this
    context at max_bytes (0: no cap beyond the default sizing, which is 96 KB
    per 64 rays at N_s <= 8, 192 KB for small calls, at least 64 MB, at most
-   16 GiB).  Tiles whose records do
+   16 GiB); 256 bytes are held whatever the cap.  Tiles whose records do
    not fit are not recorded (RGX_TOT_UNRECORDED counts them) and their
    backward searches and sums again, with the same results, so a cap trades
    backward time for device memory and never changes results.
